@@ -17,6 +17,7 @@
 #include "lsgd_host.hpp"
 #include "lsgd_np2.hpp"
 #include "lsgd_plan_kernels.hpp"
+#include "lsgd_pow2.hpp"
 
 struct lsgd_plan {
     int device;
@@ -44,9 +45,6 @@ struct lsgd_plan {
 
 namespace lsgd {
 namespace {
-
-using PlanKernel = void (*)(PlanArgs);
-using LarsKernel = void (*)(LarsArgs);
 
 // LARS scratch: each tensor's slice of the mean-gradient scratch starts on a
 // 64-float (256-byte) boundary.
@@ -78,73 +76,12 @@ PlanKernel plan_seg(int max_count, bool cached) {
     return step_plan_seg<GT, 8, 0>;
 }
 
-template <typename GT, int W, int G>
-PlanKernel plan_ct(bool cached) {
-    constexpr int U = tile_units<GT>(W * G, G);
-    if constexpr (cached_state_for(W * G))
-        if (cached) return plan_step_kernel<GT, W, G, U, 1>();
-    return plan_step_kernel<GT, W, G, U, 0>();
-}
-
-template <typename GT, int W>
-PlanKernel pick_plan_g(int G, bool cached) {
-    switch (G) {
-        case 1: return plan_ct<GT, W, 1>(cached);
-        case 2: return plan_ct<GT, W, 2>(cached);
-        case 4: return plan_ct<GT, W, 4>(cached);
-        case 8: return plan_ct<GT, W, 8>(cached);
-        case 16:
-            if constexpr (W * 16 <= kMaxWorkers) return plan_ct<GT, W, 16>(cached);
-            else return nullptr;
-        case 32:
-            if constexpr (W <= 4) return plan_ct<GT, W, 32>(cached);
-            else return nullptr;
-        case 64:
-            if constexpr (W <= 2) return plan_ct<GT, W, 64>(cached);
-            else return nullptr;
-        case 128:
-            if constexpr (W == 1) return plan_ct<GT, W, 128>(cached);
-            else return nullptr;
-    }
-    return nullptr;
-}
-
-// Groups of 32 to 128 workers, in up to 4 groups.
-template <typename GT, int W>
-PlanKernel pick_plan_big_w(int G, bool cached) {
-    switch (G) {
-        case 1: return plan_ct<GT, W, 1>(cached);
-        case 2:
-            if constexpr (W * 2 <= kMaxWorkers) return plan_ct<GT, W, 2>(cached);
-            else return nullptr;
-        case 4:
-            if constexpr (W * 4 <= kMaxWorkers) return plan_ct<GT, W, 4>(cached);
-            else return nullptr;
-    }
-    return nullptr;
-}
-
 // The plan kernel for (W, G): compile-time for the power-of-two groupings of
 // pick_flat (lsgd_flat.hip), with parameters and momentum through the caches
 // when `cached`; else segmented.
 template <typename GT>
 PlanPick pick_plan(int W, int G, bool cached = false) {
-    PlanKernel k = nullptr;
-    switch (W) {
-        case 1: k = pick_plan_g<GT, 1>(G, cached); break;
-        case 2: k = pick_plan_g<GT, 2>(G, cached); break;
-        case 3: k = pick_plan_g<GT, 3>(G, cached); break;
-        case 4: k = pick_plan_g<GT, 4>(G, cached); break;
-        case 5: k = pick_plan_g<GT, 5>(G, cached); break;
-        case 6: k = pick_plan_g<GT, 6>(G, cached); break;
-        case 7: k = pick_plan_g<GT, 7>(G, cached); break;
-        case 8: k = pick_plan_g<GT, 8>(G, cached); break;
-        case 12: k = pick_plan_g<GT, 12>(G, cached); break;
-        case 16: k = pick_plan_g<GT, 16>(G, cached); break;
-        case 32: k = pick_plan_big_w<GT, 32>(G, cached); break;
-        case 64: k = pick_plan_big_w<GT, 64>(G, cached); break;
-        case 128: k = pick_plan_big_w<GT, 128>(G, cached); break;
-    }
+    const PlanKernel k = pick_plan_pow2<GT>(W, G, cached);
     if (k) return PlanPick{k, tile_units<GT>(W * G, G), false};
     if (np2_group_count(G)) {   // group counts 3, 5, 6, 7 and 12 (lsgd_np2.hpp)
         const Np2PlanPick q = pick_plan_np2(W, G, cached, sizeof(GT) == 2);
@@ -207,62 +144,9 @@ lsgd_status launch_plan_copy_out(const lsgd_plan* plan, PlanArgs& a, hipStream_t
 }
 
 // LARS pass-1 kernels: compile-time (W, G) as for the step, else segmented.
-template <typename GT, int W>
-LarsKernel pick_lars_g(int G) {
-    switch (G) {
-        case 1: return lars_kernel_for<GT, W, 1>();
-        case 2: return lars_kernel_for<GT, W, 2>();
-        case 4: return lars_kernel_for<GT, W, 4>();
-        case 8: return lars_kernel_for<GT, W, 8>();
-        case 16:
-            if constexpr (W * 16 <= kMaxWorkers) return lars_kernel_for<GT, W, 16>();
-            else return nullptr;
-        case 32:
-            if constexpr (W <= 4) return lars_kernel_for<GT, W, 32>();
-            else return nullptr;
-        case 64:
-            if constexpr (W <= 2) return lars_kernel_for<GT, W, 64>();
-            else return nullptr;
-        case 128:
-            if constexpr (W == 1) return lars_kernel_for<GT, W, 128>();
-            else return nullptr;
-    }
-    return nullptr;
-}
-
-template <typename GT, int W>
-LarsKernel pick_lars_big_w(int G) {
-    switch (G) {
-        case 1: return lars_kernel_for<GT, W, 1>();
-        case 2:
-            if constexpr (W * 2 <= kMaxWorkers) return lars_kernel_for<GT, W, 2>();
-            else return nullptr;
-        case 4:
-            if constexpr (W * 4 <= kMaxWorkers) return lars_kernel_for<GT, W, 4>();
-            else return nullptr;
-    }
-    return nullptr;
-}
-
 template <typename GT>
 LarsKernel pick_lars(int W, int G) {
-    LarsKernel k = nullptr;
-    switch (W) {
-        case 1: k = pick_lars_g<GT, 1>(G); break;
-        case 2: k = pick_lars_g<GT, 2>(G); break;
-        case 3: k = pick_lars_g<GT, 3>(G); break;
-        case 4: k = pick_lars_g<GT, 4>(G); break;
-        case 5: k = pick_lars_g<GT, 5>(G); break;
-        case 6: k = pick_lars_g<GT, 6>(G); break;
-        case 7: k = pick_lars_g<GT, 7>(G); break;
-        case 8: k = pick_lars_g<GT, 8>(G); break;
-        case 12: k = pick_lars_g<GT, 12>(G); break;
-        case 16: k = pick_lars_g<GT, 16>(G); break;
-        case 32: k = pick_lars_big_w<GT, 32>(G); break;
-        case 64: k = pick_lars_big_w<GT, 64>(G); break;
-        case 128: k = pick_lars_big_w<GT, 128>(G); break;
-    }
-    if (k) return k;
+    if (const LarsKernel k = pick_lars_pow2<GT>(W, G)) return k;
     if (np2_group_count(G))
         if (const Np2LarsKernel q = pick_lars_np2(W, G, sizeof(GT) == 2)) return q;
     switch (seg_levels(W > G ? W : G)) {
