@@ -4,12 +4,9 @@
 // lsgd_plan_create cuts every tensor into pieces of P workgroup tile passes
 // (256 lanes x the kernel's lane tile: 2048 elements for binary32 and bf16
 // gradients alike, times P = the launch shape's passes per workgroup at plan
-// creation, 1 by default), starting on unit boundaries, then packs consecutive
-// pieces into buckets of at most one piece: a large tensor yields one bucket per piece
-// (so it is walked exactly like the flat kernel walks a vector), while runs of
-// small tensors (ResNet-50's 64..1024-element batch-norm and bias vectors)
-// share a bucket. One workgroup runs one bucket; buckets are taken in the
-// XCD-chunked order of the launch shape.
+// creation, 1 by default), starting on unit boundaries. One workgroup runs one
+// piece (a large tensor is walked exactly like the flat kernel walks a
+// vector); pieces are taken in the XCD-chunked order of the launch shape.
 #include <string.h>
 
 #include <algorithm>
@@ -23,12 +20,10 @@ struct lsgd_plan {
     int device;
     int32_t n_tensors, n_workers, n_groups, W, n_replicas;
     lsgd_dtype gdt, rdt;
-    int32_t n_buckets, n_chunks, stride;
-    int64_t piece;  // elements per piece and per bucket
+    int32_t n_chunks, stride;
+    int64_t piece;  // elements per piece
     int64_t total_elems;  // elements of all tensors
     lsgd::PlanChunk* d_chunks;
-    int32_t* d_bucket_begin;
-    lsgd::CopyDesc* d_copy_desc;
     void** d_ptrs;
     // LARS: per-tensor scratch offsets and chunk ranges, and every buffer's
     // byte range (for the workspace aliasing check)
@@ -58,7 +53,7 @@ struct PlanPick {
     bool segmented;
 };
 
-// Elements per piece and per bucket: one tile pass of the plan's kernel.
+// Elements per piece: one tile pass of the plan's kernel.
 template <typename GT>
 constexpr int64_t piece_elems(int tile) { return static_cast<int64_t>(kBlock) * Unit<GT>::VEC * tile; }
 static_assert(piece_elems<float>(1) % 8 == 0 && piece_elems<uint16_t>(1) % 8 == 0,
@@ -97,13 +92,11 @@ lsgd_status check_device(const lsgd_plan* plan) {
     return LSGD_OK;
 }
 
-// Kernel arguments of a plan step and the launch shape over its buckets.
+// Kernel arguments of a plan step and the launch shape over its pieces.
 PlanArgs plan_args(const lsgd_plan* plan, Hyper h, const float* lr_device, LaunchShape& ls) {
     PlanArgs a;
     memset(&a, 0, sizeof a);
     a.chunks = plan->d_chunks;
-    a.bucket_begin = plan->d_bucket_begin;
-    a.copy_desc = plan->d_copy_desc;
     a.ptrs = plan->d_ptrs;
     a.stride = plan->stride;
     a.n_workers = plan->n_workers;
@@ -114,12 +107,12 @@ PlanArgs plan_args(const lsgd_plan* plan, Hyper h, const float* lr_device, Launc
     a.rdt = static_cast<int32_t>(plan->rdt);
     a.h = h;
     a.lr_ptr = lr_device;
-    a.n_buckets = plan->n_buckets;
+    a.n_chunks = plan->n_chunks;
     a.copy_src = 0;                              // the copy-out: p to the replicas
     a.copy_dst = 2 + plan->n_workers;
     for (int32_t j = 0; j <= plan->n_groups; ++j) a.group_start[j] = static_cast<uint8_t>(plan->group_start[j]);
     const int64_t block_bytes = (plan->gdt == LSGD_BF16 ? 2 : 4) * plan->piece;
-    ls = pad_for_xcd_chunk(plan->n_buckets, block_bytes);
+    ls = pad_for_xcd_chunk(plan->n_chunks, block_bytes);
     a.xcd_chunk = ls.xcd_chunk;
     return a;
 }
@@ -128,14 +121,14 @@ PlanArgs plan_args(const lsgd_plan* plan, Hyper h, const float* lr_device, Launc
 // lane loads 32 bytes of p and stores 32 bytes per tile).
 constexpr int kPlanCopyRKF32 = 1, kPlanCopyRKBF16 = 2;
 
-// The copy-out pass of a plan step: one workgroup per bucket and replica
+// The copy-out pass of a plan step: one workgroup per piece and replica
 // group; a lane tile covers a 2048-element piece (the usual piece size).
 template <int VEC, int RK>
 lsgd_status launch_plan_copy_out(const lsgd_plan* plan, PlanArgs& a, hipStream_t s) {
     constexpr int U = 2048 / (VEC * kBlock);
     static_assert(U >= 1, "at least one unit per lane");
-    const int64_t win = copy_window_blocks(4 * plan->piece, plan->n_buckets);
-    const int64_t blocks = (plan->n_buckets + win - 1) / win * ((a.n_replicas + RK - 1) / RK) * win;
+    const int64_t win = copy_window_blocks(4 * plan->piece, plan->n_chunks);
+    const int64_t blocks = (plan->n_chunks + win - 1) / win * ((a.n_replicas + RK - 1) / RK) * win;
     a.win_blocks = static_cast<int32_t>(win);
     a.copy_blocks = blocks;
     const int64_t grid = std::min<int64_t>(blocks, stride_grid_cap());   // the kernel strides over the rest
@@ -177,8 +170,6 @@ LarsLayout lars_layout(const lsgd_plan* plan) {
 void free_plan(lsgd_plan* p) {
     if (!p) return;
     if (p->d_chunks) (void)hipFree(p->d_chunks);
-    if (p->d_bucket_begin) (void)hipFree(p->d_bucket_begin);
-    if (p->d_copy_desc) (void)hipFree(p->d_copy_desc);
     if (p->d_ptrs) (void)hipFree(p->d_ptrs);
     if (p->d_gbar_off) (void)hipFree(p->d_gbar_off);
     if (p->d_tensor_chunks) (void)hipFree(p->d_tensor_chunks);
@@ -250,7 +241,7 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     la.n_tensors = plan->n_tensors;
     la.trust_coef = trust_coef;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    if (plan->n_buckets > 0) {
+    if (plan->n_chunks > 0) {
         int32_t W = plan->W, G = plan->n_groups;
         if (one_group_form(W, G, false)) {
             W = plan->n_workers;
@@ -266,7 +257,7 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     }
     hipLaunchKernelGGL(lars_trust_kernel, dim3(plan->n_tensors), dim3(kBlock), 0, s, la);
     if ((st = check_launch("lsgd_lars_step_plan (trust)")) != LSGD_OK) return st;
-    if (plan->n_buckets == 0) return LSGD_OK;
+    if (plan->n_chunks == 0) return LSGD_OK;
     // the update reads and writes as lsgd_sgd_step does: the same copy-out rule
     const bool split = separate_copy_out_update(plan->n_replicas, plan->rdt == LSGD_BF16 ? 2 : 4,
                                                 use_cached_state(plan->n_workers, plan->total_elems));
@@ -316,13 +307,11 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     std::vector<void*> table(static_cast<size_t>(n_tensors) * stride, nullptr);
     std::vector<Range> ranges;
     std::vector<PlanChunk> chunks;
-    std::vector<int32_t> bucket_begin;
     // one tile pass of the kernel, times the launch shape's passes per workgroup
     const int32_t W = equal ? n_workers / n_groups : 0;
     const int tile = gdt == LSGD_BF16 ? pick_plan<uint16_t>(W, n_groups).tile : pick_plan<float>(W, n_groups).tile;
     const int64_t kPiece = (gdt == LSGD_BF16 ? piece_elems<uint16_t>(tile) : piece_elems<float>(tile)) *
                            launch_passes_per_block();
-    int64_t bucket_fill = kPiece;  // forces a new bucket at the first piece
     std::vector<int64_t> gbar_off(n_tensors, 0);
     std::vector<int32_t> tensor_chunks(n_tensors + 1, 0);
     int64_t gbar_floats = 0;
@@ -358,21 +347,15 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
         }
         for (int64_t s0 = 0; s0 < ne; s0 += kPiece) {
             const int64_t len = std::min(kPiece, ne - s0);
-            if (bucket_fill + len > kPiece) {
-                bucket_begin.push_back(static_cast<int32_t>(chunks.size()));
-                bucket_fill = 0;
-            }
             // every piece but a tensor's last has len == kPiece (a multiple of the unit)
-            chunks.push_back(PlanChunk{t, 0, s0, len});
-            bucket_fill += len;
+            chunks.push_back(PlanChunk{params[t], t, 0, s0, len});
         }
     }
     if ((st = check_overlap(ranges)) != LSGD_OK) return st;
     if (chunks.size() > 0x7fffffff) return fail(LSGD_ERR_SIZE, "too many pieces");
-    // one workgroup per bucket (and per tensor in the LARS trust kernel), in one launch
-    if (static_cast<int64_t>(bucket_begin.size()) > kMaxGridBlocks || n_tensors > kMaxGridBlocks)
-        return fail(LSGD_ERR_SIZE, "more than %lld buckets or tensors", static_cast<long long>(kMaxGridBlocks));
-    bucket_begin.push_back(static_cast<int32_t>(chunks.size()));
+    // one workgroup per tensor in the LARS trust kernel, in one launch
+    if (n_tensors > kMaxGridBlocks)
+        return fail(LSGD_ERR_SIZE, "more than %lld tensors", static_cast<long long>(kMaxGridBlocks));
     tensor_chunks[n_tensors] = static_cast<int32_t>(chunks.size());
 
     lsgd_plan* p = new lsgd_plan;
@@ -391,7 +374,6 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     p->gdt = gdt;
     p->rdt = rdt;
     p->n_chunks = static_cast<int32_t>(chunks.size());
-    p->n_buckets = static_cast<int32_t>(bucket_begin.size()) - 1;
     p->stride = stride;
     p->piece = kPiece;
     for (int32_t t = 0; t < n_tensors; ++t) p->total_elems += numel[t];
@@ -399,25 +381,12 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     p->ranges = new std::vector<Range>(ranges);
     hipError_t e = hipSuccess;
     const size_t chunk_bytes = std::max<size_t>(1, chunks.size()) * sizeof(PlanChunk);
-    const size_t bucket_bytes = bucket_begin.size() * sizeof(int32_t);
     const size_t table_bytes = table.size() * sizeof(void*);
     if (e == hipSuccess) e = hipMalloc(&p->d_chunks, chunk_bytes);
-    if (e == hipSuccess) e = hipMalloc(&p->d_bucket_begin, bucket_bytes);
     if (e == hipSuccess) e = hipMalloc(&p->d_ptrs, table_bytes);
     if (e == hipSuccess && !chunks.empty())
         e = hipMemcpy(p->d_chunks, chunks.data(), chunks.size() * sizeof(PlanChunk), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(p->d_bucket_begin, bucket_begin.data(), bucket_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_ptrs, table.data(), table_bytes, hipMemcpyHostToDevice);
-    std::vector<CopyDesc> desc(static_cast<size_t>(std::max(p->n_buckets, 1)));
-    for (int32_t b = 0; b < p->n_buckets; ++b) {
-        const PlanChunk& ch = chunks[static_cast<size_t>(bucket_begin[b])];
-        desc[b] = CopyDesc{static_cast<const float*>(table[static_cast<size_t>(ch.tensor) * stride]), ch.tensor,
-                           bucket_begin[b + 1] - bucket_begin[b], ch.start, ch.len};
-    }
-    if (e == hipSuccess) e = hipMalloc(&p->d_copy_desc, desc.size() * sizeof(CopyDesc));
-    if (e == hipSuccess)
-        e = hipMemcpy(p->d_copy_desc, desc.data(), desc.size() * sizeof(CopyDesc), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&p->d_gbar_off, gbar_off.size() * sizeof(int64_t));
     if (e == hipSuccess) e = hipMalloc(&p->d_lars_exclude, static_cast<size_t>(n_tensors));
     if (e == hipSuccess) {
@@ -467,7 +436,7 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
         lsgd_status st = check_overlap(ranges);
         if (st != LSGD_OK) return st;
     }
-    if (plan->n_buckets == 0) return LSGD_OK;
+    if (plan->n_chunks == 0) return LSGD_OK;
     lsgd_status st = check_device(plan);
     if (st != LSGD_OK) return st;
     LaunchShape ls;
@@ -532,7 +501,7 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
 
 LSGD_API lsgd_status lsgd_plan_copy_out(const lsgd_plan* plan, void* stream) {
     if (!plan) return fail(LSGD_ERR_NULL, "plan is NULL");
-    if (plan->n_buckets == 0 || plan->n_replicas == 0) return LSGD_OK;
+    if (plan->n_chunks == 0 || plan->n_replicas == 0) return LSGD_OK;
     lsgd_status st = check_device(plan);
     if (st != LSGD_OK) return st;
     LaunchShape ls;
