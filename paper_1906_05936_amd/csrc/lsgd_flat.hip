@@ -9,6 +9,7 @@
 #include "lsgd_np2.hpp"
 #include "lsgd_pow2.hpp"
 #include "lsgd_schedule.hpp"
+#include "lsgd_split_host.hpp"
 
 namespace lsgd {
 namespace {
@@ -104,6 +105,28 @@ lsgd_status launch_copy_out(StepArgs& a, void* stream) {
     const hipStream_t s = static_cast<hipStream_t>(stream);
     if (a.rdt == static_cast<int32_t>(LSGD_BF16)) return launch_copy_out_rmajor<8, kCopyUBF16, kCopyRKBF16>(a, s);
     return launch_copy_out_rmajor<4, kCopyUF32, kCopyRKF32>(a, s);
+}
+
+// The copy passes after a step kernel that wrote the first k_step of R
+// replicas and, with the broadcast, the first member's gradient.
+lsgd_status launch_copies(StepArgs& a, int32_t R, int32_t k_step, int32_t bcast_copies, void* stream) {
+    lsgd_status st = LSGD_OK;
+    if (R > k_step) {
+        for (int32_t r = k_step; r < R; ++r) a.replicas[r - k_step] = a.replicas[r];
+        a.n_replicas = R - k_step;
+        if ((st = launch_copy_out(a, stream)) != LSGD_OK) return st;
+    }
+    if (bcast_copies > 0) {
+        StepArgs b;
+        memset(&b, 0, sizeof b);
+        b.p = static_cast<float*>(const_cast<void*>(a.grads[0]));   // read only by the copy pass
+        b.n = a.n;
+        b.n_replicas = bcast_copies;
+        b.rdt = static_cast<int32_t>(LSGD_F32);
+        for (int32_t k = 0; k < bcast_copies; ++k) b.replicas[k] = const_cast<void*>(a.grads[k + 1]);
+        st = launch_copy_out(b, stream);
+    }
+    return st;
 }
 
 // Long vectors are processed range by range, unless one pass writes the
@@ -244,6 +267,42 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     }
     if ((st = check_overlap(ranges)) != LSGD_OK) return st;
 
+    a.p = params;
+    a.m = momentum;
+    a.n = n;
+    a.h = Hyper{lr, momentum_coef, weight_decay};
+    a.n_workers = n_workers;
+    a.n_groups = n_groups;
+    a.n_replicas = n_replicas;
+    a.rdt = static_cast<int32_t>(rdt);
+    a.lr_ptr = o.lr_device;
+    a.literal = literal ? 1 : 0;
+    for (int32_t r = 0; r < n_replicas; ++r) a.replicas[r] = replicas[r];
+    const int32_t bcast_copies = bcast ? n_workers - 1 : 0;
+    const int64_t copy_bytes = static_cast<int64_t>(n_replicas) * dtype_size(rdt) + 4 * bcast_copies;
+    const char* what = literal ? "lsgd_step_ex" : "lsgd_step";
+
+    if (use_split_flat(n, n_workers, gdt == LSGD_BF16, 1)) {
+        if (!literal) {
+            gstart.resize(n_groups + 1);
+            for (int32_t j = 0; j <= n_groups; ++j) gstart[j] = j * (n_workers / n_groups);
+        }
+        Program pr;
+        build_program(n_groups, gstart.data(), literal, pr);
+        if (use_split_flat(n, n_workers, gdt == LSGD_BF16, pr.n_batches)) {
+            const bool apart = separate_copy_out_small(
+                n, copy_bytes, separate_copy_out_bytes(n_workers, dtype_size(gdt), copy_bytes, n, false));
+            a.bcast_grad = bcast ? (apart ? 1 : n_workers) : 0;
+            a.n_replicas = apart ? replicas_in_step(n_workers, n_replicas, dtype_size(rdt), n) : n_replicas;
+            const LaunchShape ls = split_launch_shape(n, dtype_size(gdt));
+            a.xcd_chunk = ls.xcd_chunk;
+            launch_flat_split(a, pr, gdt == LSGD_BF16, ls.blocks, a.n_replicas + a.bcast_grad,
+                              static_cast<hipStream_t>(stream));
+            if ((st = check_launch(what)) != LSGD_OK || !apart) return st;
+            return launch_copies(a, n_replicas, a.n_replicas, bcast_copies, stream);
+        }
+    }
+
     // equal group sizes: the literal reduction then runs in the compile-time
     // kernels too (W = 0 marks unequal groups)
     int32_t W = n_workers / n_groups;
@@ -269,18 +328,8 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
         G = 1;
         k = pick_ct(W, G);
     }
-    a.p = params;
-    a.m = momentum;
-    a.n = n;
-    a.h = Hyper{lr, momentum_coef, weight_decay};
-    a.n_workers = n_workers;
     a.n_groups = G;
     a.W = W;
-    a.n_replicas = n_replicas;
-    a.rdt = static_cast<int32_t>(rdt);
-    a.lr_ptr = o.lr_device;
-    a.literal = literal ? 1 : 0;
-    for (int32_t r = 0; r < n_replicas; ++r) a.replicas[r] = replicas[r];
 
     const int64_t vec = gdt == LSGD_BF16 ? Unit<uint16_t>::VEC : Unit<float>::VEC;
     const bool segmented = !k.kernel;
@@ -299,15 +348,11 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     // with the broadcast the mean gradient to the other N - 1 members. Split
     // off, the step kernel writes the mean gradient to the first member only
     // and copy passes of their own write the rest (range by range: split_ranges).
-    const int32_t bcast_copies = bcast ? n_workers - 1 : 0;
-    const bool split = separate_copy_out_bytes(
-        n_workers, dtype_size(gdt), static_cast<int64_t>(n_replicas) * dtype_size(rdt) + 4 * bcast_copies, n,
-        !pow2_grouping);
+    const bool split = separate_copy_out_bytes(n_workers, dtype_size(gdt), copy_bytes, n, !pow2_grouping);
     a.bcast_grad = bcast ? (split ? 1 : n_workers) : 0;
     // split: the step kernel writes the first k replicas, the copy-out pass the rest
     const int32_t k_step = split ? replicas_in_step(n_workers, n_replicas, dtype_size(rdt), n) : n_replicas;
     a.n_replicas = k_step;
-    const char* what = literal ? "lsgd_step_ex" : "lsgd_step";
     // a fused pass that writes replicas or broadcast copies stays one launch
     // (ranges measured 0.8% slower there: 3.5e8-element 8x8 bfloat16 step, 64 replicas)
     const int64_t K = split || (n_replicas == 0 && !bcast) ? split_ranges(n) : 1;
@@ -320,21 +365,7 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
         hipLaunchKernelGGL(k.kernel, dim3(ls.blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream), ra);
         if ((st = check_launch(what)) != LSGD_OK) return st;
         if (!split) continue;
-        if (n_replicas > k_step) {
-            for (int32_t r = k_step; r < n_replicas; ++r) ra.replicas[r - k_step] = ra.replicas[r];
-            ra.n_replicas = n_replicas - k_step;
-            if ((st = launch_copy_out(ra, stream)) != LSGD_OK) return st;
-        }
-        if (bcast_copies > 0) {
-            StepArgs b;
-            memset(&b, 0, sizeof b);
-            b.p = static_cast<float*>(const_cast<void*>(ra.grads[0]));   // read only by the copy pass
-            b.n = ra.n;
-            b.n_replicas = bcast_copies;
-            b.rdt = static_cast<int32_t>(LSGD_F32);
-            for (int32_t k2 = 0; k2 < bcast_copies; ++k2) b.replicas[k2] = const_cast<void*>(ra.grads[k2 + 1]);
-            if ((st = launch_copy_out(b, stream)) != LSGD_OK) return st;
-        }
+        if ((st = launch_copies(ra, n_replicas, k_step, bcast_copies, stream)) != LSGD_OK) return st;
     }
     return LSGD_OK;
 }

@@ -15,6 +15,7 @@
 #include "lsgd_np2.hpp"
 #include "lsgd_plan_kernels.hpp"
 #include "lsgd_pow2.hpp"
+#include "lsgd_split_host.hpp"
 
 struct lsgd_plan {
     int device;
@@ -24,6 +25,12 @@ struct lsgd_plan {
     int64_t piece;  // elements per piece
     int64_t total_elems;  // elements of all tensors
     lsgd::PlanChunk* d_chunks;
+    // small plans: the split kernels' pieces of at most kSplitElems elements
+    // (n_fine == 0: the plan takes the other kernels)
+    int32_t n_fine;
+    lsgd::PlanChunk* d_fine;
+    lsgd::Program mean_program, literal_program;
+    bool lars_merge;      // the LARS update sums each tensor's partials itself
     void** d_ptrs;
     // LARS: per-tensor scratch offsets and chunk ranges, and every buffer's
     // byte range (for the workspace aliasing check)
@@ -117,6 +124,14 @@ PlanArgs plan_args(const lsgd_plan* plan, Hyper h, const float* lr_device, Launc
     return a;
 }
 
+// The same over the plan's fine pieces, for the split kernels.
+void use_fine_pieces(const lsgd_plan* plan, PlanArgs& a, LaunchShape& ls) {
+    a.chunks = plan->d_fine;
+    a.n_chunks = plan->n_fine;
+    ls = pad_for_xcd_chunk(plan->n_fine, (plan->gdt == LSGD_BF16 ? 2 : 4) * kSplitElems);
+    a.xcd_chunk = ls.xcd_chunk;
+}
+
 // Replicas per workgroup of the plan's copy-out pass (as for flat steps: a
 // lane loads 32 bytes of p and stores 32 bytes per tile).
 constexpr int kPlanCopyRKF32 = 1, kPlanCopyRKBF16 = 2;
@@ -134,6 +149,38 @@ lsgd_status launch_plan_copy_out(const lsgd_plan* plan, PlanArgs& a, hipStream_t
     const int64_t grid = std::min<int64_t>(blocks, stride_grid_cap());   // the kernel strides over the rest
     hipLaunchKernelGGL((copy_out_plan_rmajor<VEC, U, RK>), dim3(static_cast<unsigned>(grid)), dim3(kBlock), 0, s, a);
     return check_launch("lsgd_step_plan (copy-out)");
+}
+
+// The copy passes after a plan step that wrote the first k_step replicas and,
+// with the broadcast, the first member's gradient.
+lsgd_status launch_plan_copies(const lsgd_plan* plan, PlanArgs& a, int32_t k_step, int32_t bcast_copies, hipStream_t s) {
+    if (plan->n_replicas > k_step) {
+        a.copy_dst = 2 + plan->n_workers + k_step;
+        a.n_replicas = plan->n_replicas - k_step;
+        const lsgd_status st = plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, a, s)
+                                                      : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, a, s);
+        if (st != LSGD_OK) return st;
+    }
+    if (bcast_copies > 0) {   // the first member's gradient (slot 2) to the others (slots 3 ..)
+        a.copy_src = 2;
+        a.copy_dst = 3;
+        a.n_replicas = bcast_copies;
+        a.rdt = static_cast<int32_t>(LSGD_F32);
+        return launch_plan_copy_out<4, kPlanCopyRKF32>(plan, a, s);
+    }
+    return LSGD_OK;
+}
+
+// LARS pass 2: one workgroup per tensor.
+__global__ __launch_bounds__(kBlock) void lars_trust_kernel(LarsArgs la) {
+    __shared__ double lds[kBlock / 64][2];
+    const int32_t t = static_cast<int32_t>(blockIdx.x);
+    if (t >= la.n_tensors) return;
+    const float tr = lars_trust(la, t, la.tensor_chunks[t], la.tensor_chunks[t + 1], lds);
+    if (threadIdx.x == 0) {
+        la.trust[t] = tr;
+        if (la.trust_out) la.trust_out[t] = tr;
+    }
 }
 
 // LARS pass-1 kernels: compile-time (W, G) as for the step, else segmented.
@@ -162,7 +209,7 @@ LarsLayout lars_layout(const lsgd_plan* plan) {
     LarsLayout l;
     l.gbar = 0;
     l.partials = round256(static_cast<size_t>(plan->gbar_floats) * sizeof(float));
-    l.trust = l.partials + round256(static_cast<size_t>(plan->n_chunks) * 2 * sizeof(double));
+    l.trust = l.partials + round256(static_cast<size_t>(plan->n_fine ? plan->n_fine : plan->n_chunks) * 2 * sizeof(double));
     l.total = l.trust + round256(static_cast<size_t>(plan->n_tensors) * sizeof(float));
     return l;
 }
@@ -170,6 +217,7 @@ LarsLayout lars_layout(const lsgd_plan* plan) {
 void free_plan(lsgd_plan* p) {
     if (!p) return;
     if (p->d_chunks) (void)hipFree(p->d_chunks);
+    if (p->d_fine) (void)hipFree(p->d_fine);
     if (p->d_ptrs) (void)hipFree(p->d_ptrs);
     if (p->d_gbar_off) (void)hipFree(p->d_gbar_off);
     if (p->d_tensor_chunks) (void)hipFree(p->d_tensor_chunks);
@@ -241,7 +289,23 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     la.n_tensors = plan->n_tensors;
     la.trust_coef = trust_coef;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    if (plan->n_chunks > 0) {
+    const int rsz = plan->rdt == LSGD_BF16 ? 2 : 4;
+    if (plan->n_fine > 0) {
+        LarsArgs fa = la;
+        LaunchShape fs;
+        use_fine_pieces(plan, fa.pa, fs);
+        launch_lars_norms_split(fa, plan->mean_program, plan->gdt == LSGD_BF16, fs.blocks, s);
+        if ((st = check_launch("lsgd_lars_step_plan (norms)")) != LSGD_OK) return st;
+        if (plan->lars_merge) {
+            const bool apart = separate_copy_out_small(plan->total_elems, static_cast<int64_t>(plan->n_replicas) * rsz,
+                                                       separate_copy_out_update(plan->n_replicas, rsz, true));
+            if (apart) fa.pa.n_replicas = 0;
+            launch_lars_update_split(fa, fs.blocks, s);
+            if ((st = check_launch("lsgd_lars_step_plan (update)")) != LSGD_OK || !apart) return st;
+            return plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, la.pa, s)
+                                          : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, la.pa, s);
+        }
+    } else if (plan->n_chunks > 0) {
         int32_t W = plan->W, G = plan->n_groups;
         if (one_group_form(W, G, false)) {
             W = plan->n_workers;
@@ -259,7 +323,7 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     if ((st = check_launch("lsgd_lars_step_plan (trust)")) != LSGD_OK) return st;
     if (plan->n_chunks == 0) return LSGD_OK;
     // the update reads and writes as lsgd_sgd_step does: the same copy-out rule
-    const bool split = separate_copy_out_update(plan->n_replicas, plan->rdt == LSGD_BF16 ? 2 : 4,
+    const bool split = separate_copy_out_update(plan->n_replicas, rsz,
                                                 use_cached_state(plan->n_workers, plan->total_elems));
     if (split) la.pa.n_replicas = 0;
     hipLaunchKernelGGL(lars_update_kernel<2>, dim3(ls.blocks), dim3(kBlock), 0, s, la);
@@ -352,11 +416,33 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
         }
     }
     if ((st = check_overlap(ranges)) != LSGD_OK) return st;
+    int64_t total_elems = 0;
+    for (int32_t t = 0; t < n_tensors; ++t) total_elems += numel[t];
+    Program mean_program, literal_program;
+    memset(&mean_program, 0, sizeof mean_program);
+    if (equal) build_program(n_groups, gstart.data(), false, mean_program);
+    build_program(n_groups, gstart.data(), true, literal_program);
+    std::vector<PlanChunk> fine;
+    bool lars_merge = false;
+    if (use_split_plan(total_elems, n_workers, gdt == LSGD_BF16,
+                       std::max(mean_program.n_batches, literal_program.n_batches))) {
+        lars_merge = true;
+        for (int32_t t = 0; t < n_tensors; ++t) {
+            tensor_chunks[t] = static_cast<int32_t>(fine.size());
+            const int64_t whole = numel[t] / kSplitVec * kSplitVec;
+            for (int64_t s0 = 0; s0 < whole; s0 += kSplitElems)
+                fine.push_back(PlanChunk{params[t], t, 0, s0, std::min<int64_t>(kSplitElems, whole - s0)});
+            if (whole < numel[t]) fine.push_back(PlanChunk{params[t], t, 0, whole, numel[t] - whole});
+            const size_t mine = fine.size() - static_cast<size_t>(tensor_chunks[t]);
+            // an empty tensor's trust ratio has no update workgroup that could write it
+            if (mine == 0 || mine > static_cast<size_t>(kLarsMergeChunks)) lars_merge = false;
+        }
+    }
     if (chunks.size() > 0x7fffffff) return fail(LSGD_ERR_SIZE, "too many pieces");
     // one workgroup per tensor in the LARS trust kernel, in one launch
     if (n_tensors > kMaxGridBlocks)
         return fail(LSGD_ERR_SIZE, "more than %lld tensors", static_cast<long long>(kMaxGridBlocks));
-    tensor_chunks[n_tensors] = static_cast<int32_t>(chunks.size());
+    tensor_chunks[n_tensors] = static_cast<int32_t>(fine.empty() ? chunks.size() : fine.size());
 
     lsgd_plan* p = new lsgd_plan;
     memset(p, 0, sizeof *p);
@@ -376,7 +462,11 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     p->n_chunks = static_cast<int32_t>(chunks.size());
     p->stride = stride;
     p->piece = kPiece;
-    for (int32_t t = 0; t < n_tensors; ++t) p->total_elems += numel[t];
+    p->total_elems = total_elems;
+    p->n_fine = static_cast<int32_t>(fine.size());
+    p->mean_program = mean_program;
+    p->literal_program = literal_program;
+    p->lars_merge = lars_merge;
     p->gbar_floats = gbar_floats;
     p->ranges = new std::vector<Range>(ranges);
     hipError_t e = hipSuccess;
@@ -384,6 +474,9 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     const size_t table_bytes = table.size() * sizeof(void*);
     if (e == hipSuccess) e = hipMalloc(&p->d_chunks, chunk_bytes);
     if (e == hipSuccess) e = hipMalloc(&p->d_ptrs, table_bytes);
+    if (e == hipSuccess && !fine.empty()) e = hipMalloc(&p->d_fine, fine.size() * sizeof(PlanChunk));
+    if (e == hipSuccess && !fine.empty())
+        e = hipMemcpy(p->d_fine, fine.data(), fine.size() * sizeof(PlanChunk), hipMemcpyHostToDevice);
     if (e == hipSuccess && !chunks.empty())
         e = hipMemcpy(p->d_chunks, chunks.data(), chunks.size() * sizeof(PlanChunk), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_ptrs, table.data(), table_bytes, hipMemcpyHostToDevice);
@@ -442,6 +535,26 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     LaunchShape ls;
     PlanArgs a = plan_args(plan, Hyper{lr, momentum_coef, weight_decay}, lr_device, ls);
     a.literal = literal ? 1 : 0;
+    if (plan->n_fine > 0) {
+        const Program& pr = literal ? plan->literal_program : plan->mean_program;
+        const int rsz = plan->rdt == LSGD_BF16 ? 2 : 4, gsz = plan->gdt == LSGD_BF16 ? 2 : 4;
+        const int32_t bcast_copies = bcast ? plan->n_workers - 1 : 0;
+        const int64_t copy_bytes = static_cast<int64_t>(plan->n_replicas) * rsz + 4 * bcast_copies;
+        const bool apart = separate_copy_out_small(
+            plan->total_elems, copy_bytes,
+            separate_copy_out_bytes(plan->n_workers, gsz, copy_bytes, plan->total_elems, false));
+        const int32_t k_step = apart ? replicas_in_step(plan->n_workers, plan->n_replicas, rsz, plan->total_elems)
+                                     : plan->n_replicas;
+        PlanArgs fa = a;
+        LaunchShape fs;
+        use_fine_pieces(plan, fa, fs);
+        fa.bcast_grad = bcast ? (apart ? 1 : plan->n_workers) : 0;
+        fa.n_replicas = k_step;
+        const hipStream_t s = static_cast<hipStream_t>(stream);
+        launch_plan_split(fa, pr, gsz == 2, fs.blocks, k_step + fa.bcast_grad, s);
+        if ((st = check_launch("lsgd_step_plan")) != LSGD_OK || !apart) return st;
+        return launch_plan_copies(plan, a, k_step, bcast_copies, s);
+    }
     const bool cached = use_cached_state(plan->n_workers, plan->total_elems);
     // equal groups (W > 0): the compile-time kernels for powers of two, for
     // either reduction; the segmented kernel otherwise
@@ -482,21 +595,7 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     const hipStream_t s = static_cast<hipStream_t>(stream);
     hipLaunchKernelGGL(k, dim3(ls.blocks), dim3(kBlock), 0, s, a);
     if ((st = check_launch("lsgd_step_plan")) != LSGD_OK || !split) return st;
-    if (plan->n_replicas > k_step) {
-        a.copy_dst = 2 + plan->n_workers + k_step;
-        a.n_replicas = plan->n_replicas - k_step;
-        st = plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, a, s)
-                                    : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, a, s);
-        if (st != LSGD_OK) return st;
-    }
-    if (bcast_copies > 0) {   // the first member's gradient (slot 2) to the others (slots 3 ..)
-        a.copy_src = 2;
-        a.copy_dst = 3;
-        a.n_replicas = bcast_copies;
-        a.rdt = static_cast<int32_t>(LSGD_F32);
-        return launch_plan_copy_out<4, kPlanCopyRKF32>(plan, a, s);
-    }
-    return LSGD_OK;
+    return launch_plan_copies(plan, a, k_step, bcast_copies, s);
 }
 
 LSGD_API lsgd_status lsgd_plan_copy_out(const lsgd_plan* plan, void* stream) {

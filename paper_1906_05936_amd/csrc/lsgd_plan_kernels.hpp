@@ -276,17 +276,22 @@ struct LarsArgs {
     float trust_coef;
 };
 
-// Workgroup sums of two doubles per lane, valid in thread 0. Within a wave an
-// xor butterfly: partners add the same two values, and addition is
-// commutative, so every lane holds the same bits after each round; then the
-// four wave sums in a fixed order. Every thread of the block calls it.
-__device__ __forceinline__ void block_sum2(double& a, double& b, double (*lds)[2]) {
-    static_assert(kBlock == 256, "four waves per workgroup");
+// Wave sums of two doubles per lane, in every lane: an xor butterfly, whose
+// partners add the same two values (addition is commutative, so every lane
+// holds the same bits after each round).
+__device__ __forceinline__ void wave_sum2(double& a, double& b) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         a += __shfl_xor(a, off, 64);
         b += __shfl_xor(b, off, 64);
     }
+}
+
+// Workgroup sums of two doubles per lane, valid in thread 0: the waves' sums,
+// then the four of them in a fixed order. Every thread of the block calls it.
+__device__ __forceinline__ void block_sum2(double& a, double& b, double (*lds)[2]) {
+    static_assert(kBlock == 256, "four waves per workgroup");
+    wave_sum2(a, b);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         lds[wave][0] = a;
@@ -421,27 +426,20 @@ __global__ __launch_bounds__(kBlock) void lars_norms_seg(LarsArgs la) {
     });
 }
 
-// Pass 2: one workgroup per tensor.
-static __global__ __launch_bounds__(kBlock) void lars_trust_kernel(LarsArgs la) {
-    __shared__ double lds[kBlock / 64][2];
-    const int32_t t = static_cast<int32_t>(blockIdx.x);
-    if (t >= la.n_tensors) return;
-    const int32_t c0 = la.tensor_chunks[t], c1 = la.tensor_chunks[t + 1];
+// The trust ratio of tensor t from the partials of its chunks [c0, c1), valid
+// in thread 0. Every thread of the block calls it.
+__device__ __forceinline__ float lars_trust(const LarsArgs& la, int32_t t, int32_t c0, int32_t c1, double (*lds)[2]) {
     double sp = 0.0, sg = 0.0;
     for (int32_t c = c0 + static_cast<int32_t>(threadIdx.x); c < c1; c += kBlock) {
         sp += la.partials[2 * static_cast<int64_t>(c)];
         sg += la.partials[2 * static_cast<int64_t>(c) + 1];
     }
     block_sum2(sp, sg, lds);
-    if (threadIdx.x == 0) {
-        const double wn = sqrt(sp), gn = sqrt(sg);
-        const double wd = static_cast<double>(la.pa.h.wd);
-        const float tr = (wn == 0.0 || gn == 0.0 || la.exclude[t] != 0)
-                             ? 1.0f
-                             : static_cast<float>((static_cast<double>(la.trust_coef) * wn) / (gn + wd * wn));
-        la.trust[t] = tr;
-        if (la.trust_out) la.trust_out[t] = tr;
-    }
+    const double wn = sqrt(sp), gn = sqrt(sg);
+    const double wd = static_cast<double>(la.pa.h.wd);
+    return (wn == 0.0 || gn == 0.0 || la.exclude[t] != 0)
+               ? 1.0f
+               : static_cast<float>((static_cast<double>(la.trust_coef) * wn) / (gn + wd * wn));
 }
 
 // Pass 3: trust-scaled update of U binary32 units per lane.
