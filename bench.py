@@ -786,7 +786,7 @@ def separate_copy_out(wl, R, mode="auto", bcast=False):
     G, W = wl.groups, wl.workers_per_group
     if W == 1 and G & (G - 1) and not ct_grouping(1, G) and not wl.group_sizes:
         G, W = 1, wl.n_workers                                  # run as one group of all workers
-    pow2_grouping = (not kernel_match(wl).endswith("_seg") and not wl.group_sizes
+    pow2_grouping = (not kernel_match(wl).endswith("_stream") and not wl.group_sizes
                      and W & (W - 1) == 0 and G & (G - 1) == 0)
     crossing = (64 if pow2_grouping else 48) if cached else 32
     return copy_bytes >= crossing or wl.n_workers * wl.grad_bytes >= 256
@@ -835,11 +835,17 @@ def kernel_match(wl, reduction=None, lars=False):
     ct = not wl.group_sizes and ct_grouping(W, G)
     if (not ct and not wl.group_sizes and W == 1 and G & (G - 1) and reduction != "literal"):
         ct = ct_grouping(G, 1)   # one worker per group: run as one group of all workers
+    few = wl.n_workers <= 16
+    f32 = wl.grad_dtype == "f32"
+    if wl.tensor_sizes:   # the library's size rules for its split kernels (lsgd_split.hip)
+        split = wl.n <= (1 << 19 if f32 and few else 1 << 20)
+    else:
+        split = wl.n <= (1 << 20 if f32 and not few else 1 << 18)
     if lars:
-        return "lars_norms_kernel" if ct else "lars_norms_seg"
+        return "lars_norms_split" if split else "lars_norms_kernel" if ct else "lars_norms_stream"
     if wl.tensor_sizes:
-        return "step_plan_kernel" if ct else "step_plan_seg"
-    return "step_flat_ct" if ct else "step_flat_seg"
+        return "step_plan_split" if split else "step_plan_kernel" if ct else "step_plan_stream"
+    return "step_flat_split" if split else "step_flat_ct" if ct else "step_flat_stream"
 
 
 def derive_traffic(args):

@@ -336,9 +336,10 @@ LSGD_API lsgd_status lsgd_lr_schedule_step(const lsgd_lr_schedule* schedule, int
  * once; lsgd_step_plan then launches one kernel. Tensors are cut into pieces
  * of 2048 elements (4096 for binary32 gradients with more than 16 workers in
  * a grouping with a compile-time kernel, as listed for lsgd_step, except 32
- * or more groups and 16 groups of 3 or 4; times the launch shape's
- * units_per_lane at creation);
- * small tensors are bucketed so that one workgroup covers several of them.
+ * or more groups and 16 groups of 3 or 4, and for binary32 gradients in any
+ * other layout; times the launch shape's units_per_lane at creation); small
+ * plans (up to 2^20 elements, 2^19 for binary32 gradients of at most 16
+ * workers, with units_per_lane 1) into pieces of 256. One workgroup per piece.
  *   numel     [n_tensors] host int64, elements of each tensor (>= 0).
  *   params, momentum [n_tensors] device pointers (binary32).
  *   grads     [n_workers * n_tensors] device pointers, worker-major:

@@ -19,9 +19,8 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblsgd.so")
 SOURCES = ["lsgd_plan_pow2_f32.hip", "lsgd_plan_pow2_bf16.hip", "lsgd_flat_pow2_f32.hip", "lsgd_flat_pow2_bf16.hip",
-           "lsgd_plan_np2.hip", "lsgd_flat_np2.hip", "lsgd_plan.hip", "lsgd_flat.hip", "lsgd_split.hip",
-           "lsgd_common.hip",
-           "lsgd_bench.hip", "lsgd_noalloc.hip"]
+           "lsgd_plan_np2.hip", "lsgd_flat_np2.hip", "lsgd_plan.hip", "lsgd_flat.hip", "lsgd_split.hip", "lsgd_stream.hip",
+           "lsgd_common.hip", "lsgd_bench.hip", "lsgd_noalloc.hip"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -10,22 +10,10 @@
 #include "lsgd_pow2.hpp"
 #include "lsgd_schedule.hpp"
 #include "lsgd_split_host.hpp"
+#include "lsgd_stream_host.hpp"
 
 namespace lsgd {
 namespace {
-
-// Runtime group layouts: accumulator levels for the largest count.
-// (the cached forms exist for counts up to 31, the only ones they can have)
-template <typename GT>
-FlatPick pick_flat_seg(int max_count, bool cached) {
-    constexpr int U = SegTileUnits<GT>::U;
-    switch (seg_levels(max_count)) {
-        case 3: return FlatPick{cached ? step_flat_seg<GT, 3, U, 1> : step_flat_seg<GT, 3, U, 0>, U};
-        case 4: return FlatPick{cached ? step_flat_seg<GT, 4, U, 1> : step_flat_seg<GT, 4, U, 0>, U};
-        case 5: return FlatPick{cached ? step_flat_seg<GT, 5, U, 1> : step_flat_seg<GT, 5, U, 0>, U};
-    }
-    return FlatPick{step_flat_seg<GT, 8, U, 0>, U};
-}
 
 using MeanKernel = void (*)(MeanArgs);
 
@@ -282,13 +270,17 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     const int64_t copy_bytes = static_cast<int64_t>(n_replicas) * dtype_size(rdt) + 4 * bcast_copies;
     const char* what = literal ? "lsgd_step_ex" : "lsgd_step";
 
-    if (use_split_flat(n, n_workers, gdt == LSGD_BF16, 1)) {
+    // the reduction program of the kernels for any layout
+    Program pr;
+    auto build = [&] {
         if (!literal) {
             gstart.resize(n_groups + 1);
             for (int32_t j = 0; j <= n_groups; ++j) gstart[j] = j * (n_workers / n_groups);
         }
-        Program pr;
         build_program(n_groups, gstart.data(), literal, pr);
+    };
+    if (use_split_flat(n, n_workers, gdt == LSGD_BF16, 1)) {
+        build();
         if (use_split_flat(n, n_workers, gdt == LSGD_BF16, pr.n_batches)) {
             const bool apart = separate_copy_out_small(
                 n, copy_bytes, separate_copy_out_bytes(n_workers, dtype_size(gdt), copy_bytes, n, false));
@@ -332,17 +324,11 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     a.W = W;
 
     const int64_t vec = gdt == LSGD_BF16 ? Unit<uint16_t>::VEC : Unit<float>::VEC;
-    const bool segmented = !k.kernel;
-    const bool pow2_grouping = !segmented && (W & (W - 1)) == 0 && (G & (G - 1)) == 0;
-    if (segmented) {
-        // runtime layout: group j is members [start[j], start[j+1]) of the member order
-        int32_t max_count = G;
-        for (int32_t j = 0; j <= G; ++j) {
-            const int32_t b = literal ? gstart[j] : j * W;
-            a.group_start[j] = static_cast<uint8_t>(b);
-            if (j > 0) max_count = std::max(max_count, b - static_cast<int32_t>(a.group_start[j - 1]));
-        }
-        k = gdt == LSGD_BF16 ? pick_flat_seg<uint16_t>(max_count, cached) : pick_flat_seg<float>(max_count, cached);
+    const bool any_layout = !k.kernel;
+    const bool pow2_grouping = !any_layout && (W & (W - 1)) == 0 && (G & (G - 1)) == 0;
+    if (any_layout) {
+        build();
+        k.tile = stream_tile(gdt == LSGD_BF16);
     }
     // Copies per element besides parameters and momentum: the replicas, and
     // with the broadcast the mean gradient to the other N - 1 members. Split
@@ -359,10 +345,14 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     for (int64_t i = 0; i < K; ++i) {
         const int64_t lo = range_edge(n, K, i), hi = range_edge(n, K, i + 1);
         StepArgs ra = K == 1 ? a : offset_args(a, lo, hi, dtype_size(gdt), dtype_size(rdt), n_replicas);
-        const LaunchShape ls = launch_shape((ra.n + vec - 1) / vec, k.tile);
+        // the stream kernels take the ragged end as a tile of its own
+        const int64_t units = any_layout && ra.n % vec != 0 ? (ra.n / vec + kBlock * k.tile - 1) / (kBlock * k.tile) * (kBlock * k.tile) + 1
+                                                            : (ra.n + vec - 1) / vec;
+        const LaunchShape ls = launch_shape(units, k.tile);
         ra.xcd_chunk = ls.xcd_chunk;
         ra.upl = ls.upl;
-        hipLaunchKernelGGL(k.kernel, dim3(ls.blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream), ra);
+        if (any_layout) launch_flat_stream(ra, pr, gdt == LSGD_BF16, cached, ls.blocks, static_cast<hipStream_t>(stream));
+        else hipLaunchKernelGGL(k.kernel, dim3(ls.blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream), ra);
         if ((st = check_launch(what)) != LSGD_OK) return st;
         if (!split) continue;
         if ((st = launch_copies(ra, n_replicas, k_step, bcast_copies, stream)) != LSGD_OK) return st;

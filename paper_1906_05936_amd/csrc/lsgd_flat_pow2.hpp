@@ -9,7 +9,7 @@ namespace lsgd {
 // Compile-time (W, G) kernels for power-of-two group counts G with N = W*G
 // <= 128: groups of up to 16 workers (W a power of two, or 3, 5, 6, 7 or 12), or
 // 32 to 128 workers in up to 4 groups, or 32 to 128 groups of up to 4
-// workers; every other grouping takes the segmented runtime-layout kernel.
+// workers; every other grouping takes the stream kernel (lsgd_stream.hpp).
 // Both give the same bits.
 // The compile-time kernel for (W, G), with parameters and momentum through
 // the caches when `cached` (instantiated only where cached_state_for holds).

@@ -503,7 +503,6 @@ struct StepArgs {
     int32_t literal;       // paper-literal reduction (else mean of means)
     int32_t win_blocks;    // replica-major copy-out: workgroups per window and replica group (a multiple of 8)
     int64_t copy_blocks;   // replica-major copy-out: logical workgroups (the grid strides over them)
-    uint8_t group_start[kMaxWorkers + 4];  // runtime-layout kernel: group j is members [start[j], start[j+1])
     const void* grads[kMaxWorkers];
     void* replicas[kMaxReplicas];
 };
@@ -526,14 +525,6 @@ struct MeanArgs {
 
 // ------------------------------------------------------------- per-unit bodies
 
-
-// Units per lane tile in the flat runtime-layout (segmented) kernel
-// (measured: two binary32 units per lane, stream-major, +2-5% over one on
-// 3x5, 4x6, 2x64 and 32x4 groupings, -1% on the literal 4x4 step; bf16 stays
-// at one unit for registers).
-template <typename GT> struct SegTileUnits;
-template <> struct SegTileUnits<float> { static constexpr int U = 2; };
-template <> struct SegTileUnits<uint16_t> { static constexpr int U = 1; };
 
 // Widened gradient values one lane may hold at once: up to kUnrollFloats the
 // whole two-level tree is unrolled with every load issued up front (32 fp32
@@ -785,63 +776,6 @@ __device__ __forceinline__ void fused_unit_ct(const Src& s, int64_t e0, int cnt)
     fused_tile_ct<GT, W, G, 1, TAIL>(s, e, cnt);
 }
 
-// The mean gradient of a lane tile (U units) for group layouts known only at
-// run time. Group j is members [gs(j), gs(j+1)) of the member-ordered
-// gradients. Mean of means (literal = false, equal groups of W): each group's
-// PW sum / W, PW over the G results, / G. Paper-literal (any partition): each
-// group's PW sum / N, PW over the G results, no further division.
-template <typename GT, int LV, int U, bool TAIL, typename Src, typename Start>
-__device__ __forceinline__ void mean_tile_seg(const Src& s, int N, int G, const Start& gs, bool literal,
-                                              const int64_t (&e0)[U], int cnt,
-                                              float (&gbar)[U * Unit<GT>::VEC]) {
-    constexpr int T = U * Unit<GT>::VEC;
-    const float dg = static_cast<float>(literal ? N : gs(1) - gs(0));
-    PwAcc<T, LV> groups;
-    const int glevels = acc_levels(G);
-    pw_segments<GT, LV, U, TAIL>(N, G, [&](int k) { return s.grad(k); }, gs, e0, cnt,
-                                 [&](int, float (&sum)[T]) {
-#pragma unroll
-                                     for (int v = 0; v < T; ++v) sum[v] = sum[v] / dg;
-                                     groups.push(sum, glevels);
-                                 });
-    groups.result(gbar, glevels);
-    if (!literal) {
-        const float gf = static_cast<float>(G);
-#pragma unroll
-        for (int v = 0; v < T; ++v) gbar[v] = gbar[v] / gf;
-    }
-}
-
-template <typename GT, int LV, bool TAIL, typename Src, typename Start>
-__device__ __forceinline__ void mean_unit_seg(const Src& s, int N, int G, const Start& gs, bool literal,
-                                              int64_t e0, int cnt, float (&gbar)[Unit<GT>::VEC]) {
-    const int64_t e[1] = {e0};
-    mean_tile_seg<GT, LV, 1, TAIL>(s, N, G, gs, literal, e, cnt, gbar);
-}
-
-// Fused step on a lane tile for runtime group layouts. Parameters and
-// momentum are loaded first so that their latency overlaps the gradient
-// stream.
-template <typename GT, int LV, int U, bool TAIL, typename Src, typename Start>
-__device__ __forceinline__ void fused_tile_seg(const Src& s, int N, int G, const Start& gs, bool literal,
-                                               const int64_t (&e0)[U], int cnt) {
-    constexpr int VEC = Unit<GT>::VEC;
-    constexpr int T = U * VEC;
-    float p[T], m[T];
-    load_state<VEC, U, TAIL>(s, e0, cnt, p, m);
-    float gbar[T];
-    mean_tile_seg<GT, LV, U, TAIL>(s, N, G, gs, literal, e0, cnt, gbar);
-    broadcast_mean<GT, U, TAIL>(s, e0, cnt, gbar);
-    update_and_store<VEC, U, TAIL>(s, e0, cnt, gbar, p, m);
-}
-
-template <typename GT, int LV, bool TAIL, typename Src, typename Start>
-__device__ __forceinline__ void fused_unit_seg(const Src& s, int N, int G, const Start& gs, bool literal,
-                                               int64_t e0, int cnt) {
-    const int64_t e[1] = {e0};
-    fused_tile_seg<GT, LV, 1, TAIL>(s, N, G, gs, literal, e, cnt);
-}
-
 // Pointer source for the planless fused step: everything from StepArgs.
 // CACHED: store parameters and momentum through the caches (1) or
 // nontemporally (0).
@@ -937,26 +871,6 @@ constexpr auto flat_step_kernel() {
     constexpr int cap = flat_wave_cap<GT>(W, G);
     if constexpr (cap != 0) return step_flat_ct_cap<GT, W, G, U, CACHED, cap>;
     else return step_flat_ct<GT, W, G, U, CACHED>;
-}
-
-// Runtime group layouts (non-power-of-two or large counts, and the
-// paper-literal reduction): group j is members [group_start[j],
-// group_start[j+1]) of the member-ordered pointer table.
-template <typename GT, int LV, int U, int CACHED>
-__global__ __launch_bounds__(kBlock) void step_flat_seg(StepArgs a) {
-    constexpr int VEC = Unit<GT>::VEC;
-    const FlatSrcT<CACHED> s{a, resolve_hyper(a.h, a.lr_ptr)};
-    const int64_t full = a.n / VEC;
-    const int rem = static_cast<int>(a.n - full * VEC);
-    const bool literal = a.literal != 0;
-    auto gs = [&](int j) { return static_cast<int>(a.group_start[j]); };
-    for_tiles<U, VEC>(
-        full, full + (rem != 0), a.xcd_chunk, a.upl,
-        [&](const int64_t (&e0)[U]) { fused_tile_seg<GT, LV, U, false>(s, a.n_workers, a.n_groups, gs, literal, e0, VEC); },
-        [&](int64_t u) {
-            if (u < full) fused_unit_seg<GT, LV, false>(s, a.n_workers, a.n_groups, gs, literal, u * VEC, VEC);
-            else fused_unit_seg<GT, LV, true>(s, a.n_workers, a.n_groups, gs, literal, u * VEC, rem);
-        });
 }
 
 // lsgd_group_mean, compile-time W (a power of two): every group's mean of its

@@ -16,10 +16,12 @@
 #include "lsgd_plan_kernels.hpp"
 #include "lsgd_pow2.hpp"
 #include "lsgd_split_host.hpp"
+#include "lsgd_stream_host.hpp"
 
 struct lsgd_plan {
     int device;
-    int32_t n_tensors, n_workers, n_groups, W, n_replicas;
+    int32_t n_tensors, n_workers, n_groups, n_replicas;
+    int32_t W;   // group size, 0 where the groups' sizes differ
     lsgd_dtype gdt, rdt;
     int32_t n_chunks, stride;
     int64_t piece;  // elements per piece
@@ -39,10 +41,6 @@ struct lsgd_plan {
     int32_t* d_tensor_chunks;
     uint8_t* d_lars_exclude;   // [n_tensors], zero until lsgd_plan_set_lars_exclude
     std::vector<lsgd::Range>* ranges;
-    // the partition: groups of equal size W (W = 0 otherwise), group j is
-    // members [group_start[j], group_start[j+1]) of the member order
-    int32_t max_group;
-    int32_t group_start[lsgd::kMaxWorkers + 1];
 };
 
 namespace lsgd {
@@ -52,12 +50,11 @@ namespace {
 // 64-float (256-byte) boundary.
 constexpr int64_t kGbarAlign = 64;
 
-// A kernel, the units per lane tile it processes, and whether it is the
-// segmented (runtime-layout) form.
+// A compile-time kernel (null: the stream kernels serve the layout) and the
+// units per lane tile it processes.
 struct PlanPick {
     PlanKernel kernel;
     int tile;
-    bool segmented;
 };
 
 // Elements per piece: one tile pass of the plan's kernel.
@@ -66,30 +63,18 @@ constexpr int64_t piece_elems(int tile) { return static_cast<int64_t>(kBlock) * 
 static_assert(piece_elems<float>(1) % 8 == 0 && piece_elems<uint16_t>(1) % 8 == 0,
               "pieces must start on unit boundaries");
 
-// The segmented plan kernel for groups and group counts up to max_count
-// (the cached form exists for counts up to 31, the only ones it can have).
-template <typename GT>
-PlanKernel plan_seg(int max_count, bool cached) {
-    switch (seg_levels(max_count)) {
-        case 3: return cached ? step_plan_seg<GT, 3, 1> : step_plan_seg<GT, 3, 0>;
-        case 4: return cached ? step_plan_seg<GT, 4, 1> : step_plan_seg<GT, 4, 0>;
-        case 5: return cached ? step_plan_seg<GT, 5, 1> : step_plan_seg<GT, 5, 0>;
-    }
-    return step_plan_seg<GT, 8, 0>;
-}
-
 // The plan kernel for (W, G): compile-time for the power-of-two groupings of
 // pick_flat (lsgd_flat.hip), with parameters and momentum through the caches
-// when `cached`; else segmented.
+// when `cached`; else none.
 template <typename GT>
 PlanPick pick_plan(int W, int G, bool cached = false) {
     const PlanKernel k = pick_plan_pow2<GT>(W, G, cached);
-    if (k) return PlanPick{k, tile_units<GT>(W * G, G), false};
+    if (k) return PlanPick{k, tile_units<GT>(W * G, G)};
     if (np2_group_count(G)) {   // group counts 3, 5, 6, 7 and 12 (lsgd_np2.hpp)
         const Np2PlanPick q = pick_plan_np2(W, G, cached, sizeof(GT) == 2);
-        if (q.kernel) return PlanPick{q.kernel, q.tile, false};
+        if (q.kernel) return PlanPick{q.kernel, q.tile};
     }
-    return PlanPick{plan_seg<GT>(W > G ? W : G, cached), SegTileUnits<GT>::U, true};
+    return PlanPick{nullptr, stream_tile(sizeof(GT) == 2)};
 }
 
 lsgd_status check_device(const lsgd_plan* plan) {
@@ -117,7 +102,6 @@ PlanArgs plan_args(const lsgd_plan* plan, Hyper h, const float* lr_device, Launc
     a.n_chunks = plan->n_chunks;
     a.copy_src = 0;                              // the copy-out: p to the replicas
     a.copy_dst = 2 + plan->n_workers;
-    for (int32_t j = 0; j <= plan->n_groups; ++j) a.group_start[j] = static_cast<uint8_t>(plan->group_start[j]);
     const int64_t block_bytes = (plan->gdt == LSGD_BF16 ? 2 : 4) * plan->piece;
     ls = pad_for_xcd_chunk(plan->n_chunks, block_bytes);
     a.xcd_chunk = ls.xcd_chunk;
@@ -183,18 +167,11 @@ __global__ __launch_bounds__(kBlock) void lars_trust_kernel(LarsArgs la) {
     }
 }
 
-// LARS pass-1 kernels: compile-time (W, G) as for the step, else segmented.
+// LARS pass-1 kernels: compile-time (W, G) as for the step, else none.
 template <typename GT>
 LarsKernel pick_lars(int W, int G) {
     if (const LarsKernel k = pick_lars_pow2<GT>(W, G)) return k;
-    if (np2_group_count(G))
-        if (const Np2LarsKernel q = pick_lars_np2(W, G, sizeof(GT) == 2)) return q;
-    switch (seg_levels(W > G ? W : G)) {
-        case 3: return lars_norms_seg<GT, 3>;
-        case 4: return lars_norms_seg<GT, 4>;
-        case 5: return lars_norms_seg<GT, 5>;
-    }
-    return lars_norms_seg<GT, 8>;
+    return np2_group_count(G) ? pick_lars_np2(W, G, sizeof(GT) == 2) : nullptr;
 }
 
 // LARS workspace layout: [gbar scratch | per-chunk partials | trust ratios],
@@ -310,13 +287,10 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
         if (one_group_form(W, G, false)) {
             W = plan->n_workers;
             G = 1;
-            la.pa.W = W;
-            la.pa.n_groups = 1;
-            la.pa.group_start[0] = 0;
-            la.pa.group_start[1] = static_cast<uint8_t>(W);
         }
         const LarsKernel k1 = plan->gdt == LSGD_BF16 ? pick_lars<uint16_t>(W, G) : pick_lars<float>(W, G);
-        hipLaunchKernelGGL(k1, dim3(ls.blocks), dim3(kBlock), 0, s, la);
+        if (k1) hipLaunchKernelGGL(k1, dim3(ls.blocks), dim3(kBlock), 0, s, la);
+        else launch_lars_norms_stream(la, plan->mean_program, plan->gdt == LSGD_BF16, ls.blocks, s);
         if ((st = check_launch("lsgd_lars_step_plan (norms)")) != LSGD_OK) return st;
     }
     hipLaunchKernelGGL(lars_trust_kernel, dim3(plan->n_tensors), dim3(kBlock), 0, s, la);
@@ -352,13 +326,8 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     lsgd_status st = partition_order(n_workers, group_of_worker, n_groups, order, gstart);
     if (st != LSGD_OK) return st;
     // equal group sizes (the mean-of-means step needs them) give W > 0
-    int32_t max_group = 0;
     bool equal = true;
-    for (int32_t j = 0; j < n_groups; ++j) {
-        const int32_t c = gstart[j + 1] - gstart[j];
-        max_group = std::max(max_group, c);
-        equal = equal && c == gstart[1] - gstart[0];
-    }
+    for (int32_t j = 0; j < n_groups; ++j) equal = equal && gstart[j + 1] - gstart[j] == gstart[1] - gstart[0];
     if (gdt != LSGD_F32 && gdt != LSGD_BF16) return fail(LSGD_ERR_DTYPE, "gradient dtype %d", (int)gdt);
     if (rdt != LSGD_F32 && rdt != LSGD_BF16) return fail(LSGD_ERR_DTYPE, "replica dtype %d", (int)rdt);
     if (n_replicas < 0 || n_replicas > kMaxReplicas)
@@ -454,8 +423,6 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     p->n_workers = n_workers;
     p->n_groups = n_groups;
     p->W = W;
-    p->max_group = max_group;
-    for (int32_t j = 0; j <= n_groups; ++j) p->group_start[j] = gstart[j];
     p->n_replicas = n_replicas;
     p->gdt = gdt;
     p->rdt = rdt;
@@ -556,28 +523,18 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
         return launch_plan_copies(plan, a, k_step, bcast_copies, s);
     }
     const bool cached = use_cached_state(plan->n_workers, plan->total_elems);
-    // equal groups (W > 0): the compile-time kernels for powers of two, for
-    // either reduction; the segmented kernel otherwise
+    // equal groups (W > 0): the compile-time kernels where there is one, for
+    // either reduction; the stream kernel otherwise
     PlanKernel k = nullptr;
-    bool segmented = true;
     int32_t W = plan->W, G = plan->n_groups;
     if (one_group_form(W, G, literal)) {
         W = plan->n_workers;
         G = 1;
         a.W = W;
         a.n_groups = 1;
-        a.group_start[0] = 0;
-        a.group_start[1] = static_cast<uint8_t>(W);
     }
-    if (W > 0) {
-        const PlanPick pk = plan->gdt == LSGD_BF16 ? pick_plan<uint16_t>(W, G, cached)
-                                                   : pick_plan<float>(W, G, cached);
-        k = pk.kernel;
-        segmented = pk.segmented;
-    } else {
-        const int32_t max_count = std::max(plan->max_group, plan->n_groups);
-        k = plan->gdt == LSGD_BF16 ? plan_seg<uint16_t>(max_count, cached) : plan_seg<float>(max_count, cached);
-    }
+    if (W > 0)
+        k = plan->gdt == LSGD_BF16 ? pick_plan<uint16_t>(W, G, cached).kernel : pick_plan<float>(W, G, cached).kernel;
     // as for flat steps: the replicas and the broadcast's copies of the mean
     // gradient to the other N - 1 members go to copy passes of their own
     // where the rule takes the separate form
@@ -585,7 +542,7 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     const bool split = separate_copy_out_bytes(
         plan->n_workers, plan->gdt == LSGD_BF16 ? 2 : 4,
         static_cast<int64_t>(plan->n_replicas) * (plan->rdt == LSGD_BF16 ? 2 : 4) + 4 * bcast_copies,
-        plan->total_elems, segmented || (W & (W - 1)) != 0 || (G & (G - 1)) != 0);
+        plan->total_elems, !k || (W & (W - 1)) != 0 || (G & (G - 1)) != 0);
     a.bcast_grad = bcast ? (split ? 1 : plan->n_workers) : 0;
     // split: the step kernel writes the first k replicas, the copy-out pass the rest
     const int32_t k_step = split ? replicas_in_step(plan->n_workers, plan->n_replicas, plan->rdt == LSGD_BF16 ? 2 : 4,
@@ -593,7 +550,8 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
                                  : plan->n_replicas;
     a.n_replicas = k_step;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(k, dim3(ls.blocks), dim3(kBlock), 0, s, a);
+    if (k) hipLaunchKernelGGL(k, dim3(ls.blocks), dim3(kBlock), 0, s, a);
+    else launch_plan_stream(a, literal ? plan->literal_program : plan->mean_program, plan->gdt == LSGD_BF16, cached, ls.blocks, s);
     if ((st = check_launch("lsgd_step_plan")) != LSGD_OK || !split) return st;
     return launch_plan_copies(plan, a, k_step, bcast_copies, s);
 }

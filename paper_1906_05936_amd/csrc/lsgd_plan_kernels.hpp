@@ -41,7 +41,6 @@ struct PlanArgs {
     int32_t cached_state;  // LARS update: store parameters and momentum through the caches
     int32_t copy_src;      // copy-out pass: table slot of its source (0: p; 2: the first member's gradient)
     int32_t copy_dst;      // copy-out pass: table slot of its first destination (n_replicas of them)
-    uint8_t group_start[kMaxWorkers + 4];  // runtime-layout kernel: group j is members [start[j], start[j+1])
 };
 
 // CACHED as for FlatSrcT (-1: PlanArgs::cached_state decides).
@@ -153,33 +152,6 @@ constexpr auto plan_step_kernel() {
     constexpr int cap = sizeof(GT) == 2 ? wave_cap_in(kPlanWaveCapBF16, W, G) : wave_cap_in(kPlanWaveCapF32, W, G);
     if constexpr (cap != 0) return step_plan_kernel_cap<GT, W, G, U, CACHED, cap>;
     else return step_plan_kernel<GT, W, G, U, CACHED>;
-}
-
-// Runtime group layouts (non-power-of-two or large counts, and the
-// paper-literal reduction over any partition): one unit per lane.
-template <typename GT, int LV, int CACHED>
-__global__ __launch_bounds__(kBlock) void step_plan_seg(PlanArgs a) {
-    constexpr int VEC = Unit<GT>::VEC;
-    constexpr int U = SegTileUnits<GT>::U;
-    const bool literal = a.literal != 0;
-    auto gs = [&](int j) { return static_cast<int>(a.group_start[j]); };
-    for_plan_chunks<CACHED>(a, [&](const PlanSrcT<CACHED>& s, const PlanChunk& ch, int32_t) {
-        const int64_t full = ch.len / VEC;
-        for (int64_t t0 = threadIdx.x; t0 < full; t0 += static_cast<int64_t>(kBlock) * U) {
-            if (t0 + static_cast<int64_t>(U - 1) * kBlock < full) {
-                int64_t e0[U];
-#pragma unroll
-                for (int q = 0; q < U; ++q) e0[q] = ch.start + (t0 + static_cast<int64_t>(q) * kBlock) * VEC;
-                fused_tile_seg<GT, LV, U, false>(s, a.n_workers, a.n_groups, gs, literal, e0, VEC);
-            } else {
-                for (int64_t u = t0; u < full; u += kBlock)
-                    fused_unit_seg<GT, LV, false>(s, a.n_workers, a.n_groups, gs, literal, ch.start + u * VEC, VEC);
-            }
-        }
-        const int rem = static_cast<int>(ch.len - full * VEC);
-        if (rem != 0 && threadIdx.x == 0)
-            fused_unit_seg<GT, LV, true>(s, a.n_workers, a.n_groups, gs, literal, ch.start + full * VEC, rem);
-    });
 }
 
 // Replica-major copy-out pass over a plan's pieces (the layout of
@@ -392,38 +364,6 @@ constexpr auto lars_kernel_for() {
     constexpr int cap = sizeof(GT) == 2 ? wave_cap_in(kLarsWaveCapBF16, W, G) : 0;
     if constexpr (cap != 0) return lars_norms_kernel_cap<GT, W, G, U, cap>;
     else return lars_norms_kernel<GT, W, G, U>;
-}
-
-// Pass 1, runtime W and G (equal groups): one unit per lane.
-template <typename GT, int LV>
-__global__ __launch_bounds__(kBlock) void lars_norms_seg(LarsArgs la) {
-    constexpr int VEC = Unit<GT>::VEC;
-    __shared__ double lds[kBlock / 64][2];
-    const int W = la.pa.W;
-    auto gs = [&](int j) { return j * W; };
-    for_plan_chunks(la.pa, [&](const PlanSrc& s, const PlanChunk& ch, int32_t c) {
-        float* gb = la.gbar + read_table(&la.gbar_off[ch.tensor]);
-        double sp = 0.0, sg = 0.0;
-        const int64_t full = ch.len / VEC;
-        for (int64_t u = threadIdx.x; u < full; u += kBlock) {
-            const int64_t e[1] = {ch.start + u * VEC};
-            float gbar[VEC];
-            mean_unit_seg<GT, LV, false>(s, la.pa.n_workers, la.pa.n_groups, gs, false, e[0], VEC, gbar);
-            lars_tile_out<GT, 1, false>(s, gb, e, VEC, gbar, sp, sg);
-        }
-        const int rem = static_cast<int>(ch.len - full * VEC);
-        if (rem != 0 && threadIdx.x == 0) {
-            const int64_t e[1] = {ch.start + full * VEC};
-            float gbar[VEC];
-            mean_unit_seg<GT, LV, true>(s, la.pa.n_workers, la.pa.n_groups, gs, false, e[0], rem, gbar);
-            lars_tile_out<GT, 1, true>(s, gb, e, rem, gbar, sp, sg);
-        }
-        block_sum2(sp, sg, lds);
-        if (threadIdx.x == 0) {
-            la.partials[2 * static_cast<int64_t>(c)] = sp;
-            la.partials[2 * static_cast<int64_t>(c) + 1] = sg;
-        }
-    });
 }
 
 // The trust ratio of tensor t from the partials of its chunks [c0, c1), valid

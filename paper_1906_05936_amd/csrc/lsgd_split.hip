@@ -71,7 +71,7 @@ LaunchShape split_launch_shape(int64_t n, size_t gsz) {
 }
 
 void launch_flat_split(const StepArgs& a, const Program& pr, bool bf16, unsigned blocks, int copies, hipStream_t s) {
-    SplitArgs sa;
+    FlatProgArgs sa;
     sa.a = a;
     sa.pr = pr;
     const dim3 threads(64 * split_waves(pr, copies));
@@ -80,7 +80,7 @@ void launch_flat_split(const StepArgs& a, const Program& pr, bool bf16, unsigned
 }
 
 void launch_plan_split(const PlanArgs& a, const Program& pr, bool bf16, unsigned blocks, int copies, hipStream_t s) {
-    SplitPlanArgs sa;
+    PlanProgArgs sa;
     sa.a = a;
     sa.pr = pr;
     const dim3 threads(64 * split_waves(pr, copies));
@@ -89,7 +89,7 @@ void launch_plan_split(const PlanArgs& a, const Program& pr, bool bf16, unsigned
 }
 
 void launch_lars_norms_split(const LarsArgs& a, const Program& pr, bool bf16, unsigned blocks, hipStream_t s) {
-    SplitLarsArgs sa;
+    LarsProgArgs sa;
     sa.la = a;
     sa.pr = pr;
     const dim3 threads(64 * split_waves(pr, 0));

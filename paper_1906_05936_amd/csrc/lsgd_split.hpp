@@ -15,9 +15,7 @@
 // element per lane, so that no lane runs a second pass for it.
 #pragma once
 
-#include "lsgd_kernels.hpp"
-#include "lsgd_plan_kernels.hpp"
-#include "lsgd_program.hpp"
+#include "lsgd_batches.hpp"
 #include "lsgd_split_host.hpp"
 
 #pragma clang fp contract(off)
@@ -25,12 +23,6 @@
 namespace lsgd {
 
 constexpr int kSplitWaves = 16;   // most waves per workgroup
-
-// The flat step's arguments with the reduction program, in the kernel arguments.
-struct SplitArgs {
-    StepArgs a;
-    Program pr;
-};
 
 // A lane's four gradient elements as raw bits: 16 or 8 bytes. (Eight bfloat16
 // elements per lane took 102 registers, too many for 16 waves per workgroup.)
@@ -57,54 +49,6 @@ __device__ __forceinline__ void widen4(const typename Raw4<GT>::type& r, float (
     } else {
         x[0] = __uint_as_float(r.x << 16); x[1] = __uint_as_float(r.x & 0xffff0000u);
         x[2] = __uint_as_float(r.y << 16); x[3] = __uint_as_float(r.y & 0xffff0000u);
-    }
-}
-
-// Calls f(count, sub) with the batch's member count and inner group size as
-// compile-time constants.
-template <int V>
-struct IntC {
-    static constexpr int value = V;
-};
-template <typename F>
-__device__ __forceinline__ void with_batch(int count, int sub, const F& f) {
-#define LSGD_BATCH(C, S) \
-    case (C) | ((S) << 4): f(IntC<C>{}, IntC<S>{}); break;
-    switch (count | (sub << 4)) {
-        LSGD_BATCH(1, 0) LSGD_BATCH(2, 0) LSGD_BATCH(3, 0) LSGD_BATCH(4, 0)
-        LSGD_BATCH(5, 0) LSGD_BATCH(6, 0) LSGD_BATCH(7, 0) LSGD_BATCH(8, 0)
-        LSGD_BATCH(1, 1) LSGD_BATCH(2, 1) LSGD_BATCH(3, 1) LSGD_BATCH(4, 1)
-        LSGD_BATCH(5, 1) LSGD_BATCH(6, 1) LSGD_BATCH(7, 1) LSGD_BATCH(8, 1)
-        LSGD_BATCH(2, 2) LSGD_BATCH(4, 2) LSGD_BATCH(6, 2) LSGD_BATCH(8, 2)
-        LSGD_BATCH(3, 3) LSGD_BATCH(6, 3) LSGD_BATCH(4, 4) LSGD_BATCH(8, 4)
-    }
-#undef LSGD_BATCH
-}
-
-// x / group_div: a multiplication where the divisor is a power of two (the
-// same rounding of the same exact quotient).
-template <int T>
-__device__ __forceinline__ void divide_group(float (&x)[T], float scale, float div) {
-    if (scale != 0.f) {
-#pragma unroll
-        for (int v = 0; v < T; ++v) x[v] = x[v] * scale;
-    } else {
-#pragma unroll
-        for (int v = 0; v < T; ++v) x[v] = x[v] / div;
-    }
-}
-
-// The sum of a batch from leaves leaf(k, x): PW over its members, or over the
-// divided sums of its whole groups.
-template <int CNT, int SUB, int T, typename Leaf>
-__device__ __forceinline__ void batch_sum(const Leaf& leaf, float scale, float div, float (&out)[T]) {
-    if constexpr (SUB == 0) {
-        pw_tree<0, CNT, T>(leaf, out);
-    } else {
-        pw_tree<0, CNT / SUB, T>([&](int g, float (&x)[T]) {
-            pw_tree<0, SUB, T>([&](int k, float (&y)[T]) { leaf(g * SUB + k, y); }, x);
-            divide_group<T>(x, scale, div);
-        }, out);
     }
 }
 
@@ -257,7 +201,7 @@ __device__ __forceinline__ void split_step_slab(const Src& s, const Program& pr,
 }
 
 template <typename GT>
-__global__ __launch_bounds__(64 * kSplitWaves) void step_flat_split(SplitArgs sa) {
+__global__ __launch_bounds__(64 * kSplitWaves) void step_flat_split(FlatProgArgs sa) {
     extern __shared__ f32x4 split_lds[];
     constexpr int VEC = kSplitVec;
     const StepArgs& a = sa.a;
@@ -271,15 +215,9 @@ __global__ __launch_bounds__(64 * kSplitWaves) void step_flat_split(SplitArgs sa
     }
 }
 
-// The plan's arguments with the reduction program; a.chunks are the plan's
-// fine pieces (at most kSplitElems elements each).
-struct SplitPlanArgs {
-    PlanArgs a;
-    Program pr;
-};
-
+// a.chunks are the plan's fine pieces (at most kSplitElems elements each).
 template <typename GT>
-__global__ __launch_bounds__(64 * kSplitWaves) void step_plan_split(SplitPlanArgs sa) {
+__global__ __launch_bounds__(64 * kSplitWaves) void step_plan_split(PlanProgArgs sa) {
     extern __shared__ f32x4 split_lds[];
     bool again = false;
     for_plan_chunks<1>(sa.a, [&](const PlanSrcT<1>& s, const PlanChunk& ch, int32_t) {
@@ -292,13 +230,8 @@ __global__ __launch_bounds__(64 * kSplitWaves) void step_plan_split(SplitPlanArg
 // LARS pass 1 on the fine pieces: the mean gradient to the scratch, and the
 // piece's binary64 sums of p^2 and gbar^2 (wave 0; xor butterfly, so in a
 // fixed order).
-struct SplitLarsArgs {
-    LarsArgs la;
-    Program pr;
-};
-
 template <typename GT>
-__global__ __launch_bounds__(64 * kSplitWaves) void lars_norms_split(SplitLarsArgs sa) {
+__global__ __launch_bounds__(64 * kSplitWaves) void lars_norms_split(LarsProgArgs sa) {
     extern __shared__ f32x4 split_lds[];
     const LarsArgs& la = sa.la;
     const int lane = static_cast<int>(threadIdx.x) & 63;
