@@ -784,7 +784,7 @@ def separate_copy_out(wl, R, mode="auto", bcast=False):
         return True
     cached = wl.n_workers <= 16 and 8 * wl.n <= (288 << 20)   # parameters and momentum through the caches
     G, W = wl.groups, wl.workers_per_group
-    if W == 1 and G & (G - 1) and not ct_grouping(1, G) and not wl.group_sizes:
+    if W == 1 and G & (G - 1) and not wl.group_sizes:
         G, W = 1, wl.n_workers                                  # run as one group of all workers
     pow2_grouping = (not kernel_match(wl).endswith("_stream") and not wl.group_sizes
                      and W & (W - 1) == 0 and G & (G - 1) == 0)
@@ -820,10 +820,16 @@ def library_ranges(n):
     return list(zip(edges[:-1], edges[1:]))
 
 
-def ct_grouping(W, G):
-    """Whether the library has a compile-time kernel for G groups of W."""
+def ct_grouping(W, G, f32=None, listed=False):
+    """Whether the library has a compile-time step kernel for G groups of W
+    (f32: for that gradient type, else for either); listed: whether its pickers
+    know the grouping at all."""
+    if f32 is None and not listed:
+        return ct_grouping(W, G, True) or ct_grouping(W, G, False)
     pow2 = (1, 2, 4, 8, 16, 32, 64, 128)
-    if W * G > 128:
+    if W * G > 128 or (W == 1 and G not in pow2):
+        return False
+    if not listed and (f32 and W * G > 16 and not (W == 16 and G in pow2) or not f32 and G == 12):
         return False
     if G in pow2:
         return (W in pow2 or W in (3, 5, 6, 7, 12)) and (W <= 16 and G <= 16 or W <= 4 or G <= 4)
@@ -832,16 +838,17 @@ def ct_grouping(W, G):
 
 def kernel_match(wl, reduction=None, lars=False):
     G, W = wl.groups, wl.workers_per_group
-    ct = not wl.group_sizes and ct_grouping(W, G)
-    if (not ct and not wl.group_sizes and W == 1 and G & (G - 1) and reduction != "literal"):
-        ct = ct_grouping(G, 1)   # one worker per group: run as one group of all workers
     few = wl.n_workers <= 16
     f32 = wl.grad_dtype == "f32"
+    ct = not wl.group_sizes and ct_grouping(W, G, f32)
+    if (not ct and not wl.group_sizes and W == 1 and G & (G - 1) and reduction != "literal"):
+        ct = ct_grouping(G, 1, f32)   # one worker per group: run as one group of all workers
     if wl.tensor_sizes:   # the library's size rules for its split kernels (lsgd_split.hip)
         split = wl.n <= (1 << 19 if f32 and few else 1 << 20)
     else:
         split = wl.n <= (1 << 20 if f32 and not few else 1 << 18)
     if lars:
+        ct = ct or f32 and (W > 1 or G & (G - 1) == 0) and ct_grouping(W, G, listed=True)
         return "lars_norms_split" if split else "lars_norms_kernel" if ct else "lars_norms_stream"
     if wl.tensor_sizes:
         return "step_plan_split" if split else "step_plan_kernel" if ct else "step_plan_stream"

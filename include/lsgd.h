@@ -235,11 +235,14 @@ LSGD_API lsgd_status lsgd_copy_out(const float* params, int64_t n, void* const* 
  * replicas). Vectors longer than 2^26 elements are processed range by range
  * (about 2^24 elements each, edges on multiples of 2^20 elements: the step
  * kernel, then its copy-out pass) unless the step kernel writes every
- * replica itself. Compile-time kernels (the pairwise trees unrolled) serve
- * power-of-two group counts with groups of 1 to 16 workers (a power of two,
- * or 3, 5, 6, 7 or 12), 32 to 128 workers in up to 4 groups, 32 to 128
- * groups of up to 4 workers, and 3, 5, 6, 7 or 12 groups of 1 to 8, 12, 16
- * or 32 workers (N at most 128);
+ * replica itself. Short vectors (up to 2^18 elements, 2^20 for binary32
+ * gradients of more than 16 workers) take kernels that divide the workers'
+ * gradients over the waves of a workgroup. Compile-time kernels (the pairwise
+ * trees unrolled) serve binary32 gradients of up to 16 workers, and a power of
+ * two of groups of 16, and bfloat16 gradients, for power-of-two group counts
+ * with groups of 1 to 16 workers (a power of two, or 3, 5, 6, 7 or 12), 32 to
+ * 128 workers in up to 4 groups, 32 to 128 groups of up to 4 workers, and 3,
+ * 5, 6 or 7 (binary32: or 12) groups of 2 to 8, 12, 16 or 32 workers;
  * every other grouping takes a runtime-layout kernel. Arguments as for the
  * three calls above. The results are bit-identical to lsgd_group_mean, then
  * lsgd_global_mean, then lsgd_sgd_step, in every form.
@@ -334,10 +337,10 @@ LSGD_API lsgd_status lsgd_lr_schedule_step(const lsgd_lr_schedule* schedule, int
  * (e.g. the 161 tensors of ResNet-50, the model of Sec. 5.3) in ONE kernel
  * launch. The plan copies a chunk table and a pointer table to device memory
  * once; lsgd_step_plan then launches one kernel. Tensors are cut into pieces
- * of 2048 elements (4096 for binary32 gradients with more than 16 workers in
- * a grouping with a compile-time kernel, as listed for lsgd_step, except 32
- * or more groups and 16 groups of 3 or 4, and for binary32 gradients in any
- * other layout; times the launch shape's units_per_lane at creation); small
+ * of 2048 elements (4096 for binary32 gradients without a compile-time kernel,
+ * as listed for lsgd_step, or of 32 to 128 workers in groups of 16, and for
+ * bfloat16 gradients without one; times the launch shape's units_per_lane at
+ * creation); small
  * plans (up to 2^20 elements, 2^19 for binary32 gradients of at most 16
  * workers, with units_per_lane 1) into pieces of 256. One workgroup per piece.
  *   numel     [n_tensors] host int64, elements of each tensor (>= 0).

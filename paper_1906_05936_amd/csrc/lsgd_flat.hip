@@ -314,12 +314,11 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     };
     int32_t G = n_groups;
     FlatPick k{nullptr, 1};
-    if (W > 0) k = pick_ct(W, G);
-    if (!k.kernel && one_group_form(W, G, literal)) {
+    if (one_group_form(W, G, literal)) {
         W = n_workers;
         G = 1;
-        k = pick_ct(W, G);
     }
+    if (W > 0) k = pick_ct(W, G);
     a.n_groups = G;
     a.W = W;
 

@@ -10,16 +10,18 @@ using FlatKernel = void (*)(StepArgs);
 
 template <typename GT, int W, int G>
 FlatKernel np2_flat(bool cached) {
-    constexpr int U = tile_units<GT>(W * G, G);
-    if constexpr (cached_state_for(W * G))
-        if (cached) return flat_step_kernel<GT, W, G, U, 1>();
-    return flat_step_kernel<GT, W, G, U, 0>();
+    if constexpr (ct_serves<GT>(W, G)) {
+        constexpr int U = tile_units<GT>(W * G);
+        if constexpr (cached_state_for(W * G))
+            if (cached) return flat_step_kernel<GT, W, G, U, 1>();
+        return flat_step_kernel<GT, W, G, U, 0>();
+    }
+    return nullptr;
 }
 
 template <typename GT, int G>
 FlatKernel np2_flat_w(int W, bool cached) {
     switch (W) {
-        case 1: return np2_flat<GT, 1, G>(cached);
         case 2: return np2_flat<GT, 2, G>(cached);
         case 3: return np2_flat<GT, 3, G>(cached);
         case 4: return np2_flat<GT, 4, G>(cached);
@@ -57,7 +59,7 @@ FlatKernel np2_flat_g(int W, int G, bool cached) {
 Np2FlatPick pick_flat_np2(int W, int G, bool cached, bool bf16) {
     const FlatKernel k = bf16 ? np2_flat_g<uint16_t>(W, G, cached) : np2_flat_g<float>(W, G, cached);
     if (!k) return Np2FlatPick{nullptr, 1};
-    return Np2FlatPick{k, bf16 ? tile_units<uint16_t>(W * G, G) : tile_units<float>(W * G, G)};
+    return Np2FlatPick{k, bf16 ? tile_units<uint16_t>(W * G) : tile_units<float>(W * G)};
 }
 
 }  // namespace lsgd

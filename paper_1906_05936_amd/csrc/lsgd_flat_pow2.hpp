@@ -15,10 +15,13 @@ namespace lsgd {
 // the caches when `cached` (instantiated only where cached_state_for holds).
 template <typename GT, int W, int G>
 FlatKernel flat_ct(bool cached) {
-    constexpr int U = tile_units<GT>(W * G, G);
-    if constexpr (cached_state_for(W * G))
-        if (cached) return flat_step_kernel<GT, W, G, U, 1>();
-    return flat_step_kernel<GT, W, G, U, 0>();
+    if constexpr (ct_serves<GT>(W, G)) {
+        constexpr int U = tile_units<GT>(W * G);
+        if constexpr (cached_state_for(W * G))
+            if (cached) return flat_step_kernel<GT, W, G, U, 1>();
+        return flat_step_kernel<GT, W, G, U, 0>();
+    }
+    return nullptr;
 }
 
 template <typename GT, int W>
@@ -77,7 +80,7 @@ FlatPick pick_flat(int W, int G, bool cached) {
         case 64: k = pick_flat_big_w<GT, 64>(G, cached); break;
         case 128: k = pick_flat_big_w<GT, 128>(G, cached); break;
     }
-    if (k) return FlatPick{k, tile_units<GT>(W * G, G)};
+    if (k) return FlatPick{k, tile_units<GT>(W * G)};
     return FlatPick{nullptr, 1};
 }
 

@@ -535,29 +535,34 @@ struct MeanArgs {
 constexpr int kUnrollFloats = 128;
 constexpr int kStreamFloats = 128;
 
-// Units per lane tile in the compile-time fused kernels for N = W*G
-// gradients. Binary32: two units (visited stream-major; measured +6-8% over
-// one) while the whole tree fits the unrolled form (N <= 16), four once the
-// groups stream through the accumulator (N >= 32: +3-8% over two at 8x4,
-// 4x8, 8x8, 16x4, 2x16 and 16x8, in same-process A/Bs; at N <= 16 three or
-// four units lose 1-3%, since they leave the unrolled form). bfloat16 tiles
-// stay at one unit: two units measured -1% at 4x4, +0.6% / -0.2% on the
-// 3.5e8-element 8x8 workload (step kernel alone / whole step), +1.6% at 8x8
-// and +4% at 16x8 on 2.6e7 elements.
-// With 32 or more groups the pairwise accumulator over groups holds
-// log2(G) + 1 partial sums of the tile, and four-unit tiles spilled to
-// scratch (2.3 KB per lane at 4x32 and 2x32): those kernels take two units.
-// So do 16 groups of 4 (and of 3), whose four-unit kernels spilled 2.3 KB
-// per lane; with two (158 VGPRs, no scratch) the ResNet-50-sized 16x4 step
-// ran 49% faster with 64 replicas, 87% without, the plan step 5% and the
-// LARS step 11% faster.
+// The groupings that compile-time kernels serve (among those the pickers
+// list); every other one takes the stream kernels (lsgd_stream.hpp). Step of
+// 1e7 elements without replicas, two states in turn, compile-time / stream, us:
+//   binary32, N <= 16: 4x4 127 / 135, 8x1 72 / 82, 1x5 55 / 70;
+//   binary32, N > 16: 8x4 256 / 229, 8x8 480 / 428, 1x64 477 / 429, 16x8 904 /
+//     822, 5x5 195 / 186, 4x6 187 / 180, 32x2 434 / 431, but groups of 16: 2x16
+//     225 / 231, 4x16 425 / 431, 8x16 807 / 822 (3x16 347 / 331);
+//   bfloat16: 3x5 72 / 81, 4x6 107 / 109, 8x8 242 / 241, 16x8 457 / 450, but 12
+//     groups: 12x2 120 / 108, 12x5 230 / 219, 12x3 148 / 149.
+// One worker per group in a count that is no power of two runs as one group
+// (one_group_form) or, in the paper-literal reduction, in the stream kernels.
 template <typename GT>
-constexpr int tile_units(int n_workers, int n_groups = 1) {
-    return sizeof(GT) == 4 ? (n_workers * 2 * Unit<GT>::VEC <= kUnrollFloats || n_groups >= 32 ||
-                                      (n_groups == 16 && (n_workers == 48 || n_workers == 64))
-                                  ? 2
-                                  : 4)
-                           : 1;
+constexpr bool ct_serves(int W, int G) {
+    if (W == 1 && (G & (G - 1)) != 0) return false;
+    return sizeof(GT) == 4 ? W * G <= 16 || (W == 16 && (G & (G - 1)) == 0) : G != 12;
+}
+
+// Units per lane tile in the compile-time fused kernels for N gradients.
+// Binary32: two units (visited stream-major; measured +6-8% over one) while the
+// whole tree fits the unrolled form (N <= 16), four once the groups stream
+// through the accumulator (+3-8% over two; at N <= 16 three or four units lose
+// 1-3%, since they leave the unrolled form). bfloat16 tiles stay at one unit:
+// two units measured -1% at 4x4, +0.6% / -0.2% on the 3.5e8-element 8x8
+// workload (step kernel alone / whole step), +1.6% at 8x8 and +4% at 16x8 on
+// 2.6e7 elements.
+template <typename GT>
+constexpr int tile_units(int n_workers) {
+    return sizeof(GT) == 4 ? (n_workers * 2 * Unit<GT>::VEC <= kUnrollFloats ? 2 : 4) : 1;
 }
 
 // Pairwise sum of K leaves (compile-time K) of T floats each: unrolled while
@@ -844,16 +849,14 @@ struct WaveCapEntry {
     short W, G, cap;
 };
 constexpr WaveCapEntry kWaveCapF32[] = {
-    {1, 8, 2},  {1, 16, 2}, {1, 128, 2}, {2, 4, 2},  {2, 8, 2},  {2, 12, 2}, {3, 3, 2},  {3, 4, 2},
-    {3, 5, 2},  {4, 2, 2},  {4, 4, 2},   {4, 6, 2},  {5, 2, 2},  {5, 3, 2},  {6, 2, 2},  {8, 1, 2},
-    {12, 1, 2}, {12, 5, 2}, {16, 1, 2},  {16, 2, 2}, {16, 4, 2}, {16, 8, 2}, {1, 2, 3},  {1, 3, 3},
-    {1, 4, 3},  {1, 5, 3},  {1, 6, 3},   {2, 1, 3},  {2, 2, 3},  {3, 1, 3},  {3, 2, 3},  {3, 8, 3},
-    {3, 12, 3}, {3, 16, 3}, {4, 1, 3},   {4, 3, 3},  {5, 1, 3},  {6, 1, 3},  {8, 6, 3},  {12, 3, 3},
+    {1, 8, 2}, {1, 16, 2}, {2, 4, 2}, {2, 8, 2}, {3, 3, 2}, {3, 4, 2}, {3, 5, 2}, {4, 2, 2}, {4, 4, 2},
+    {5, 2, 2}, {5, 3, 2}, {6, 2, 2}, {8, 1, 2}, {12, 1, 2}, {16, 1, 2}, {16, 2, 2}, {16, 4, 2}, {16, 8, 2},
+    {1, 2, 3}, {1, 4, 3}, {2, 1, 3}, {2, 2, 3}, {3, 1, 3}, {3, 2, 3}, {4, 1, 3}, {4, 3, 3}, {5, 1, 3},
+    {6, 1, 3},
 };
 constexpr WaveCapEntry kWaveCapBF16[] = {
-    {1, 2, 2}, {1, 4, 2},  {2, 1, 2},  {2, 2, 2}, {3, 1, 2}, {3, 8, 2}, {3, 12, 2},
-    {3, 16, 2}, {3, 32, 2}, {4, 1, 2}, {5, 16, 2}, {8, 1, 2}, {8, 6, 2}, {8, 12, 2},
-    {1, 8, 3}, {1, 16, 3}, {2, 4, 3}, {4, 2, 3}, {5, 1, 3}, {6, 1, 3},
+    {1, 2, 2}, {1, 4, 2}, {2, 1, 2}, {2, 2, 2}, {3, 1, 2}, {3, 8, 2}, {3, 16, 2}, {3, 32, 2}, {4, 1, 2},
+    {5, 16, 2}, {8, 1, 2}, {8, 6, 2}, {1, 8, 3}, {1, 16, 3}, {2, 4, 3}, {4, 2, 3}, {5, 1, 3}, {6, 1, 3},
 };
 template <typename GT>
 constexpr int flat_wave_cap(int W, int G) {

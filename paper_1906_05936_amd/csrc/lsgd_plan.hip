@@ -69,7 +69,7 @@ static_assert(piece_elems<float>(1) % 8 == 0 && piece_elems<uint16_t>(1) % 8 == 
 template <typename GT>
 PlanPick pick_plan(int W, int G, bool cached = false) {
     const PlanKernel k = pick_plan_pow2<GT>(W, G, cached);
-    if (k) return PlanPick{k, tile_units<GT>(W * G, G)};
+    if (k) return PlanPick{k, tile_units<GT>(W * G)};
     if (np2_group_count(G)) {   // group counts 3, 5, 6, 7 and 12 (lsgd_np2.hpp)
         const Np2PlanPick q = pick_plan_np2(W, G, cached, sizeof(GT) == 2);
         if (q.kernel) return PlanPick{q.kernel, q.tile};
@@ -342,7 +342,9 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     std::vector<PlanChunk> chunks;
     // one tile pass of the kernel, times the launch shape's passes per workgroup
     const int32_t W = equal ? n_workers / n_groups : 0;
-    const int tile = gdt == LSGD_BF16 ? pick_plan<uint16_t>(W, n_groups).tile : pick_plan<float>(W, n_groups).tile;
+    const bool as_one = one_group_form(W, n_groups, false);
+    const int32_t tW = as_one ? n_workers : W, tG = as_one ? 1 : n_groups;
+    const int tile = gdt == LSGD_BF16 ? pick_plan<uint16_t>(tW, tG).tile : pick_plan<float>(tW, tG).tile;
     const int64_t kPiece = (gdt == LSGD_BF16 ? piece_elems<uint16_t>(tile) : piece_elems<float>(tile)) *
                            launch_passes_per_block();
     std::vector<int64_t> gbar_off(n_tensors, 0);

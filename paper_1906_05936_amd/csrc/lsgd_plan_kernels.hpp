@@ -121,24 +121,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, CAP))
 // with caps 2 and 3 against the uncapped kernel; a grouping is listed where
 // a cap gains at least one point of the 8 TB/s peak.
 constexpr WaveCapEntry kPlanWaveCapF32[] = {
-    {1, 4, 2}, {2, 2, 2}, {2, 12, 2}, {4, 1, 2}, {5, 1, 2}, {16, 2, 2}, {1, 2, 3}, {1, 3, 3},
-    {1, 5, 3}, {1, 6, 3}, {2, 1, 3}, {2, 3, 3}, {3, 1, 3}, {3, 16, 3}, {6, 16, 3}, {8, 6, 3},
-    {12, 3, 3}, {12, 4, 3}, {12, 5, 3},
+    {1, 4, 2}, {2, 2, 2}, {4, 1, 2}, {5, 1, 2}, {16, 2, 2}, {1, 2, 3}, {2, 1, 3}, {2, 3, 3}, {3, 1, 3},
 };
 constexpr WaveCapEntry kPlanWaveCapBF16[] = {
-    {1, 2, 2}, {1, 4, 2}, {1, 8, 2}, {2, 1, 2}, {2, 2, 2}, {2, 3, 2}, {2, 5, 2}, {2, 64, 2},
-    {3, 1, 2}, {3, 2, 2}, {3, 3, 2}, {3, 6, 2}, {3, 8, 2}, {3, 12, 2}, {3, 16, 2}, {3, 32, 2},
-    {4, 1, 2}, {4, 2, 2}, {4, 32, 2}, {5, 1, 2}, {5, 2, 2}, {5, 6, 2}, {5, 8, 2}, {5, 12, 2},
-    {5, 16, 2}, {6, 1, 2}, {6, 8, 2}, {6, 12, 2}, {8, 1, 2}, {8, 16, 2}, {12, 5, 2}, {12, 6, 2},
-    {12, 8, 2}, {2, 4, 3}, {2, 8, 3}, {4, 3, 3},
+    {1, 2, 2}, {1, 4, 2}, {1, 8, 2}, {2, 1, 2}, {2, 2, 2}, {2, 3, 2}, {2, 5, 2}, {2, 64, 2}, {3, 1, 2},
+    {3, 2, 2}, {3, 3, 2}, {3, 6, 2}, {3, 8, 2}, {3, 16, 2}, {3, 32, 2}, {4, 1, 2}, {4, 2, 2}, {4, 32, 2},
+    {5, 1, 2}, {5, 2, 2}, {5, 6, 2}, {5, 8, 2}, {5, 16, 2}, {6, 1, 2}, {6, 8, 2}, {8, 1, 2}, {8, 16, 2},
+    {12, 5, 2}, {12, 6, 2}, {12, 8, 2}, {2, 4, 3}, {2, 8, 3}, {4, 3, 3},
 };
 // The LARS norms kernel (pass 1), same measurement of the whole LARS step; its
 // run-to-run spread reached three points, so an entry gains at least three.
 constexpr WaveCapEntry kLarsWaveCapBF16[] = {
-    {1, 16, 2}, {2, 8, 2}, {2, 32, 2}, {3, 6, 2}, {3, 8, 2}, {3, 12, 2}, {3, 16, 2}, {3, 32, 2},
-    {4, 4, 2}, {4, 16, 2}, {5, 6, 2}, {5, 12, 2}, {8, 2, 2}, {8, 8, 2}, {16, 1, 2}, {16, 8, 2},
-    {5, 2, 3}, {5, 4, 3}, {5, 8, 3}, {5, 16, 3}, {6, 2, 3}, {6, 4, 3}, {6, 6, 3}, {12, 1, 3},
-    {12, 3, 3}, {12, 4, 3},
+    {1, 16, 2}, {2, 8, 2}, {2, 32, 2}, {3, 6, 2}, {3, 8, 2}, {3, 16, 2}, {3, 32, 2}, {4, 4, 2}, {4, 16, 2},
+    {5, 6, 2}, {8, 2, 2}, {8, 8, 2}, {16, 1, 2}, {16, 8, 2}, {5, 2, 3}, {5, 4, 3}, {5, 8, 3}, {5, 16, 3},
+    {6, 2, 3}, {6, 4, 3}, {6, 6, 3}, {12, 1, 3}, {12, 3, 3}, {12, 4, 3},
 };
 template <size_t K>
 constexpr int wave_cap_in(const WaveCapEntry (&t)[K], int W, int G) {
@@ -357,13 +353,35 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(1, CAP))
     lars_norms_body<GT, W, G, U>(la, lds);
 }
 
-// The LARS norms kernel for (W, G), capped where kLarsWaveCapBF16 lists it.
+// The groupings whose LARS norms have a compile-time kernel. Binary32 keeps it
+// for more than 16 workers too: a LARS pass ends every piece with a reduction,
+// and the stream kernel's two-unit tiles cover it less well (1.2e7 elements,
+// whole step, compile-time / stream, us: 8x4 346 / 361, 8x8 609 / 633, 16x8
+// 1096 / 1158, 4x6 274 / 295; bfloat16 12x2 198 / 179).
+template <typename GT>
+constexpr bool lars_ct_serves(int W, int G) {
+    return sizeof(GT) == 4 ? W > 1 || (G & (G - 1)) == 0 : ct_serves<GT>(W, G);
+}
+
+// Units per lane tile of the LARS norms kernels: those of the step, but two
+// where four spilled to scratch (32 or more groups; 16 groups of 3 or 4).
+template <typename GT>
+constexpr int lars_tile_units(int n_workers, int n_groups) {
+    const bool many = n_groups >= 32 || (n_groups == 16 && (n_workers == 48 || n_workers == 64));
+    return sizeof(GT) == 4 && many ? 2 : tile_units<GT>(n_workers);
+}
+
+// The LARS norms kernel for (W, G), capped where kLarsWaveCapBF16 lists it;
+// null where no compile-time kernel serves the grouping.
 template <typename GT, int W, int G>
-constexpr auto lars_kernel_for() {
-    constexpr int U = tile_units<GT>(W * G, G);
-    constexpr int cap = sizeof(GT) == 2 ? wave_cap_in(kLarsWaveCapBF16, W, G) : 0;
-    if constexpr (cap != 0) return lars_norms_kernel_cap<GT, W, G, U, cap>;
-    else return lars_norms_kernel<GT, W, G, U>;
+constexpr void (*lars_kernel_for())(LarsArgs) {
+    if constexpr (lars_ct_serves<GT>(W, G)) {
+        constexpr int U = lars_tile_units<GT>(W * G, G);
+        constexpr int cap = sizeof(GT) == 2 ? wave_cap_in(kLarsWaveCapBF16, W, G) : 0;
+        if constexpr (cap != 0) return lars_norms_kernel_cap<GT, W, G, U, cap>;
+        else return lars_norms_kernel<GT, W, G, U>;
+    }
+    return nullptr;
 }
 
 // The trust ratio of tensor t from the partials of its chunks [c0, c1), valid

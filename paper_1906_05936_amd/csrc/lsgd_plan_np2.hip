@@ -11,16 +11,18 @@ using PlanKernel = void (*)(PlanArgs);
 
 template <typename GT, int W, int G>
 PlanKernel np2_plan(bool cached) {
-    constexpr int U = tile_units<GT>(W * G, G);
-    if constexpr (cached_state_for(W * G))
-        if (cached) return plan_step_kernel<GT, W, G, U, 1>();
-    return plan_step_kernel<GT, W, G, U, 0>();
+    if constexpr (ct_serves<GT>(W, G)) {
+        constexpr int U = tile_units<GT>(W * G);
+        if constexpr (cached_state_for(W * G))
+            if (cached) return plan_step_kernel<GT, W, G, U, 1>();
+        return plan_step_kernel<GT, W, G, U, 0>();
+    }
+    return nullptr;
 }
 
 template <typename GT, int G>
 PlanKernel np2_plan_w(int W, bool cached) {
     switch (W) {
-        case 1: return np2_plan<GT, 1, G>(cached);
         case 2: return np2_plan<GT, 2, G>(cached);
         case 3: return np2_plan<GT, 3, G>(cached);
         case 4: return np2_plan<GT, 4, G>(cached);
@@ -49,7 +51,6 @@ Np2LarsKernel np2_lars() {
 template <typename GT, int G>
 Np2LarsKernel np2_lars_w(int W) {
     switch (W) {
-        case 1: return np2_lars<GT, 1, G>();
         case 2: return np2_lars<GT, 2, G>();
         case 3: return np2_lars<GT, 3, G>();
         case 4: return np2_lars<GT, 4, G>();
@@ -99,7 +100,7 @@ Np2LarsKernel np2_lars_g(int W, int G) {
 Np2PlanPick pick_plan_np2(int W, int G, bool cached, bool bf16) {
     const PlanKernel k = bf16 ? np2_plan_g<uint16_t>(W, G, cached) : np2_plan_g<float>(W, G, cached);
     if (!k) return Np2PlanPick{nullptr, 1};
-    return Np2PlanPick{k, bf16 ? tile_units<uint16_t>(W * G, G) : tile_units<float>(W * G, G)};
+    return Np2PlanPick{k, bf16 ? tile_units<uint16_t>(W * G) : tile_units<float>(W * G)};
 }
 
 Np2LarsKernel pick_lars_np2(int W, int G, bool bf16) {

@@ -9,10 +9,13 @@ namespace lsgd {
 
 template <typename GT, int W, int G>
 PlanKernel plan_ct(bool cached) {
-    constexpr int U = tile_units<GT>(W * G, G);
-    if constexpr (cached_state_for(W * G))
-        if (cached) return plan_step_kernel<GT, W, G, U, 1>();
-    return plan_step_kernel<GT, W, G, U, 0>();
+    if constexpr (ct_serves<GT>(W, G)) {
+        constexpr int U = tile_units<GT>(W * G);
+        if constexpr (cached_state_for(W * G))
+            if (cached) return plan_step_kernel<GT, W, G, U, 1>();
+        return plan_step_kernel<GT, W, G, U, 0>();
+    }
+    return nullptr;
 }
 
 template <typename GT, int W>

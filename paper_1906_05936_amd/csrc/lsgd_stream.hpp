@@ -82,13 +82,12 @@ __device__ __forceinline__ u32x4 load_element(const void* g, int64_t e) {
 
 // The mean gradient of a lane tile. stk: this workgroup's LDS, slot s of a
 // lane at (s * T/4 + part) * kBlock + thread (conflict-free 128-bit accesses).
-template <typename GT, int U, typename Src>
+// kAhead: the next batch's loads are issued before the additions in LDS.
+template <typename GT, int U, bool kAhead, typename Src>
 __device__ __forceinline__ void stream_mean(const Src& s, const Program& pr, const Tile<U>& t, f32x4* stk,
                                             float (&x)[U * Unit<GT>::VEC]) {
     constexpr int VEC = Unit<GT>::VEC;
     constexpr int T = U * VEC;
-    // binary32: the next batch's loads are issued before the additions in LDS
-    constexpr bool kAhead = sizeof(GT) == 4;
     const float scale = pr.group_scale, div = pr.group_div;
     int sp = static_cast<int>(threadIdx.x);   // the stack's top, as an index of stk
     auto add_top = [&] {
@@ -173,7 +172,7 @@ __device__ __forceinline__ void stream_step_tile(const Src& s, const Program& pr
     constexpr int T = U * VEC;
     if (t.tail) {   // one element per lane
         float g[T];
-        stream_mean<GT, U>(s, pr, t, stk, g);
+        stream_mean<GT, U, sizeof(GT) == 4>(s, pr, t, stk, g);
         if (!t.own[0]) return;
         const int64_t e = t.e[0];
         float g1[1] = {g[0]}, p[1] = {gload_ptr<float>(s.p())[e]}, m[1] = {gload_ptr<float>(s.m())[e]};
@@ -191,7 +190,7 @@ __device__ __forceinline__ void stream_step_tile(const Src& s, const Program& pr
     }
     float p[T], m[T], g[T];
     load_state<VEC, U, false>(s, t.e, VEC, p, m);   // their latency overlaps the gradient stream
-    stream_mean<GT, U>(s, pr, t, stk, g);
+    stream_mean<GT, U, sizeof(GT) == 4>(s, pr, t, stk, g);
     sgd_update<T>(s.hyper(), g, p, m);
     // a lane's units past the end are its last ones: q units are its own
 #pragma unroll
@@ -237,12 +236,15 @@ __global__ __launch_bounds__(kBlock) void step_plan_stream(PlanProgArgs pa) {
     });
 }
 
-// LARS pass 1: the mean gradient to the scratch and the piece's sums of squares.
+// LARS pass 1: the mean gradient to the scratch and the piece's sums of
+// squares. Two units per lane and no loads ahead for either type, so that
+// several waves per SIMD cover one another's reductions (binary32 with the
+// step's form, one wave per SIMD: 8x4 409 us for the whole LARS step, now 361).
 template <typename GT>
 __global__ __launch_bounds__(kBlock) void lars_norms_stream(LarsProgArgs sa) {
     extern __shared__ f32x4 stream_lds[];
     __shared__ double sums[kBlock / 64][2];
-    constexpr int U = StreamTile<GT>::U;
+    constexpr int U = 2;
     constexpr int VEC = Unit<GT>::VEC;
     constexpr int T = U * VEC;
     const LarsArgs& la = sa.la;
@@ -253,7 +255,7 @@ __global__ __launch_bounds__(kBlock) void lars_norms_stream(LarsProgArgs sa) {
         for (int64_t i = 0; i < tiles; ++i) {
             const Tile<U> t = tile_at<U, VEC>(ch.start, ch.len, i);
             float g[T];
-            stream_mean<GT, U>(s, sa.pr, t, stream_lds, g);
+            stream_mean<GT, U, false>(s, sa.pr, t, stream_lds, g);
             if (t.tail) {
                 if (t.own[0]) {
                     const float p1[1] = {gload_ptr<float>(s.p())[t.e[0]]}, g1[1] = {g[0]};
@@ -262,13 +264,16 @@ __global__ __launch_bounds__(kBlock) void lars_norms_stream(LarsProgArgs sa) {
                 }
                 continue;
             }
+            // all units' parameters in one go (addresses past the end are
+            // clamped): one after the other they cost a memory latency each
+            float p[T];
+#pragma unroll
+            for (int q = 0; q < U; ++q) load_f32_cached<VEC, false>(s.p(), t.e[q], VEC, slice<VEC, T>(p, q));
 #pragma unroll
             for (int q = 0; q < U; ++q) {
-                if (!t.own[q]) break;
-                float p[VEC];
+                if (!t.own[q]) continue;
                 store_f32_cached<VEC, false>(gb, t.e[q], VEC, slice<VEC, T>(g, q));
-                load_f32_cached<VEC, false>(s.p(), t.e[q], VEC, p);
-                lars_accumulate<VEC>(p, slice<VEC, T>(g, q), VEC, sp, sg);
+                lars_accumulate<VEC>(slice<VEC, T>(p, q), slice<VEC, T>(g, q), VEC, sp, sg);
             }
         }
         block_sum2(sp, sg, sums);
