@@ -2,11 +2,17 @@
 method runs in the library's HIP kernels. torch supplies device memory and the
 stream; nothing here computes on tensor values.
 
+The calls over lists of tensors first try the extension _marshal, which reads
+the tensors natively and makes the same C call; it declines anything but plain
+arguments (and says nothing about why), and the checks here then run as they
+stand.
+
 The C ABI is declared in include/lsgd.h; the Python names mirror it:
 ``group_mean`` -> lsgd_group_mean, ``global_mean`` -> lsgd_global_mean,
 ``sgd_step`` -> lsgd_sgd_step, ``step`` -> lsgd_step, ``Plan`` ->
 lsgd_plan_create / lsgd_step_plan / lsgd_plan_destroy.
 """
+import contextlib
 import ctypes
 import os
 
@@ -106,6 +112,12 @@ def _load():
 
 lib = _load()
 
+from . import _marshal  # noqa: E402  (finds liblsgd.so next to it; torch is loaded above)
+
+_current_device = torch._C._cuda_getDevice
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_HERE_ALREADY = contextlib.nullcontext()
+
 
 def check(status):
     """Raise LsgdError for a non-OK status returned by the library."""
@@ -172,6 +184,23 @@ def _stream(stream, device):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+def _on(index):
+    """Makes GPU `index` current for a with block (which costs nothing where it is)."""
+    return _HERE_ALREADY if _current_device() == index else torch.cuda.device(index)
+
+
+def _native_target(t, stream):
+    """(device index, raw stream) for a native call on tensor t's device, or
+    None where the call has to take the general path (not a tensor on the
+    current GPU)."""
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+        return None
+    index = t.get_device()
+    if _current_device() != index:
+        return None
+    return index, _raw_stream(index) if stream is None else stream.cuda_stream
+
+
 def set_launch_shape(xcd_chunk, blocks_per_cu, units_per_lane=1):
     """lsgd_set_launch_shape: process-wide launch shape (never changes results)."""
     check(lib.lsgd_set_launch_shape(int(xcd_chunk), int(blocks_per_cu), int(units_per_lane)))
@@ -225,6 +254,15 @@ def step(params, momentum, grads, group_of_worker, n_groups, lr, momentum_coef, 
     the learning rate when the kernel runs. Enqueued on ``stream`` (default: the
     current stream).
     """
+    target = _native_target(params, stream)
+    if target is not None:
+        red = 0 if reduction in ("mean_of_means", REDUCE_MEAN_OF_MEANS) else \
+            1 if reduction in ("literal", REDUCE_LITERAL) else None
+        st = None if red is None else _marshal.step(
+            params, momentum, grads, group_of_worker, n_groups, lr, momentum_coef, weight_decay, replicas, red,
+            1 if broadcast_grad else 0, lr_device, *target)
+        if st is not None:
+            return check(st)
     n = params.numel()
     dev = params.device
     _dev_tensor(params, "params", torch.float32)
@@ -272,6 +310,11 @@ def group_mean(grads, group_of_worker, n_groups, out, stream=None):
     """lsgd_group_mean: out[j] = mean over the members of group j (float32 tensors)."""
     if not grads:
         raise ValueError("grads is empty")
+    target = _native_target(grads[0], stream)
+    if target is not None:
+        st = _marshal.group_mean(grads, group_of_worker, n_groups, out, *target)
+        if st is not None:
+            return check(st)
     n = grads[0].numel()
     dev = grads[0].device
     for g in grads:
@@ -290,6 +333,11 @@ def group_mean(grads, group_of_worker, n_groups, out, stream=None):
 
 def global_mean(group_means, out, stream=None):
     """lsgd_global_mean: out = mean of the float32 group-mean tensors."""
+    target = _native_target(out, stream)
+    if target is not None:
+        st = _marshal.global_mean(group_means, out, *target)
+        if st is not None:
+            return check(st)
     n = out.numel()
     dev = out.device
     _dev_tensor(out, "grad mean", torch.float32)
@@ -303,6 +351,11 @@ def global_mean(group_means, out, stream=None):
 
 def sgd_step(params, momentum, grad_mean, lr, momentum_coef, weight_decay, replicas=(), stream=None):
     """lsgd_sgd_step: update and copy-out from a precomputed mean gradient."""
+    target = _native_target(params, stream)
+    if target is not None:
+        st = _marshal.sgd_step(params, momentum, grad_mean, lr, momentum_coef, weight_decay, replicas, *target)
+        if st is not None:
+            return check(st)
     n = params.numel()
     dev = params.device
     _dev_tensor(params, "params", torch.float32)
@@ -321,6 +374,11 @@ def sgd_step(params, momentum, grad_mean, lr, momentum_coef, weight_decay, repli
 
 def copy_out(params, replicas, stream=None):
     """lsgd_copy_out: every replica = params (binary32, or bfloat16 nearest-even)."""
+    target = _native_target(params, stream)
+    if target is not None:
+        st = _marshal.copy_out(params, replicas, *target)
+        if st is not None:
+            return check(st)
     n = params.numel()
     dev = params.device
     _dev_tensor(params, "params", torch.float32)
@@ -357,6 +415,7 @@ class Plan:
         gdt = _common_dtype([g for gl in grads for g in gl], "grads")
         rdt = _common_dtype([r for rl in replicas for r in rl], "replicas")
         self.device = dev
+        self._index = dev.index if dev is not None else None
         self._keep = (list(params), list(momentum), [list(g) for g in grads],
                       [list(r) for r in replicas])
         handle = ctypes.c_void_p()
@@ -371,6 +430,9 @@ class Plan:
         check(st)
         self._handle = handle
 
+    def _raw(self, stream):
+        return _raw_stream(self._index) if stream is None else stream.cuda_stream
+
     def step(self, lr, momentum_coef, weight_decay, stream=None, lr_device=None,
              reduction="mean_of_means", broadcast_grad=False):
         """lsgd_step_plan, or lsgd_step_plan_ex with the paper-literal
@@ -378,22 +440,22 @@ class Plan:
         if self._handle is None:
             raise RuntimeError("plan is closed")
         plain = reduction in ("mean_of_means", REDUCE_MEAN_OF_MEANS) and not broadcast_grad and lr_device is None
-        with torch.cuda.device(self.device):
+        with _on(self._index):
             if plain:
                 st = lib.lsgd_step_plan(self._handle, lr, momentum_coef, weight_decay,
-                                        _stream(stream, self.device))
+                                        self._raw(stream))
             else:
                 opts = _options(reduction, broadcast_grad, lr_device, self.device)
                 st = lib.lsgd_step_plan_ex(self._handle, lr, momentum_coef, weight_decay,
-                                           ctypes.byref(opts), _stream(stream, self.device))
+                                           ctypes.byref(opts), self._raw(stream))
         check(st)
 
     def copy_out(self, stream=None):
         """lsgd_plan_copy_out: every replica tensor = its params tensor."""
         if self._handle is None:
             raise RuntimeError("plan is closed")
-        with torch.cuda.device(self.device):
-            st = lib.lsgd_plan_copy_out(self._handle, _stream(stream, self.device))
+        with _on(self._index):
+            st = lib.lsgd_plan_copy_out(self._handle, self._raw(stream))
         check(st)
 
     def set_lars_exclude(self, exclude=None):
@@ -406,7 +468,7 @@ class Plan:
             if len(exclude) != len(self._keep[0]):
                 raise ValueError("exclude needs one flag per tensor")
             arr = (ctypes.c_uint8 * len(exclude))(*[1 if x else 0 for x in exclude])
-        with torch.cuda.device(self.device):
+        with _on(self._index):
             check(lib.lsgd_plan_set_lars_exclude(self._handle, arr))
 
     def lars_workspace_size(self):
@@ -427,12 +489,10 @@ class Plan:
         if self._handle is None:
             raise RuntimeError("plan is closed")
         if workspace is None:
-            need = self.lars_workspace_size()
-            ws = getattr(self, "_lars_ws", None)
-            if ws is None or ws.numel() < need:
-                ws = torch.empty(max(need, 256), dtype=torch.uint8, device=self.device)
-                self._lars_ws = ws
-            workspace = ws
+            workspace = getattr(self, "_lars_ws", None)
+            if workspace is None:   # the plan's size, and so its need, never changes
+                workspace = torch.empty(max(self.lars_workspace_size(), 256), dtype=torch.uint8, device=self.device)
+                self._lars_ws = workspace
         tp = None
         if trust_out is not None:
             _dev_tensor(trust_out, "trust_out", torch.float32, len(self._keep[0]), self.device)
@@ -441,10 +501,10 @@ class Plan:
         if lr_device is not None:
             _dev_tensor(lr_device, "lr_device", torch.float32, 1, self.device)
             lp = lr_device.data_ptr()
-        with torch.cuda.device(self.device):
+        with _on(self._index):
             st = lib.lsgd_lars_step_plan(self._handle, lr, momentum_coef, weight_decay, trust_coef,
                                          workspace.data_ptr(), workspace.numel() * workspace.element_size(),
-                                         tp, lp, _stream(stream, self.device))
+                                         tp, lp, self._raw(stream))
         check(st)
 
     def lars_step_noalloc(self, lr, momentum_coef, weight_decay, trust_coef, trust_out=None, stream=None,
@@ -462,9 +522,9 @@ class Plan:
         if lr_device is not None:
             _dev_tensor(lr_device, "lr_device", torch.float32, 1, self.device)
             lp = lr_device.data_ptr()
-        with torch.cuda.device(self.device):
+        with _on(self._index):
             st = lib.lsgd_lars_step_plan_noalloc(self._handle, lr, momentum_coef, weight_decay, trust_coef, tp,
-                                                 lp, _stream(stream, self.device))
+                                                 lp, self._raw(stream))
         check(st)
 
     def close(self):

@@ -1,6 +1,7 @@
-"""Builds liblsgd.so (HIP, gfx950) in-tree next to this file.
+"""Builds liblsgd.so (HIP, gfx950) and the binding's extension _marshal.so
+(host code) in-tree next to this file.
 
-Every translation unit is compiled with:
+Every HIP translation unit is compiled with:
   -ffp-contract=off       no a*b+c contraction into fused multiply-add: each
                           operation of the update is rounded on its own;
   -Xclang -target-feature -Xclang -packed-fp32-ops
@@ -68,10 +69,46 @@ def _compile(src, verbose):
     return obj
 
 
+# The binding's CPython extension (csrc/marshal.cpp): host code, against the
+# headers of the installed torch and Python.
+MARSHAL = os.path.join(PKG, "_marshal.so")
+
+
+def _compile_marshal(verbose):
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    obj = os.path.join(BUILD_DIR, "marshal.o")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + INCLUDE,
+           "-isystem", sysconfig.get_paths()["include"]]
+    for d in cpp_extension.include_paths():
+        cmd += ["-isystem", d]
+    cmd += ["-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on marshal.cpp:\n%s%s" % (r.stdout, r.stderr))
+    return obj
+
+
+def _link_marshal(obj, verbose):
+    from torch.utils import cpp_extension
+    tmp = MARSHAL + ".tmp%d" % os.getpid()
+    cmd = ["g++", "-shared", "-o", tmp, obj, "-L" + PKG, "-l:liblsgd.so", "-Wl,-rpath,$ORIGIN"]
+    cmd += ["-L" + d for d in cpp_extension.library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), file=sys.stderr)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, MARSHAL)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
-    jobs = min(len(SOURCES), max(1, min(16, os.cpu_count() or 1)))
+    jobs = min(len(SOURCES) + 1, max(1, min(16, os.cpu_count() or 1)))
     with ThreadPoolExecutor(jobs) as ex:
+        marshal = ex.submit(_compile_marshal, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
     tmp = LIB + ".tmp%d" % os.getpid()
     cmd = [HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", "-Wl,--no-undefined", "-o", tmp] + objs
@@ -79,6 +116,7 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd), file=sys.stderr)
     subprocess.run(cmd, check=True)
     os.replace(tmp, LIB)
+    _link_marshal(marshal.result(), verbose)
     return LIB
 
 

@@ -115,6 +115,35 @@ lsgd_status check_overlap(std::vector<Range>& ranges) {
     return LSGD_OK;
 }
 
+bool any_written_overlap(const std::vector<Range>& sorted) {
+    uintptr_t any = 0, written = 0;
+    for (const Range& r : sorted) {
+        if (r.begin < (r.written ? any : written)) return true;
+        any = std::max(any, r.end);
+        if (r.written) written = std::max(written, r.end);
+    }
+    return false;
+}
+
+SortedRanges::SortedRanges(const std::vector<Range>& sorted) {
+    begin_.reserve(sorted.size());
+    max_end_.reserve(sorted.size());
+    max_written_end_.reserve(sorted.size());
+    uintptr_t any = 0, written = 0;
+    for (const Range& r : sorted) {
+        any = std::max(any, r.end);
+        if (r.written) written = std::max(written, r.end);
+        begin_.push_back(r.begin);
+        max_end_.push_back(any);
+        max_written_end_.push_back(written);
+    }
+}
+
+bool SortedRanges::reaches(const std::vector<uintptr_t>& max_end, uintptr_t b, uintptr_t e) const {
+    const size_t before = std::lower_bound(begin_.begin(), begin_.end(), e) - begin_.begin();   // ranges that begin below e
+    return before > 0 && max_end[before - 1] > b;
+}
+
 int device_cus() {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;

@@ -241,6 +241,7 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     StepArgs a;
     memset(&a, 0, sizeof a);
     std::vector<Range> ranges;
+    ranges.reserve(order.size() + std::max<int32_t>(0, std::min(n_replicas, kMaxReplicas)) + 4);
     if ((st = check_grads(grads, gdt, order, n, live, a.grads, ranges)) != LSGD_OK) return st;
     if ((st = check_replicas(replicas, n_replicas, rdt, n, live, ranges)) != LSGD_OK) return st;
     if (!live) return LSGD_OK;

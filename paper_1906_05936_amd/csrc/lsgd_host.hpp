@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -43,6 +44,26 @@ struct Range {
 // LSGD_ERR_ALIAS if a written range overlaps any other range (empty ranges
 // never overlap). Sort-and-sweep, O(k log k).
 lsgd_status check_overlap(std::vector<Range>& ranges);
+
+// Whether a written range overlaps another, for ranges check_overlap has sorted.
+bool any_written_overlap(const std::vector<Range>& sorted);
+
+// Ranges sorted by check_overlap (the plan's, checked at creation), so that a
+// step checks the one or two more buffers it is given against all of them
+// without sorting them again: the 5474 ranges of a ResNet-50 plan with 16
+// workers and replicas took longer to copy and sort than the step to launch.
+class SortedRanges {
+public:
+    SortedRanges() = default;
+    explicit SortedRanges(const std::vector<Range>& sorted);
+    // Whether [b, e) overlaps any range (any written one).
+    bool overlap(uintptr_t b, uintptr_t e) const { return e > b && reaches(max_end_, b, e); }
+    bool overlap_written(uintptr_t b, uintptr_t e) const { return e > b && reaches(max_written_end_, b, e); }
+
+private:
+    bool reaches(const std::vector<uintptr_t>& max_end, uintptr_t b, uintptr_t e) const;
+    std::vector<uintptr_t> begin_, max_end_, max_written_end_;   // prefix maxima over the ranges before
+};
 
 // Default launch shape of the planless kernels: automatic XCD chunk (each XCD
 // walks kAutoChunkBytes of every buffer per turn), one-shot grids, one pass per

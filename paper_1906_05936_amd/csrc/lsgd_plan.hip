@@ -41,6 +41,8 @@ struct lsgd_plan {
     int32_t* d_tensor_chunks;
     uint8_t* d_lars_exclude;   // [n_tensors], zero until lsgd_plan_set_lars_exclude
     std::vector<lsgd::Range>* ranges;
+    lsgd::SortedRanges* sorted;
+    bool grads_apart;     // no gradient buffer overlaps any other buffer (the gradient broadcast needs that)
 };
 
 namespace lsgd {
@@ -200,6 +202,7 @@ void free_plan(lsgd_plan* p) {
     if (p->d_tensor_chunks) (void)hipFree(p->d_tensor_chunks);
     if (p->d_lars_exclude) (void)hipFree(p->d_lars_exclude);
     delete p->ranges;
+    delete p->sorted;
     delete p;
 }
 
@@ -230,20 +233,17 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     const uintptr_t lb = reinterpret_cast<uintptr_t>(lr_device);
     const uintptr_t le = lb + sizeof(float);
     lsgd_status st = LSGD_OK;
-    if (library_workspace) {
-        auto overlaps = [](uintptr_t b0, uintptr_t e0, uintptr_t b1, uintptr_t e1) { return b0 < e1 && b1 < e0; };
-        if (trust_out && lr_device && overlaps(tb, te, lb, le))
-            return fail(LSGD_ERR_ALIAS, "written buffer trust_out overlaps lr_device");
-        for (const Range& r : *plan->ranges) {
-            if (trust_out && overlaps(tb, te, r.begin, r.end))
-                return fail(LSGD_ERR_ALIAS, "written buffer trust_out overlaps %s", r.what);
-            if (lr_device && r.written && overlaps(lb, le, r.begin, r.end))
-                return fail(LSGD_ERR_ALIAS, "buffer lr_device overlaps written buffer %s", r.what);
-        }
-    } else {
+    auto overlaps = [](uintptr_t b0, uintptr_t e0, uintptr_t b1, uintptr_t e1) { return b0 < e1 && b1 < e0; };
+    if (trust_out && lr_device && overlaps(tb, te, lb, le))
+        return fail(LSGD_ERR_ALIAS, "written buffer trust_out overlaps lr_device");
+    const uintptr_t wb = reinterpret_cast<uintptr_t>(workspace);
+    const uintptr_t we = library_workspace ? wb : wb + l.total;   // the library's own overlaps no caller buffer
+    const SortedRanges& known = *plan->sorted;
+    if (known.overlap(wb, we) || (trust_out && known.overlap(tb, te)) || (lr_device && known.overlap_written(lb, le)) ||
+        (trust_out && overlaps(wb, we, tb, te)) || (lr_device && overlaps(wb, we, lb, le))) {
+        // some pair does overlap: find and name it
         std::vector<Range> ranges(*plan->ranges);
-        const uintptr_t wb = reinterpret_cast<uintptr_t>(workspace);
-        ranges.push_back(Range{wb, wb + l.total, true, "workspace"});
+        ranges.push_back(Range{wb, we, true, "workspace"});
         if (trust_out) ranges.push_back(Range{tb, te, true, "trust_out"});
         if (lr_device) ranges.push_back(Range{lb, le, false, "lr_device"});
         if ((st = check_overlap(ranges)) != LSGD_OK) return st;
@@ -438,6 +438,10 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     p->lars_merge = lars_merge;
     p->gbar_floats = gbar_floats;
     p->ranges = new std::vector<Range>(ranges);
+    p->sorted = new SortedRanges(ranges);
+    for (Range& r : ranges)   // sorted already: with every buffer written, any overlap counts
+        if (strcmp(r.what, "grads") == 0) r.written = true;
+    p->grads_apart = !any_written_overlap(ranges);
     hipError_t e = hipSuccess;
     const size_t chunk_bytes = std::max<size_t>(1, chunks.size()) * sizeof(PlanChunk);
     const size_t table_bytes = table.size() * sizeof(void*);
@@ -486,15 +490,15 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
         return fail(LSGD_ERR_DTYPE, "broadcast_grad needs binary32 gradients");
     if (lr_device && (reinterpret_cast<uintptr_t>(lr_device) & 3u) != 0)
         return fail(LSGD_ERR_ALIGN, "lr_device is not 4-byte aligned");
-    if (bcast || lr_device) {
+    const uintptr_t lb = reinterpret_cast<uintptr_t>(lr_device);
+    const uintptr_t le = lb + sizeof(float);
+    if ((bcast && (!plan->grads_apart || (lr_device && plan->sorted->overlap(lb, le)))) ||
+        (lr_device && plan->sorted->overlap_written(lb, le))) {   // some pair does overlap: find and name it
         std::vector<Range> ranges(*plan->ranges);
         if (bcast)   // the gradient buffers are written too
             for (Range& r : ranges)
                 if (strcmp(r.what, "grads") == 0) r.written = true;
-        if (lr_device) {
-            const uintptr_t lb = reinterpret_cast<uintptr_t>(lr_device);
-            ranges.push_back(Range{lb, lb + sizeof(float), false, "lr_device"});
-        }
+        if (lr_device) ranges.push_back(Range{lb, le, false, "lr_device"});
         lsgd_status st = check_overlap(ranges);
         if (st != LSGD_OK) return st;
     }
