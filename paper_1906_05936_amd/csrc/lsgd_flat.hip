@@ -22,43 +22,50 @@ struct MeanPick {
     int tile;
 };
 
-// Group means: compile-time W for powers of two up to 16, else runtime W.
+// The mean of K inputs: compile-time K of 1 to 8, 12, 16; else none
+// (mean_stream).
 template <typename GT>
-MeanPick pick_group_mean(int W) {
-    constexpr int U = sizeof(GT) == 4 ? 2 : 1;   // W gradients per tile: the unrolled form up to 16
-    switch (W) {
-        case 1: return MeanPick{group_mean_kernel_ct<GT, 1, U>, U};
-        case 2: return MeanPick{group_mean_kernel_ct<GT, 2, U>, U};
-        case 4: return MeanPick{group_mean_kernel_ct<GT, 4, U>, U};
-        case 8: return MeanPick{group_mean_kernel_ct<GT, 8, U>, U};
-        case 16: return MeanPick{group_mean_kernel_ct<GT, 16, U>, U};
+MeanPick pick_mean(int K) {
+    constexpr int U = sizeof(GT) == 4 ? 2 : 1;   // up to 16 inputs: the unrolled form
+    switch (K) {
+        case 1: return MeanPick{mean_kernel_ct<GT, 1, U>, U};
+        case 2: return MeanPick{mean_kernel_ct<GT, 2, U>, U};
+        case 3: return MeanPick{mean_kernel_ct<GT, 3, U>, U};
+        case 4: return MeanPick{mean_kernel_ct<GT, 4, U>, U};
+        case 5: return MeanPick{mean_kernel_ct<GT, 5, U>, U};
+        case 6: return MeanPick{mean_kernel_ct<GT, 6, U>, U};
+        case 7: return MeanPick{mean_kernel_ct<GT, 7, U>, U};
+        case 8: return MeanPick{mean_kernel_ct<GT, 8, U>, U};
+        case 12: return MeanPick{mean_kernel_ct<GT, 12, U>, U};
+        case 16: return MeanPick{mean_kernel_ct<GT, 16, U>, U};
     }
-    switch (seg_levels(W)) {
-        case 3: return MeanPick{group_mean_kernel<GT, 3>, 1};
-        case 4: return MeanPick{group_mean_kernel<GT, 4>, 1};
-        case 5: return MeanPick{group_mean_kernel<GT, 5>, 1};
-    }
-    return MeanPick{group_mean_kernel<GT, 8>, 1};
+    return MeanPick{nullptr, 1};
 }
 
-// Global mean: compile-time G for powers of two up to 128, else runtime G.
-MeanPick pick_global_mean(int G) {
-    switch (G) {
-        case 1: return MeanPick{global_mean_kernel_ct<1, 2>, 2};
-        case 2: return MeanPick{global_mean_kernel_ct<2, 2>, 2};
-        case 4: return MeanPick{global_mean_kernel_ct<4, 2>, 2};
-        case 8: return MeanPick{global_mean_kernel_ct<8, 2>, 2};
-        case 16: return MeanPick{global_mean_kernel_ct<16, 2>, 2};
-        case 32: return MeanPick{global_mean_kernel_ct<32, 2>, 2};
-        case 64: return MeanPick{global_mean_kernel_ct<64, 2>, 2};
-        case 128: return MeanPick{global_mean_kernel_ct<128, 2>, 2};
+// Means of `runs` runs of K consecutive inputs of a.in to a.out.
+lsgd_status launch_means(MeanArgs& a, int K, int runs, bool bf16, void* stream, const char* what) {
+    const MeanPick k = bf16 ? pick_mean<uint16_t>(K) : pick_mean<float>(K);
+    const int64_t vec = bf16 ? Unit<uint16_t>::VEC : Unit<float>::VEC;
+    a.W = K;
+    LaunchShape ls = k.kernel ? launch_shape((a.n + vec - 1) / vec, k.tile)
+                              : launch_shape(stream_units(a.n, bf16), stream_tile(bf16));
+    if (static_cast<int64_t>(ls.blocks) * runs > kMaxGridBlocks) {   // the kernels stride over the rest
+        ls.blocks = static_cast<unsigned>(kMaxGridBlocks / runs);
+        ls.xcd_chunk = 0;
     }
-    switch (seg_levels(G)) {
-        case 3: return MeanPick{global_mean_kernel<3>, 1};
-        case 4: return MeanPick{global_mean_kernel<4>, 1};
-        case 5: return MeanPick{global_mean_kernel<5>, 1};
+    a.xcd_chunk = ls.xcd_chunk;
+    a.upl = ls.upl;
+    const dim3 blocks(ls.blocks, static_cast<unsigned>(runs));
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    if (k.kernel) {
+        hipLaunchKernelGGL(k.kernel, blocks, dim3(kBlock), 0, s, a);
+    } else {
+        const int32_t start[2] = {0, K};
+        Program pr;
+        build_program(1, start, false, pr);
+        launch_mean_stream(a, pr, bf16, blocks, s);
     }
-    return MeanPick{global_mean_kernel<8>, 1};
+    return check_launch(what);
 }
 
 size_t dtype_size(lsgd_dtype d) { return d == LSGD_BF16 ? 2 : 4; }
@@ -345,9 +352,7 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     for (int64_t i = 0; i < K; ++i) {
         const int64_t lo = range_edge(n, K, i), hi = range_edge(n, K, i + 1);
         StepArgs ra = K == 1 ? a : offset_args(a, lo, hi, dtype_size(gdt), dtype_size(rdt), n_replicas);
-        // the stream kernels take the ragged end as a tile of its own
-        const int64_t units = any_layout && ra.n % vec != 0 ? (ra.n / vec + kBlock * k.tile - 1) / (kBlock * k.tile) * (kBlock * k.tile) + 1
-                                                            : (ra.n + vec - 1) / vec;
+        const int64_t units = any_layout ? stream_units(ra.n, gdt == LSGD_BF16) : (ra.n + vec - 1) / vec;
         const LaunchShape ls = launch_shape(units, k.tile);
         ra.xcd_chunk = ls.xcd_chunk;
         ra.upl = ls.upl;
@@ -393,16 +398,7 @@ LSGD_API lsgd_status lsgd_group_mean(const void* const* grads, lsgd_dtype gdt, i
     }
     if ((st = check_overlap(ranges)) != LSGD_OK) return st;
     a.n = n;
-    a.n_workers = n_workers;
-    a.n_groups = n_groups;
-    a.W = n_workers / n_groups;
-    const int64_t vec = gdt == LSGD_BF16 ? Unit<uint16_t>::VEC : Unit<float>::VEC;
-    const MeanPick k = gdt == LSGD_BF16 ? pick_group_mean<uint16_t>(a.W) : pick_group_mean<float>(a.W);
-    const LaunchShape ls = launch_shape((n + vec - 1) / vec, k.tile);
-    a.xcd_chunk = ls.xcd_chunk;
-    a.upl = ls.upl;
-    hipLaunchKernelGGL(k.kernel, dim3(ls.blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream), a);
-    return check_launch("lsgd_group_mean");
+    return launch_means(a, n_workers / n_groups, n_groups, gdt == LSGD_BF16, stream, "lsgd_group_mean");
 }
 
 LSGD_API lsgd_status lsgd_global_mean(const float* const* group_means, int32_t n_groups, int64_t n,
@@ -428,13 +424,7 @@ LSGD_API lsgd_status lsgd_global_mean(const float* const* group_means, int32_t n
     if (st != LSGD_OK) return st;
     a.out[0] = grad_mean;
     a.n = n;
-    a.n_groups = n_groups;
-    const MeanPick k = pick_global_mean(n_groups);
-    const LaunchShape ls = launch_shape((n + 3) / 4, k.tile);
-    a.xcd_chunk = ls.xcd_chunk;
-    a.upl = ls.upl;
-    hipLaunchKernelGGL(k.kernel, dim3(ls.blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream), a);
-    return check_launch("lsgd_global_mean");
+    return launch_means(a, n_groups, 1, false, stream, "lsgd_global_mean");
 }
 
 LSGD_API lsgd_status lsgd_sgd_step(float* params, float* momentum, const float* grad_mean, int64_t n,

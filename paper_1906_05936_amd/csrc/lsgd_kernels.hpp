@@ -374,97 +374,6 @@ __host__ __device__ constexpr int largest_divisor_le(int k, int b) {
     return b <= 1 ? 1 : (k % b == 0 ? b : largest_divisor_le(k, b - 1));
 }
 
-// Levels a PwAcc needs for `cnt` pushes (uniform runtime value).
-__device__ __forceinline__ int acc_levels(int cnt) { return 32 - __builtin_clz(static_cast<unsigned>(cnt)); }
-
-// Member gradient loads a lane holds in one register batch of the segmented
-// sum: 8 for binary32 gradients, 4 for bfloat16. Halving the bfloat16 batch
-// cut its kernels from 186-256 VGPRs to 154-234 (3 waves per SIMD instead of
-// 2 for counts up to 7) and their code by half; measured on the ResNet-50
-// size, same process: 2x3 +9% (R = N) / +14% (R = 0), 6x4 +6% / +10%, 3x32
-// +19% / +85%, 12x1 and 5x16 within 1%. The instruction cache was not the
-// limit (0.01% misses with either batch, as for the compile-time kernels).
-// For binary32 the same change was mixed (12x1 +8%, 2x3 +1%, 12x8 -1% / -2%,
-// 3x32 -2%), so it keeps 8.
-template <typename GT>
-constexpr int seg_batch() { return sizeof(GT) == 2 ? 4 : 8; }
-
-// Pairwise sums of consecutive runs of the N member-ordered gradients of one
-// lane tile (U units, stream-major), for group layouts known only at run time:
-// group j holds members [gs(j), gs(j+1)), j < G, and done(j, sum) receives PW
-// over them for every element of the tile. Loads run ahead of the additions
-// in two alternating register batches of seg_batch loads (seg_batch / U
-// members) that ignore group boundaries, so a lane keeps between one and two
-// batches of 128-bit loads in flight whatever the group sizes. Each group is
-// folded through a binary-counter accumulator (LV levels: sizes below 2^LV).
-// N, G and gs are uniform, so every branch here is uniform.
-template <typename GT, int LV, int U, bool TAIL, typename Ptr, typename Start, typename Done>
-__device__ __forceinline__ void pw_segments(int N, int G, const Ptr& ptr, const Start& gs, const int64_t (&e0)[U],
-                                            int cnt, const Done& done) {
-    constexpr int VEC = Unit<GT>::VEC;
-    constexpr int T = U * VEC;
-    constexpr int B = seg_batch<GT>() / U;
-    static_assert(B >= 1 && B * U == seg_batch<GT>(), "the batch holds whole members");
-    u32x4 xa[B][U], xb[B][U];
-    PwAcc<T, LV> acc;
-    int j = 0;
-    int gend = gs(1);
-    int lv = acc_levels(gend - gs(0));
-    auto fetch = [&](int k0, u32x4 (&x)[B][U]) {
-#pragma unroll
-        for (int q = 0; q < B; ++q) {
-            if (k0 + q < N) {
-                const void* g = ptr(k0 + q);
-#pragma unroll
-                for (int u = 0; u < U; ++u) x[q][u] = load_raw<GT, TAIL>(g, e0[u], cnt);
-            }
-        }
-    };
-    auto consume = [&](int k0, const u32x4 (&x)[B][U]) {
-#pragma unroll
-        for (int q = 0; q < B; ++q) {
-            if (k0 + q < N) {
-                float v[T];
-#pragma unroll
-                for (int u = 0; u < U; ++u) widen<GT>(x[q][u], slice<VEC, T>(v, u));
-                acc.push(v, lv);
-                if (k0 + q + 1 == gend) {
-                    float sum[T];
-                    acc.result(sum, lv);
-                    acc.count = 0;
-                    done(j, sum);
-                    if (++j < G) {
-                        const int gbeg = gend;
-                        gend = gs(j + 1);
-                        lv = acc_levels(gend - gbeg);
-                    }
-                }
-            }
-        }
-    };
-    fetch(0, xa);
-#pragma unroll 1
-    for (int k0 = 0; k0 < N; k0 += 2 * B) {
-        if (k0 + B < N) fetch(k0 + B, xb);
-        consume(k0, xa);
-        if (k0 + 2 * B < N) fetch(k0 + 2 * B, xa);
-        if (k0 + B < N) consume(k0 + B, xb);
-    }
-}
-
-// Accumulator levels for runtime counts up to `max_count` (host side): the
-// segmented kernels are built for 3, 4, 5 and 8 levels (counts up to 7, 15,
-// 31 and 255). Every level holds a tile of partial sums in registers, so the
-// smallest sufficient form runs more waves per SIMD (binary32 step kernel:
-// 200 VGPRs at 5 levels, 168 at 3). Measured on the ResNet-50 size against
-// 5 levels for everything up to 31, same process: unequal groups 2, 3, 5, 6
-// +6.9% (R = 16), 6x4 +6.9%, 2x3 +5.8%, 4x6 +3.3% with 3 levels; 12x8 +2.1%
-// and 4x10 +1.2% with 4; without replicas +3.5% to +20%; one loss, 3x5 with
-// its 15 replicas written by the step kernel, -2.5%.
-__host__ __device__ constexpr int seg_levels(int max_count) {
-    return max_count <= 7 ? 3 : max_count <= 15 ? 4 : max_count <= 31 ? 5 : 8;
-}
-
 // ------------------------------------------------------------- the update
 
 struct Hyper {
@@ -517,7 +426,7 @@ __device__ __forceinline__ Hyper resolve_hyper(const Hyper& h, const float* lr_p
 // Group-mean outputs of lsgd_group_mean / inputs of lsgd_global_mean.
 struct MeanArgs {
     int64_t n;
-    int32_t n_workers, n_groups, W;
+    int32_t W;   // inputs per mean: mean j is over in[j*W .. j*W + W)
     uint32_t xcd_chunk, upl;
     const void* in[kMaxWorkers];
     float* out[kMaxWorkers];
@@ -876,120 +785,40 @@ constexpr auto flat_step_kernel() {
     else return step_flat_ct<GT, W, G, U, CACHED>;
 }
 
-// lsgd_group_mean, compile-time W (a power of two): every group's mean of its
-// W members for one tile of U units, stored stream-major.
-template <typename GT, int W, int U, bool TAIL>
-__device__ __forceinline__ void group_mean_tile(const MeanArgs& a, const int64_t (&e0)[U], int cnt) {
+// The mean of a run of K of the call's inputs (PW, / K), compile-time K:
+// lsgd_group_mean takes group blockIdx.y's members, lsgd_global_mean the group
+// means. A workgroup reads one group's K + 1 streams; walking all groups per
+// lane kept K loads in flight at a time and switched streams for each.
+template <typename GT, int K, int U, bool TAIL>
+__device__ __forceinline__ void mean_tile(const MeanArgs& a, const int64_t (&e0)[U], int cnt) {
     constexpr int VEC = Unit<GT>::VEC;
     constexpr int T = U * VEC;
-    for (int j = 0; j < a.n_groups; ++j) {
-        float sum[T];
-        pw_leaves<W, T, T>([&](int k, float (&x)[T]) {
-            const void* g = a.in[j * W + k];
+    const int j = static_cast<int>(blockIdx.y);
+    float sum[T];
+    pw_leaves<K, T, T>([&](int k, float (&x)[T]) {
+        const void* g = a.in[j * K + k];
 #pragma unroll
-            for (int q = 0; q < U; ++q) load_grad<GT, TAIL>(g, e0[q], cnt, slice<VEC, T>(x, q));
-        }, sum);
+        for (int q = 0; q < U; ++q) load_grad<GT, TAIL>(g, e0[q], cnt, slice<VEC, T>(x, q));
+    }, sum);
 #pragma unroll
-        for (int v = 0; v < T; ++v) sum[v] = sum[v] / static_cast<float>(W);
+    for (int v = 0; v < T; ++v) sum[v] = sum[v] / static_cast<float>(K);
 #pragma unroll
-        for (int q = 0; q < U; ++q) store_f32<VEC, TAIL>(a.out[j], e0[q], cnt, slice<VEC, T>(sum, q));
-    }
+    for (int q = 0; q < U; ++q) store_f32<VEC, TAIL>(a.out[j], e0[q], cnt, slice<VEC, T>(sum, q));
 }
 
-template <typename GT, int W, int U>
-__global__ __launch_bounds__(kBlock) void group_mean_kernel_ct(MeanArgs a) {
+template <typename GT, int K, int U>
+__global__ __launch_bounds__(kBlock) void mean_kernel_ct(MeanArgs a) {
     constexpr int VEC = Unit<GT>::VEC;
     const int64_t full = a.n / VEC;
     const int rem = static_cast<int>(a.n - full * VEC);
     for_tiles<U, VEC>(
         full, full + (rem != 0), a.xcd_chunk, a.upl,
-        [&](const int64_t (&e0)[U]) { group_mean_tile<GT, W, U, false>(a, e0, VEC); },
+        [&](const int64_t (&e0)[U]) { mean_tile<GT, K, U, false>(a, e0, VEC); },
         [&](int64_t u) {
             const int64_t e[1] = {u * VEC};
-            if (u < full) group_mean_tile<GT, W, 1, false>(a, e, VEC);
-            else group_mean_tile<GT, W, 1, true>(a, e, rem);
+            if (u < full) mean_tile<GT, K, 1, false>(a, e, VEC);
+            else mean_tile<GT, K, 1, true>(a, e, rem);
         });
-}
-
-// lsgd_group_mean, runtime W (any equal-size grouping), one unit.
-template <typename GT, int LV, bool TAIL>
-__device__ __forceinline__ void group_mean_unit(const MeanArgs& a, int64_t e0, int cnt) {
-    constexpr int VEC = Unit<GT>::VEC;
-    const int W = a.W;
-    const float wf = static_cast<float>(W);
-    const int64_t e[1] = {e0};
-    pw_segments<GT, LV, 1, TAIL>(a.n_workers, a.n_groups, [&](int k) { return a.in[k]; },
-                                 [&](int j) { return j * W; }, e, cnt, [&](int j, float (&sum)[VEC]) {
-#pragma unroll
-                                  for (int v = 0; v < VEC; ++v) sum[v] = sum[v] / wf;
-                                  store_f32<VEC, TAIL>(a.out[j], e0, cnt, sum);
-                              });
-}
-
-template <typename GT, int LV>
-__global__ __launch_bounds__(kBlock) void group_mean_kernel(MeanArgs a) {
-    constexpr int VEC = Unit<GT>::VEC;
-    const int64_t full = a.n / VEC;
-    const int rem = static_cast<int>(a.n - full * VEC);
-    for_units(full + (rem != 0), a.xcd_chunk, a.upl, [&](int64_t u) {
-        if (u < full) group_mean_unit<GT, LV, false>(a, u * VEC, VEC);
-        else group_mean_unit<GT, LV, true>(a, u * VEC, rem);
-    });
-}
-
-// lsgd_global_mean, compile-time G (a power of two): PW over the G group
-// means, / G, for one tile of U 4-element units.
-template <int G, int U, bool TAIL>
-__device__ __forceinline__ void global_mean_tile(const MeanArgs& a, const int64_t (&e0)[U], int cnt) {
-    constexpr int T = U * 4;
-    float s[T];
-    pw_leaves<G, T, T>([&](int j, float (&x)[T]) {
-        const float* in = static_cast<const float*>(a.in[j]);
-#pragma unroll
-        for (int q = 0; q < U; ++q) load_f32<4, TAIL>(in, e0[q], cnt, slice<4, T>(x, q));
-    }, s);
-#pragma unroll
-    for (int v = 0; v < T; ++v) s[v] = s[v] / static_cast<float>(G);
-#pragma unroll
-    for (int q = 0; q < U; ++q) store_f32<4, TAIL>(a.out[0], e0[q], cnt, slice<4, T>(s, q));
-}
-
-template <int G, int U>
-__global__ __launch_bounds__(kBlock) void global_mean_kernel_ct(MeanArgs a) {
-    const int64_t full = a.n / 4;
-    const int rem = static_cast<int>(a.n - full * 4);
-    for_tiles<U, 4>(
-        full, full + (rem != 0), a.xcd_chunk, a.upl,
-        [&](const int64_t (&e0)[U]) { global_mean_tile<G, U, false>(a, e0, 4); },
-        [&](int64_t u) {
-            const int64_t e[1] = {u * 4};
-            if (u < full) global_mean_tile<G, 1, false>(a, e, 4);
-            else global_mean_tile<G, 1, true>(a, e, rem);
-        });
-}
-
-// lsgd_global_mean, runtime G, one unit: the G means form one run.
-template <int LV, bool TAIL>
-__device__ __forceinline__ void global_mean_unit(const MeanArgs& a, int64_t e0, int cnt) {
-    const int G = a.n_groups;
-    const float gf = static_cast<float>(G);
-    const int64_t e[1] = {e0};
-    pw_segments<float, LV, 1, TAIL>(G, 1, [&](int j) { return a.in[j]; }, [&](int j) { return j * G; },
-                                    e, cnt, [&](int, float (&sum)[4]) {
-#pragma unroll
-                                     for (int v = 0; v < 4; ++v) sum[v] = sum[v] / gf;
-                                     store_f32<4, TAIL>(a.out[0], e0, cnt, sum);
-                                 });
-}
-
-template <int LV>
-__global__ __launch_bounds__(kBlock) void global_mean_kernel(MeanArgs a) {
-    const int64_t full = a.n / 4;
-    const int rem = static_cast<int>(a.n - full * 4);
-    for_units(full + (rem != 0), a.xcd_chunk, a.upl, [&](int64_t u) {
-        if (u < full) global_mean_unit<LV, false>(a, u * 4, 4);
-        else global_mean_unit<LV, true>(a, u * 4, rem);
-    });
 }
 
 // lsgd_sgd_step: update and copy-out from a precomputed mean gradient, one

@@ -29,6 +29,19 @@ void launch_plan_stream(const PlanArgs& a, const Program& pr, bool bf16, bool ca
     hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr), s, pa);
 }
 
+void launch_mean_stream(const MeanArgs& a, const Program& pr, bool bf16, dim3 blocks, hipStream_t s) {
+    MeanProgArgs ma;
+    ma.a = a;
+    ma.pr = pr;
+    const auto k = bf16 ? mean_stream<uint16_t> : mean_stream<float>;
+    hipLaunchKernelGGL(k, blocks, dim3(kBlock), stack_bytes(pr), s, ma);
+}
+
+int64_t stream_units(int64_t n, bool bf16) {
+    const int64_t vec = bf16 ? Unit<uint16_t>::VEC : Unit<float>::VEC, per_tile = kBlock * stream_tile(bf16);
+    return n % vec == 0 ? n / vec : (n / vec + per_tile - 1) / per_tile * per_tile + 1;
+}
+
 void launch_lars_norms_stream(const LarsArgs& a, const Program& pr, bool bf16, unsigned blocks, hipStream_t s) {
     LarsProgArgs la;
     la.la = a;

@@ -165,6 +165,46 @@ __device__ __forceinline__ void stream_mean(const Src& s, const Program& pr, con
     }
 }
 
+// The mean of a run of inputs whose count has no compile-time kernel: `pr` is
+// the program of one group of that many members, `first` the run's first input.
+struct MeanProgArgs {
+    MeanArgs a;
+    Program pr;
+};
+
+struct MeanSrc {
+    const MeanArgs& a;
+    int first;
+    __device__ const void* grad(int k) const { return a.in[first + k]; }
+};
+
+template <typename GT>
+__global__ __launch_bounds__(kBlock) void mean_stream(MeanProgArgs ma) {
+    extern __shared__ f32x4 stream_lds[];
+    constexpr int U = StreamTile<GT>::U;
+    constexpr int VEC = Unit<GT>::VEC;
+    constexpr int T = U * VEC;
+    const MeanArgs& a = ma.a;
+    const MeanSrc s{a, static_cast<int>(blockIdx.y) * a.W};
+    float* out = a.out[blockIdx.y];
+    const int64_t tiles = tile_count(a.n, VEC, U);
+    for (int64_t base = static_cast<int64_t>(logical_block(blockIdx.x, a.xcd_chunk)) * a.upl; base < tiles;
+         base += static_cast<int64_t>(gridDim.x) * a.upl) {
+        for (uint32_t i = 0; i < a.upl && base + i < tiles; ++i) {
+            const Tile<U> t = tile_at<U, VEC>(0, a.n, base + i);
+            float g[T];
+            stream_mean<GT, U, sizeof(GT) == 4>(s, ma.pr, t, stream_lds, g);
+            if (t.tail) {
+                if (t.own[0]) gstore_ptr<float>(out)[t.e[0]] = g[0];
+                continue;
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (t.own[q]) store_f32<VEC, false>(out, t.e[q], VEC, slice<VEC, T>(g, q));
+        }
+    }
+}
+
 // One lane tile of the fused step.
 template <typename GT, int U, typename Src>
 __device__ __forceinline__ void stream_step_tile(const Src& s, const Program& pr, const Tile<U>& t, f32x4* stk) {

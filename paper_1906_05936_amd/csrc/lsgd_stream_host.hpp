@@ -16,6 +16,10 @@ constexpr int stream_tile(bool bf16) { return bf16 ? 2 : 4; }
 // `cached`: parameters and momentum through the caches.
 void launch_flat_stream(const StepArgs& a, const Program& pr, bool bf16, bool cached, unsigned blocks, hipStream_t s);
 void launch_plan_stream(const PlanArgs& a, const Program& pr, bool bf16, bool cached, unsigned blocks, hipStream_t s);
+void launch_mean_stream(const MeanArgs& a, const Program& pr, bool bf16, dim3 blocks, hipStream_t s);
+// Workgroup tiles of a vector of n elements, in units (launch_shape's count):
+// the ragged end is a tile of its own.
+int64_t stream_units(int64_t n, bool bf16);
 void launch_lars_norms_stream(const LarsArgs& a, const Program& pr, bool bf16, unsigned blocks, hipStream_t s);
 
 }  // namespace lsgd
