@@ -783,12 +783,10 @@ def separate_copy_out(wl, R, mode="auto", bcast=False):
     if mode == "separate":
         return True
     cached = wl.n_workers <= 16 and 8 * wl.n <= (288 << 20)   # parameters and momentum through the caches
-    G, W = wl.groups, wl.workers_per_group
-    if W == 1 and G & (G - 1) and not wl.group_sizes:
-        G, W = 1, wl.n_workers                                  # run as one group of all workers
-    pow2_grouping = (not kernel_match(wl).endswith("_stream") and not wl.group_sizes
-                     and W & (W - 1) == 0 and G & (G - 1) == 0)
-    crossing = (64 if pow2_grouping else 48) if cached else 32
+    stream = kernel_match(wl).endswith("_stream")
+    crossing = 32 if not cached or 8 * wl.n > (128 << 20) else 48 if stream else 40
+    if kernel_match(wl).endswith("_split") and wl.n * copy_bytes <= (64 << 20):
+        return False
     return copy_bytes >= crossing or wl.n_workers * wl.grad_bytes >= 256
 
 
@@ -798,6 +796,8 @@ def step_replicas(wl, R):
     16 bytes per element where parameters and momentum go through the caches."""
     rb = 2 if wl.replica_dtype == "bf16" else 4
     cached = wl.n_workers <= 16 and 8 * wl.n <= (288 << 20)
+    if rb == 2 and kernel_match(wl).endswith("_stream"):
+        return 0
     return min(R, 16 // rb) if cached else 0
 
 

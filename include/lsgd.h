@@ -139,11 +139,11 @@ LSGD_API lsgd_status lsgd_get_launch_shape(int32_t* xcd_chunk, int32_t* blocks_p
  * mostly from cache) and writes the replicas one window of the vector at a
  * time. Results are identical either way. LSGD_COPY_OUT_AUTO (the default)
  * takes the separate pass where it measured faster: for the fused steps when
- * the replica bytes R*s_r per element are at least 32 (for at most 16
- * workers with parameters and momentum within 288 MB, whose step kernels
- * access them through the caches: 64 for power-of-two groups in a
- * power-of-two count, 48 for every other group layout) or the gradient bytes
- * N*s_g at least 256;
+ * the replica bytes R*s_r per element are at least 32 (for at most 16 workers
+ * with parameters and momentum within 128 MB: 40, or 48 for a layout without a
+ * compile-time kernel; with bfloat16 gradients and binary32 replicas 24, or 16
+ * up to 288 MB) or the gradient bytes N*s_g at least 256; short vectors and
+ * small plans write up to 64 MB of copies in the step kernel;
  * for lsgd_sgd_step and the LARS update when R*s_r >= 16 (parameters and
  * momentum within 288 MB; beyond, binary32 replicas and R >= 4).
  * Process-wide, for launches after the call returns. Errors: LSGD_ERR_SIZE
@@ -159,7 +159,8 @@ LSGD_API int32_t lsgd_get_copy_out_mode(void);
  * replicas itself (fewer if the step has fewer) and the copy-out pass writes
  * the rest. -1 (the default) is the automatic choice: 16 bytes of replicas per
  * element (4 binary32 or 8 bfloat16 replicas) for steps with at most 16
- * workers whose parameters and momentum fit in 288 MB, none otherwise (the
+ * workers whose parameters and momentum fit in 288 MB, none otherwise, nor for
+ * bfloat16 gradients with binary32 replicas or without a compile-time kernel (the
  * step kernel's mostly-read stream mix takes a few write streams at little
  * cost; measured fastest). Results are identical for every value.
  * Process-wide, for launches after the call returns. Errors: LSGD_ERR_SIZE
@@ -226,10 +227,7 @@ LSGD_API lsgd_status lsgd_copy_out(const float* params, int64_t n, void* const* 
  * The step kernel reads every gradient, parameter and momentum element once
  * and writes parameters and momentum once; the group means and the mean
  * gradient stay in registers. The replicas are written either by that kernel
- * or, where lsgd_set_copy_out_mode's rule takes the separate form (the
- * default with up to 16 workers at 64 or more replica bytes per element for
- * power-of-two groups in a power-of-two count, 48 for every other group
- * layout), by a copy-out
+ * or, where lsgd_set_copy_out_mode's rule takes the separate form, by a copy-out
  * pass launched right after it, which reads the new parameters once more
  * (the step kernel then still writes the first lsgd_set_step_replicas
  * replicas). Vectors longer than 2^26 elements are processed range by range

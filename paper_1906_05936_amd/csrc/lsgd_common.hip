@@ -181,31 +181,39 @@ LaunchShape pad_for_xcd_chunk(int64_t blocks, int64_t block_bytes) {
 
 int32_t launch_passes_per_block() { return g_units_per_lane.load(std::memory_order_relaxed); }
 
-// Automatic rule, from same-process measurements of the fused pass against
-// step-then-copy-out (the replica-major pass) at N = 4..128 gradients and
-// R = 1..128 replicas, flat steps and plans, binary32 and bfloat16. With
-// nontemporal parameter and momentum accesses the separate pass won once the
-// replicas take 32 bytes per element or more (R = 16 with 16 gradients:
-// +7-9%; R = 64: +18-20%) or the gradients 256 bytes (128 binary32
-// gradients, R = 2: +6%, R = 128: +20%), and was within 3% either way below
-// that. When parameters and momentum go through the caches
-// (use_cached_state) the fused pass gains more, and the crossing moves to 64
-// bytes: at 32 the fused pass won by 2-4% (4x4 R = 8, 2x2 R = 8, 4x4
-// bfloat16 R = 16), at 64 the separate one by 3-12% (4x4 R = 16, 2x2 R = 16,
-// the ResNet-50 plan), at 256 by 28%. Groupings other than power-of-two
-// groups in a power-of-two count cross earlier there: with the segmented
-// kernels the separate pass won by 5-8% at 56 and 60 replica bytes (2x7,
-// 3x5, 5x3 binary32) and lost by 3-8% at 24 and 36 (2x3, 3x2, 1x9); with
-// their compile-time kernels the fused form lost 4% at 3x5 and 11% at 3x5
-// with bfloat16 gradients (60 bytes) and 13% at 12x1 bfloat16 (48 bytes).
-// Their crossing is 48 bytes (`other_layout`).
-bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, int64_t copy_bytes, int64_t n, bool other_layout) {
+// Parameters and momentum beyond this do not survive in the Infinity Cache
+// from one step to the next, whatever runs in between.
+constexpr int64_t kWarmStateBytes = int64_t{128} << 20;
+
+// Automatic rule, from measurements of the step with all copies in the step
+// kernel against the separate pass (two or three states in turn, so that no
+// step finds the state of the one before; us, fused / separate):
+//  - more than 16 workers (nontemporal parameters and momentum): the separate
+//    pass from 32 bytes of copies per element (8x4 binary32 R = 8 364 / 342,
+//    8x4 bfloat16 R = 16 241 / 234), or where the gradients take 256 bytes;
+//  - bfloat16 gradients with binary32 replicas: from 24 bytes, 16 beyond
+//    kWarmStateBytes (2x5, n = 1.2e7: 16 B 104 / 101, 24 B 126 / 115, 40 B 178
+//    / 144; unequal groups, n = 2.5e7: 16 B 297 / 275; plans of 60 tensors are
+//    even at 16 to 24);
+//  - beyond kWarmStateBytes: from 32 bytes (unequal 2, 3, 5, 6, n = 2.5e7:
+//    binary32 32 B 486 / 472, 48 B 569 / 512, bfloat16 32 B 361 / 341, 1x9
+//    bfloat16 32 B 304 / 280; 4x4 binary32 32 B 485 / 481);
+//  - else from 40 bytes with the compile-time kernels (4x4 binary32, n =
+//    1.2e7: 32 B 208 / 210, 40 B 229 / 224, 56 B 265 / 253; 2x2 48 B 154 / 148;
+//    3x5 44 B 228 / 222; 4x4 bfloat16 48 B 187 / 184), 48 with the stream
+//    kernels (unequal, 40 B 225 / 233, 48 B bfloat16 194 / 193).
+bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, size_t rsz, int64_t copy_bytes, int64_t n, bool stream) {
     if (copy_bytes <= 0) return false;
     const int32_t mode = g_copy_out_mode.load(std::memory_order_relaxed);
     if (mode == LSGD_COPY_OUT_FUSED) return false;
     if (mode == LSGD_COPY_OUT_SEPARATE) return true;
     const int64_t grad_bytes = static_cast<int64_t>(n_workers) * static_cast<int64_t>(gsz);
-    const int64_t crossing = !use_cached_state(n_workers, n) ? 32 : other_layout ? 48 : 64;
+    const bool warm = n <= kWarmStateBytes / 8;
+    const int64_t crossing = !use_cached_state(n_workers, n) ? 32
+                             : gsz == 2 && rsz == 4          ? (warm ? 24 : 16)
+                             : !warm                         ? 32
+                             : stream                        ? 48
+                                                             : 40;
     return copy_bytes >= crossing || grad_bytes >= 256;
 }
 
@@ -221,11 +229,13 @@ bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, int64_t copy_bytes, 
 // momentum accesses) every k > 0 lost (128: k = 2 -1.4%, 4 -2.2%; 64 bfloat16:
 // k = 4 -2%, 16 -3.8%). The rule: 16 bytes of replicas per element in the
 // step kernel where parameters and momentum go through the caches, none
-// otherwise.
-int32_t replicas_in_step(int32_t n_workers, int32_t n_replicas, size_t rsz, int64_t n) {
+// otherwise, nor with bfloat16 gradients where the replicas are binary32 (2x5,
+// R = 8: none 128 us, 4 139) or the kernel is the stream one (1x9, R = 16:
+// none 278 us, 8 286).
+int32_t replicas_in_step(int32_t n_workers, int32_t n_replicas, size_t gsz, size_t rsz, int64_t n, bool stream) {
     const int32_t forced = g_step_replicas.load(std::memory_order_relaxed);
     if (forced >= 0) return std::min(forced, n_replicas);
-    if (!use_cached_state(n_workers, n)) return 0;
+    if (!use_cached_state(n_workers, n) || (gsz == 2 && (rsz == 4 || stream))) return 0;
     return std::min<int32_t>(n_replicas, static_cast<int32_t>(16 / rsz));
 }
 

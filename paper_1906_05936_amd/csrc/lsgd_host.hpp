@@ -90,11 +90,11 @@ LaunchShape launch_shape(int64_t units, int tile = 1);
 int32_t launch_passes_per_block();
 
 // Whether a step with N gradients of gsz bytes, n elements and `copy_bytes`
-// bytes per element of copies (replicas, and the gradient broadcast's copies
-// of the mean gradient to the other members) writes them in copy passes of
-// their own (lsgd_set_copy_out_mode); `other_layout`: the step's grouping is
-// not power-of-two groups in a power-of-two count.
-bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, int64_t copy_bytes, int64_t n, bool other_layout);
+// bytes per element of copies (replicas of rsz bytes, and the gradient
+// broadcast's copies of the mean gradient to the other members) writes them in
+// copy passes of their own (lsgd_set_copy_out_mode); `stream`: the step runs in
+// a stream kernel.
+bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, size_t rsz, int64_t copy_bytes, int64_t n, bool stream);
 // Group counts other than powers of two that have compile-time kernels too
 // (lsgd_np2.hpp).
 inline bool np2_group_count(int G) { return G == 3 || G == 5 || G == 6 || G == 7 || G == 12; }
@@ -112,7 +112,7 @@ inline bool one_group_form(int32_t W, int32_t G, bool literal) {
 // With the separate copy-out: how many of the n_replicas replicas (rsz bytes
 // each) the step kernel still writes itself; the copy-out pass writes the
 // rest (lsgd_set_step_replicas).
-int32_t replicas_in_step(int32_t n_workers, int32_t n_replicas, size_t rsz, int64_t n);
+int32_t replicas_in_step(int32_t n_workers, int32_t n_replicas, size_t gsz, size_t rsz, int64_t n, bool stream);
 // The same for lsgd_sgd_step and the LARS update; `cached`: their parameter
 // and momentum accesses go through the caches.
 bool separate_copy_out_update(int32_t n_replicas, size_t rsz, bool cached);

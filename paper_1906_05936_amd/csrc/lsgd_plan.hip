@@ -515,9 +515,9 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
         const int64_t copy_bytes = static_cast<int64_t>(plan->n_replicas) * rsz + 4 * bcast_copies;
         const bool apart = separate_copy_out_small(
             plan->total_elems, copy_bytes,
-            separate_copy_out_bytes(plan->n_workers, gsz, copy_bytes, plan->total_elems, false));
-        const int32_t k_step = apart ? replicas_in_step(plan->n_workers, plan->n_replicas, rsz, plan->total_elems)
-                                     : plan->n_replicas;
+            separate_copy_out_bytes(plan->n_workers, gsz, rsz, copy_bytes, plan->total_elems, false));
+        const int32_t k_step =
+            apart ? replicas_in_step(plan->n_workers, plan->n_replicas, gsz, rsz, plan->total_elems, false) : plan->n_replicas;
         PlanArgs fa = a;
         LaunchShape fs;
         use_fine_pieces(plan, fa, fs);
@@ -545,15 +545,14 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     // gradient to the other N - 1 members go to copy passes of their own
     // where the rule takes the separate form
     const int32_t bcast_copies = bcast ? plan->n_workers - 1 : 0;
-    const bool split = separate_copy_out_bytes(
-        plan->n_workers, plan->gdt == LSGD_BF16 ? 2 : 4,
-        static_cast<int64_t>(plan->n_replicas) * (plan->rdt == LSGD_BF16 ? 2 : 4) + 4 * bcast_copies,
-        plan->total_elems, !k || (W & (W - 1)) != 0 || (G & (G - 1)) != 0);
+    const int rsz = plan->rdt == LSGD_BF16 ? 2 : 4, gsz = plan->gdt == LSGD_BF16 ? 2 : 4;
+    const bool split = separate_copy_out_bytes(plan->n_workers, gsz, rsz,
+                                               static_cast<int64_t>(plan->n_replicas) * rsz + 4 * bcast_copies,
+                                               plan->total_elems, !k);
     a.bcast_grad = bcast ? (split ? 1 : plan->n_workers) : 0;
     // split: the step kernel writes the first k replicas, the copy-out pass the rest
-    const int32_t k_step = split ? replicas_in_step(plan->n_workers, plan->n_replicas, plan->rdt == LSGD_BF16 ? 2 : 4,
-                                                    plan->total_elems)
-                                 : plan->n_replicas;
+    const int32_t k_step =
+        split ? replicas_in_step(plan->n_workers, plan->n_replicas, gsz, rsz, plan->total_elems, !k) : plan->n_replicas;
     a.n_replicas = k_step;
     const hipStream_t s = static_cast<hipStream_t>(stream);
     if (k) hipLaunchKernelGGL(k, dim3(ls.blocks), dim3(kBlock), 0, s, a);
