@@ -81,7 +81,7 @@ def _compile_marshal(verbose):
     obj = os.path.join(BUILD_DIR, "marshal.o")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + INCLUDE,
-           "-isystem", sysconfig.get_paths()["include"]]
+           "-I" + CSRC, "-isystem", sysconfig.get_paths()["include"]]
     for d in cpp_extension.include_paths():
         cmd += ["-isystem", d]
     cmd += ["-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj]

@@ -12,6 +12,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "lsgd.h"
+#include "marshal_call.h"
 
 namespace {
 
@@ -86,17 +87,9 @@ bool number(PyObject* o, float* out) {
 
 void* stream_of(PyObject* o) { return PyLong_AsVoidPtr(o); }
 
-template <typename Call>
-PyObject* without_gil(const Call& call) {
-    lsgd_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = call();
-    Py_END_ALLOW_THREADS
-    return PyLong_FromLong(st);
-}
-
 // A C++ exception of a tensor accessor (a tensor without storage): the general
-// path meets the same tensor and reports it.
+// path meets the same tensor and reports it. (without_gil lets none of the
+// library's through.)
 template <typename Body>
 PyObject* guarded(const Body& body) {
     try {
