@@ -16,9 +16,10 @@
 
 namespace {
 
-// A plain dense GPU tensor, or null.
+// A plain dense GPU tensor, or null: a torch.Tensor or Parameter itself, as a
+// subclass may answer for its address, size or dtype with __torch_function__.
 const at::Tensor* plain(PyObject* o) {
-    if (!THPVariable_Check(o)) return nullptr;
+    if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor& t = THPVariable_Unpack(o);
     if (!t.defined() || t.layout() != at::kStrided || !t.is_cuda() || t.unsafeGetTensorImpl()->is_python_dispatch() ||
         t.is_conj() || t.is_neg() || !t.is_contiguous())

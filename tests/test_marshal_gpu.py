@@ -48,6 +48,37 @@ FORMS = {
 }
 
 
+class Elsewhere(torch.Tensor):
+    """A tensor subclass whose elements are those of another tensor."""
+
+    @classmethod
+    def __torch_function__(cls, func, types, args=(), kwargs=None):
+        if func is torch.Tensor.data_ptr:
+            return args[0].real_one.data_ptr()
+        return super().__torch_function__(func, types, args, kwargs or {})
+
+
+def test_subclass_answers_for_its_address():
+    """A tensor subclass with __torch_function__ is read through it, whichever
+    argument it is."""
+    for name in ("p", "m", "g", "r"):
+        p, m, g, r = state()
+        want = [x.clone() for x in [p, m] + r]
+        lsgd.step(want[0], want[1], g, GOW, 2, 0.1, 0.9, 1e-4, want[2:])
+        a = dict(p=p, m=m, g=list(g), r=list(r))
+        real = a[name] if name in "pm" else a[name][0]
+        outer = torch.zeros_like(real).as_subclass(Elsewhere)
+        outer.real_one = real
+        if name in "pm":
+            a[name] = outer
+        else:
+            a[name][0] = outer
+        lsgd.step(a["p"], a["m"], a["g"], GOW, 2, 0.1, 0.9, 1e-4, a["r"])
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip([p, m] + r, want)), name
+        assert not outer.as_subclass(torch.Tensor).any()
+
+
 @pytest.mark.parametrize("form", FORMS)
 def test_step_forms_agree(form, monkeypatch):
     got = []
