@@ -112,7 +112,18 @@ def _load():
 
 lib = _load()
 
-from . import _marshal  # noqa: E402  (finds liblsgd.so next to it; torch is loaded above)
+
+def _load_marshal():
+    """The extension _marshal, or None where there is none for this Python or
+    it was built against another torch: every call then takes the general path."""
+    try:
+        from . import _marshal as ext   # finds liblsgd.so next to it; torch is loaded above
+    except ImportError:
+        return None
+    return ext if getattr(ext, "torch_build", None) == "%s %s" % (torch.__version__, torch.version.git_version) else None
+
+
+_marshal = _load_marshal()
 
 _current_device = torch._C._cuda_getDevice
 _raw_stream = torch._C._cuda_getCurrentRawStream
@@ -191,9 +202,9 @@ def _on(index):
 
 def _native_target(t, stream):
     """(device index, raw stream) for a native call on tensor t's device, or
-    None where the call has to take the general path (not a tensor on the
-    current GPU)."""
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    None where the call has to take the general path (no extension, or not a
+    tensor on the current GPU)."""
+    if _marshal is None or not isinstance(t, torch.Tensor) or not t.is_cuda:
         return None
     index = t.get_device()
     if _current_device() != index:

@@ -1,5 +1,5 @@
-"""Builds liblsgd.so (HIP, gfx950) and the binding's extension _marshal.so
-(host code) in-tree next to this file.
+"""Builds liblsgd.so (HIP, gfx950) and the binding's extension _marshal (host
+code) in-tree next to this file.
 
 Every HIP translation unit is compiled with:
   -ffp-contract=off       no a*b+c contraction into fused multiply-add: each
@@ -11,6 +11,7 @@ Every HIP translation unit is compiled with:
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -70,18 +71,25 @@ def _compile(src, verbose):
 
 
 # The binding's CPython extension (csrc/marshal.cpp): host code, against the
-# headers of the installed torch and Python.
-MARSHAL = os.path.join(PKG, "_marshal.so")
+# headers of the installed torch and Python. Its name carries Python's ABI tag,
+# so that another Python does not find it, and it holds torch_build(), which the
+# binding compares: torch's tensor layouts are compiled in.
+MARSHAL = os.path.join(PKG, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def torch_build() -> str:
+    """The torch build that _marshal is compiled against."""
+    import torch
+    return "%s %s" % (torch.__version__, torch.version.git_version)
 
 
 def _compile_marshal(verbose):
-    import sysconfig
     import torch
     from torch.utils import cpp_extension
     obj = os.path.join(BUILD_DIR, "marshal.o")
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + INCLUDE,
-           "-I" + CSRC, "-isystem", sysconfig.get_paths()["include"]]
+           '-DLSGD_TORCH_BUILD="%s"' % torch_build(), "-I" + CSRC, "-isystem", sysconfig.get_paths()["include"]]
     for d in cpp_extension.include_paths():
         cmd += ["-isystem", d]
     cmd += ["-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj]

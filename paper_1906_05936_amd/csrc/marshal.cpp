@@ -231,4 +231,8 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__marshal() { return PyModule_Create(&module_def); }
+PyMODINIT_FUNC PyInit__marshal() {
+    PyObject* m = PyModule_Create(&module_def);
+    if (m && PyModule_AddStringConstant(m, "torch_build", LSGD_TORCH_BUILD) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -34,6 +34,22 @@ class Declined:
         return lambda *a: None
 
 
+def test_extension_is_loaded():
+    """The native path is there where the library was built."""
+    assert _lib._marshal is not None
+
+
+def test_without_the_extension(monkeypatch):
+    p, m, g, r = state()
+    lsgd.step(p, m, g, GOW, 2, 0.1, 0.9, 1e-4, r)
+    want = [p, m] + r
+    monkeypatch.setattr(_lib, "_marshal", None)
+    p, m, g, r = state()
+    lsgd.step(p, m, g, GOW, 2, 0.1, 0.9, 1e-4, r)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip([p, m] + r, want))
+
+
 FORMS = {
     "lists": lambda p, m, g, r: dict(),
     "tuples": lambda p, m, g, r: dict(grads=tuple(g), gow=tuple(GOW), replicas=tuple(r)),
