@@ -278,33 +278,6 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     const int64_t copy_bytes = static_cast<int64_t>(n_replicas) * dtype_size(rdt) + 4 * bcast_copies;
     const char* what = literal ? "lsgd_step_ex" : "lsgd_step";
 
-    // the reduction program of the kernels for any layout
-    Program pr;
-    auto build = [&] {
-        if (!literal) {
-            gstart.resize(n_groups + 1);
-            for (int32_t j = 0; j <= n_groups; ++j) gstart[j] = j * (n_workers / n_groups);
-        }
-        build_program(n_groups, gstart.data(), literal, pr);
-    };
-    if (use_split_flat(n, n_workers, gdt == LSGD_BF16, 1)) {
-        build();
-        if (use_split_flat(n, n_workers, gdt == LSGD_BF16, pr.n_batches)) {
-            const bool apart = separate_copy_out_small(
-                n, copy_bytes,
-                separate_copy_out_bytes(n_workers, dtype_size(gdt), dtype_size(rdt), copy_bytes, n, false));
-            a.bcast_grad = bcast ? (apart ? 1 : n_workers) : 0;
-            a.n_replicas = apart ? replicas_in_step(n_workers, n_replicas, dtype_size(gdt), dtype_size(rdt), n, false)
-                                 : n_replicas;
-            const LaunchShape ls = split_launch_shape(n, dtype_size(gdt));
-            a.xcd_chunk = ls.xcd_chunk;
-            launch_flat_split(a, pr, gdt == LSGD_BF16, ls.blocks, a.n_replicas + a.bcast_grad,
-                              static_cast<hipStream_t>(stream));
-            if ((st = check_launch(what)) != LSGD_OK || !apart) return st;
-            return launch_copies(a, n_replicas, a.n_replicas, bcast_copies, stream);
-        }
-    }
-
     // equal group sizes: the literal reduction then runs in the compile-time
     // kernels too (W = 0 marks unequal groups)
     int32_t W = n_workers / n_groups;
@@ -329,9 +302,35 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
         G = 1;
     }
     if (W > 0) k = pick_ct(W, G);
+    // the reduction program of the kernels for any layout
+    Program pr;
+    auto build = [&] {
+        if (!literal) {
+            gstart.resize(n_groups + 1);
+            for (int32_t j = 0; j <= n_groups; ++j) gstart[j] = j * (n_workers / n_groups);
+        }
+        build_program(n_groups, gstart.data(), literal, pr);
+    };
+    if (use_split_flat(n, n_workers, gdt == LSGD_BF16, k.kernel != nullptr, 1)) {
+        build();
+        if (use_split_flat(n, n_workers, gdt == LSGD_BF16, k.kernel != nullptr, pr.n_batches)) {
+            const bool apart = separate_copy_out_small(
+                n, copy_bytes,
+                separate_copy_out_bytes(n_workers, dtype_size(gdt), dtype_size(rdt), copy_bytes, n, false));
+            a.bcast_grad = bcast ? (apart ? 1 : n_workers) : 0;
+            a.n_replicas = apart ? replicas_in_step(n_workers, n_replicas, dtype_size(gdt), dtype_size(rdt), n, false)
+                                 : n_replicas;
+            const LaunchShape ls = split_launch_shape(n, dtype_size(gdt));
+            a.xcd_chunk = ls.xcd_chunk;
+            launch_flat_split(a, pr, gdt == LSGD_BF16, ls.blocks, a.n_replicas + a.bcast_grad,
+                              static_cast<hipStream_t>(stream));
+            if ((st = check_launch(what)) != LSGD_OK || !apart) return st;
+            return launch_copies(a, n_replicas, a.n_replicas, bcast_copies, stream);
+        }
+    }
+
     a.n_groups = G;
     a.W = W;
-
     const int64_t vec = gdt == LSGD_BF16 ? Unit<uint16_t>::VEC : Unit<float>::VEC;
     const bool any_layout = !k.kernel;
     if (any_layout) {

@@ -11,19 +11,9 @@ namespace {
 // waves share a compute unit.
 constexpr int kSplitMaxBatches = 64;
 
-// Up to these sizes the split kernels were faster than the kernels with one
-// lane tile per workgroup (graph replays of one step without replicas, split
-// / other, us):
-//   flat, n = 3e5: binary32 4x4 5.4 / 5.8, 8x8 16.6 / 42.4, 10x4 10.5 / 26.5,
-//     bfloat16 4x4 4.8 / 4.9, 8x8 11.8 / 13.0, 16x8 25.3 / 20.5;
-//   flat, n = 1e6: binary32 4x4 12.9 / 11.2, 8x8 49.3 / 50.1, 16x8 102 / 122,
-//     10x4 30.5 / 38.5, bfloat16 8x8 31.4 / 25.7, 16x8 73.1 / 46.2;
-//   plan of 30 tensors, n = 3e5: binary32 4x4 5.6 / 8.1; n = 1e6: binary32
-//     4x4 13.8 / 12.7, 8x8 50.8 / 62.2, bfloat16 4x4 9.6 / 14.0, 8x8 31.4 /
-//     51.2; n = 3e6: binary32 8x8 169 / 136, bfloat16 8x8 135 / 109.
-// At n = 1e4 a step took 3.3 to 6.4 us (other kernels 3.2 to 104).
-constexpr int64_t kSplitFlatMax = int64_t{1} << 18;
-constexpr int64_t kSplitFlatMaxManyF32 = int64_t{1} << 20;   // binary32, more than 16 workers
+// Plans of up to these sizes take the split kernels (30 tensors, split / the
+// others, us: n = 3e5 binary32 4x4 5.6 / 8.1; n = 1e6 8x8 50.8 / 62.2, bfloat16
+// 4x4 9.6 / 14.0, 8x8 31.4 / 51.2; n = 3e6 binary32 8x8 169 / 136).
 constexpr int64_t kSplitPlanMax = int64_t{1} << 20;
 constexpr int64_t kSplitPlanMaxFewF32 = int64_t{1} << 19;    // binary32, at most 16 workers
 
@@ -33,8 +23,8 @@ bool split_allowed(int n_batches) { return n_batches <= kSplitMaxBatches && laun
 
 }  // namespace
 
-bool use_split_flat(int64_t n, int32_t n_workers, bool bf16, int n_batches) {
-    return n <= (!bf16 && n_workers > 16 ? kSplitFlatMaxManyF32 : kSplitFlatMax) && split_allowed(n_batches);
+bool use_split_flat(int64_t n, int32_t n_workers, bool bf16, bool compile_time, int n_batches) {
+    return split_serves(n, n_workers, bf16, compile_time) && split_allowed(n_batches);
 }
 
 bool use_split_plan(int64_t n, int32_t n_workers, bool bf16, int n_batches) {

@@ -1,0 +1,67 @@
+"""The dispatch rules of lsgd_rules.hpp (host C++, no GPU) at calls measured on
+both sides of their lines: each row names a call and which kernel was the
+faster one there."""
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1906_05936_amd", "csrc")
+
+MAIN = r"""
+#include <cstdio>
+#include <string>
+#include <iostream>
+#include "lsgd_rules.hpp"
+using namespace lsgd;
+int main() {
+    std::string rule;
+    long long v[8];
+    while (std::cin >> rule) {
+        int k = 0;
+        std::cin >> k;
+        for (int i = 0; i < k; ++i) std::cin >> v[i];
+        bool r = false;
+        if (rule == "split") r = split_serves(v[0], (int)v[1], v[2], v[3]);
+        else return 1;
+        std::printf("%d\n", (int)r);
+    }
+    return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "main.cpp").write_text(MAIN)
+    exe = str(d / "main")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I" + CSRC, str(d / "main.cpp"), "-o", exe], check=True)
+
+    def run(rule, rows):
+        text = "".join("%s %d %s\n" % (rule, len(r), " ".join(str(int(x)) for x in r)) for r in rows)
+        return [x == "1" for x in subprocess.run([exe], input=text, capture_output=True, text=True, check=True).stdout.split()]
+
+    return run
+
+
+F32, BF16 = False, True
+
+# (n, workers, bfloat16, compile-time kernel), split kernel faster?
+SPLIT = [
+    ((65_536, 4, F32, True), False), ((131_072, 4, F32, True), False), ((10_007, 4, F32, True), True),
+    ((1_000, 16, F32, True), False), ((2_003, 16, F32, True), True), ((65_536, 16, F32, True), True),
+    ((262_144, 16, F32, True), True), ((262_145, 16, F32, True), False), ((40_000, 8, F32, True), True),
+    ((3_000, 8, F32, True), False), ((100_003, 1, F32, True), False), ((10_007, 2, F32, True), True),
+    ((65_536, 4, BF16, True), False), ((131_072, 16, BF16, True), False), ((131_069, 16, BF16, True), True),
+    ((100_000, 10, BF16, True), False), ((1_003, 4, BF16, True), True), ((262_144, 128, BF16, True), False),
+    ((185_360, 128, BF16, True), True), ((262_141, 128, BF16, True), True), ((262_144, 64, BF16, True), True),
+    ((262_144, 40, BF16, False), True), ((300_000, 40, BF16, False), False),
+    ((370_727, 64, F32, False), True), ((524_288, 64, F32, False), False), ((1_000_000, 30, F32, False), False),
+    ((1_000_000, 80, F32, False), False), ((200_000, 9, F32, False), True), ((300_000, 9, F32, False), False),
+]
+
+
+def test_split_kernels(ask):
+    got = ask("split", [r for r, _ in SPLIT])
+    assert got == [want for _, want in SPLIT], [r for (r, w), g in zip(SPLIT, got) if w != g]
