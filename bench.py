@@ -783,11 +783,20 @@ def separate_copy_out(wl, R, mode="auto", bcast=False):
     if mode == "separate":
         return True
     cached = wl.n_workers <= 16 and 8 * wl.n <= (288 << 20)   # parameters and momentum through the caches
-    stream = kernel_match(wl).endswith("_stream")
-    crossing = 32 if not cached or 8 * wl.n > (128 << 20) else 48 if stream else 40
     if kernel_match(wl).endswith("_split") and wl.n * copy_bytes <= (64 << 20):
         return False
-    return copy_bytes >= crossing or wl.n_workers * wl.grad_bytes >= 256
+    # copies_apart of lsgd_rules.hpp
+    if wl.n_workers * wl.grad_bytes >= 256 or not cached:
+        return copy_bytes >= 32 or wl.n_workers * wl.grad_bytes >= 256
+    widened = wl.grad_bytes == 2 and rb == 4
+    if 8 * wl.n > (128 << 20):
+        return copy_bytes >= (16 if widened else 32)
+    mb = wl.n * copy_bytes >> 20
+    if widened:
+        return copy_bytes >= 24 and mb >= 32
+    crossing = ((52 if wl.n_workers >= 12 else 64) if bcast else 64 if kernel_match(wl).endswith("_stream")
+                else 56 if wl.n_workers <= 4 else 48)
+    return copy_bytes >= crossing and mb >= 128
 
 
 def step_replicas(wl, R):
@@ -843,10 +852,16 @@ def kernel_match(wl, reduction=None, lars=False):
     ct = not wl.group_sizes and ct_grouping(W, G, f32)
     if (not ct and not wl.group_sizes and W == 1 and G & (G - 1) and reduction != "literal"):
         ct = ct_grouping(G, 1, f32)   # one worker per group: run as one group of all workers
-    if wl.tensor_sizes:   # the library's size rules for its split kernels (lsgd_split.hip)
+    if wl.tensor_sizes:   # the library's size rules for its split kernels (lsgd_split.hip, lsgd_rules.hpp)
         split = wl.n <= (1 << 19 if f32 and few else 1 << 20)
+    elif ct and few:   # split_serves of lsgd_rules.hpp
+        whole = wl.n % (4 if f32 else 8) == 0
+        split = wl.n <= 1 << 18 and (wl.n_workers >= (8 if whole else 2) and wl.n > (1024 if wl.n_workers > 8 else 4096)
+                                     if f32 else not whole)
+    elif f32:
+        split = wl.n <= (1 << 18 if few else 3 << 17)
     else:
-        split = wl.n <= (1 << 20 if f32 and not few else 1 << 18)
+        split = wl.n <= (3 << 16 if ct and wl.n % 8 == 0 and wl.n_workers > 64 else 1 << 18)
     if lars:
         ct = ct or f32 and (W > 1 or G & (G - 1) == 0) and ct_grouping(W, G, listed=True)
         return "lars_norms_split" if split else "lars_norms_kernel" if ct else "lars_norms_stream"

@@ -10,6 +10,7 @@
 
 #include "lsgd_host.hpp"
 #include "lsgd_kernels.hpp"
+#include "lsgd_rules.hpp"
 
 namespace lsgd {
 
@@ -181,40 +182,14 @@ LaunchShape pad_for_xcd_chunk(int64_t blocks, int64_t block_bytes) {
 
 int32_t launch_passes_per_block() { return g_units_per_lane.load(std::memory_order_relaxed); }
 
-// Parameters and momentum beyond this do not survive in the Infinity Cache
-// from one step to the next, whatever runs in between.
-constexpr int64_t kWarmStateBytes = int64_t{128} << 20;
-
-// Automatic rule, from measurements of the step with all copies in the step
-// kernel against the separate pass (two or three states in turn, so that no
-// step finds the state of the one before; us, fused / separate):
-//  - more than 16 workers (nontemporal parameters and momentum): the separate
-//    pass from 32 bytes of copies per element (8x4 binary32 R = 8 364 / 342,
-//    8x4 bfloat16 R = 16 241 / 234), or where the gradients take 256 bytes;
-//  - bfloat16 gradients with binary32 replicas: from 24 bytes, 16 beyond
-//    kWarmStateBytes (2x5, n = 1.2e7: 16 B 104 / 101, 24 B 126 / 115, 40 B 178
-//    / 144; unequal groups, n = 2.5e7: 16 B 297 / 275; plans of 60 tensors are
-//    even at 16 to 24);
-//  - beyond kWarmStateBytes: from 32 bytes (unequal 2, 3, 5, 6, n = 2.5e7:
-//    binary32 32 B 486 / 472, 48 B 569 / 512, bfloat16 32 B 361 / 341, 1x9
-//    bfloat16 32 B 304 / 280; 4x4 binary32 32 B 485 / 481);
-//  - else from 40 bytes with the compile-time kernels (4x4 binary32, n =
-//    1.2e7: 32 B 208 / 210, 40 B 229 / 224, 56 B 265 / 253; 2x2 48 B 154 / 148;
-//    3x5 44 B 228 / 222; 4x4 bfloat16 48 B 187 / 184), 48 with the stream
-//    kernels (unequal, 40 B 225 / 233, 48 B bfloat16 194 / 193).
-bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, size_t rsz, int64_t copy_bytes, int64_t n, bool stream) {
+bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, size_t rsz, int64_t copy_bytes, bool broadcast, int64_t n,
+                             bool stream) {
     if (copy_bytes <= 0) return false;
     const int32_t mode = g_copy_out_mode.load(std::memory_order_relaxed);
     if (mode == LSGD_COPY_OUT_FUSED) return false;
     if (mode == LSGD_COPY_OUT_SEPARATE) return true;
-    const int64_t grad_bytes = static_cast<int64_t>(n_workers) * static_cast<int64_t>(gsz);
-    const bool warm = n <= kWarmStateBytes / 8;
-    const int64_t crossing = !use_cached_state(n_workers, n) ? 32
-                             : gsz == 2 && rsz == 4          ? (warm ? 24 : 16)
-                             : !warm                         ? 32
-                             : stream                        ? 48
-                                                             : 40;
-    return copy_bytes >= crossing || grad_bytes >= 256;
+    return copies_apart(n_workers, static_cast<int>(gsz), static_cast<int>(rsz), copy_bytes, broadcast, n, stream,
+                        use_cached_state(n_workers, n));
 }
 
 // With the separate copy-out the step kernel still writes the first k replicas

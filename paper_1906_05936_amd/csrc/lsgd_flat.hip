@@ -316,7 +316,7 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
         if (use_split_flat(n, n_workers, gdt == LSGD_BF16, k.kernel != nullptr, pr.n_batches)) {
             const bool apart = separate_copy_out_small(
                 n, copy_bytes,
-                separate_copy_out_bytes(n_workers, dtype_size(gdt), dtype_size(rdt), copy_bytes, n, false));
+                separate_copy_out_bytes(n_workers, dtype_size(gdt), dtype_size(rdt), copy_bytes, bcast, n, false));
             a.bcast_grad = bcast ? (apart ? 1 : n_workers) : 0;
             a.n_replicas = apart ? replicas_in_step(n_workers, n_replicas, dtype_size(gdt), dtype_size(rdt), n, false)
                                  : n_replicas;
@@ -342,7 +342,7 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     // off, the step kernel writes the mean gradient to the first member only
     // and copy passes of their own write the rest (range by range: split_ranges).
     const bool split =
-        separate_copy_out_bytes(n_workers, dtype_size(gdt), dtype_size(rdt), copy_bytes, n, any_layout);
+        separate_copy_out_bytes(n_workers, dtype_size(gdt), dtype_size(rdt), copy_bytes, bcast, n, any_layout);
     a.bcast_grad = bcast ? (split ? 1 : n_workers) : 0;
     // split: the step kernel writes the first k replicas, the copy-out pass the rest
     const int32_t k_step =

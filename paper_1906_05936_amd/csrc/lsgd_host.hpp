@@ -94,7 +94,8 @@ int32_t launch_passes_per_block();
 // broadcast's copies of the mean gradient to the other members) writes them in
 // copy passes of their own (lsgd_set_copy_out_mode); `stream`: the step runs in
 // a stream kernel.
-bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, size_t rsz, int64_t copy_bytes, int64_t n, bool stream);
+bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, size_t rsz, int64_t copy_bytes, bool broadcast, int64_t n,
+                             bool stream);
 // Group counts other than powers of two that have compile-time kernels too
 // (lsgd_np2.hpp).
 inline bool np2_group_count(int G) { return G == 3 || G == 5 || G == 6 || G == 7 || G == 12; }

@@ -515,7 +515,7 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
         const int64_t copy_bytes = static_cast<int64_t>(plan->n_replicas) * rsz + 4 * bcast_copies;
         const bool apart = separate_copy_out_small(
             plan->total_elems, copy_bytes,
-            separate_copy_out_bytes(plan->n_workers, gsz, rsz, copy_bytes, plan->total_elems, false));
+            separate_copy_out_bytes(plan->n_workers, gsz, rsz, copy_bytes, bcast, plan->total_elems, false));
         const int32_t k_step =
             apart ? replicas_in_step(plan->n_workers, plan->n_replicas, gsz, rsz, plan->total_elems, false) : plan->n_replicas;
         PlanArgs fa = a;
@@ -547,7 +547,7 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     const int32_t bcast_copies = bcast ? plan->n_workers - 1 : 0;
     const int rsz = plan->rdt == LSGD_BF16 ? 2 : 4, gsz = plan->gdt == LSGD_BF16 ? 2 : 4;
     const bool split = separate_copy_out_bytes(plan->n_workers, gsz, rsz,
-                                               static_cast<int64_t>(plan->n_replicas) * rsz + 4 * bcast_copies,
+                                               static_cast<int64_t>(plan->n_replicas) * rsz + 4 * bcast_copies, bcast,
                                                plan->total_elems, !k);
     a.bcast_grad = bcast ? (split ? 1 : plan->n_workers) : 0;
     // split: the step kernel writes the first k replicas, the copy-out pass the rest

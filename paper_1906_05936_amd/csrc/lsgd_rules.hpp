@@ -43,4 +43,47 @@ inline bool split_serves(int64_t n, int n_workers, bool bf16, bool compile_time)
     return n <= (n_workers > 16 ? int64_t{3} << 17 : int64_t{1} << 18);
 }
 
+// ------------------------------------------------ copies in a pass of their own
+//
+// Parameters and momentum beyond this do not survive in the Infinity Cache
+// from one step to the next, whatever runs in between.
+constexpr int64_t kWarmStateBytes = int64_t{128} << 20;
+
+// Whether a step of n elements writes `copy_bytes` bytes of copies per element
+// (replicas of rsz bytes, the broadcast's copies of the mean gradient) after the
+// step kernel (apart) or in it. gsz: bytes of a gradient element. `cached`:
+// parameters and momentum go through the caches (at most 16 workers); `stream`:
+// the step runs in a stream kernel.
+//  - gradients of 256 bytes and more: apart;
+//  - nontemporal parameters and momentum: from 32 bytes (in the kernel / apart:
+//    8x4 binary32 R = 8 364 / 342, bfloat16 R = 16 241 / 234);
+//  - beyond kWarmStateBytes: from 32 bytes (unequal 2, 3, 5, 6, n = 2.5e7:
+//    binary32 32 B 486 / 472, 48 B 569 / 512, 1x9 bfloat16 32 B 304 / 280),
+//    16 for bfloat16 gradients with binary32 replicas (unequal, 297 / 275);
+//  - else the pass has a launch (2 to 3 us) and a second reading of the
+//    parameters to make good. bfloat16 gradients with binary32 replicas: from
+//    24 bytes and 32 MB of copies (apart / in the kernel, 1x4 to 4x4: n = 6e5
+//    32 B 1.04 to 1.07, 1e6 24 B 1.05 to 1.14, 32 B 0.89 to 0.97, 3e6 24 B
+//    0.83 to 0.88);
+//  - the others: from 48 bytes (up to 4 workers 56, stream kernels 64) and 128
+//    MB of copies (4x4 binary32: n = 3e5 48 B 1.34, 1e6 48 B 1.15, 56 B 1.13, 2e6
+//    56 B 1.00, 3e6 48 B 0.98, 40 B 0.97 to 1.00 from 2e6; 1x4 48 B 1.01 to 1.11,
+//    56 B 0.96 to 0.99 from 3e6; 2x4 48 B 0.98 to 1.03; 1x9, a stream kernel, 48
+//    B 1.05 to 1.08, 56 B 1.03 to 1.07);
+//  - with the broadcast, whose copies the step kernel already has at hand: from
+//    64 bytes, 52 from 12 workers (n = 3e6: 2x4 60 B 1.09, 3x3 48 B 1.07, 3x4 52
+//    B 1.02, 4x4 60 B 0.97; 1.2e7: 2x4 60 B 1.04, 3x4 60 B 0.98).
+inline bool copies_apart(int n_workers, int gsz, int rsz, int64_t copy_bytes, bool broadcast, int64_t n, bool stream,
+                         bool cached) {
+    if (copy_bytes <= 0) return false;
+    if (static_cast<int64_t>(n_workers) * gsz >= 256) return true;
+    if (!cached) return copy_bytes >= 32;
+    const bool widened = gsz == 2 && rsz == 4;
+    if (n > kWarmStateBytes / 8) return copy_bytes >= (widened ? 16 : 32);
+    const int64_t mb = n * copy_bytes >> 20;
+    if (widened) return copy_bytes >= 24 && mb >= 32;
+    const int crossing = broadcast ? (n_workers >= 12 ? 52 : 64) : stream ? 64 : n_workers <= 4 ? 56 : 48;
+    return copy_bytes >= crossing && mb >= 128;
+}
+
 }  // namespace lsgd

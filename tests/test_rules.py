@@ -23,6 +23,7 @@ int main() {
         for (int i = 0; i < k; ++i) std::cin >> v[i];
         bool r = false;
         if (rule == "split") r = split_serves(v[0], (int)v[1], v[2], v[3]);
+        else if (rule == "apart") r = copies_apart((int)v[0], (int)v[1], (int)v[2], v[3], v[4], v[5], v[6], v[7]);
         else return 1;
         std::printf("%d\n", (int)r);
     }
@@ -65,3 +66,27 @@ SPLIT = [
 def test_split_kernels(ask):
     got = ask("split", [r for r, _ in SPLIT])
     assert got == [want for _, want in SPLIT], [r for (r, w), g in zip(SPLIT, got) if w != g]
+
+
+# (workers, gradient bytes, replica bytes, copy bytes, broadcast, n, stream, cached), copies in their own pass faster?
+APART = [
+    ((4, 4, 4, 40, False, 300_000, False, True), False), ((16, 4, 4, 40, False, 300_000, False, True), False),
+    ((16, 4, 4, 56, False, 1_000_000, False, True), False), ((4, 4, 4, 40, False, 12_000_000, False, True), False),
+    ((16, 4, 4, 48, False, 3_000_000, False, True), True), ((4, 4, 4, 56, False, 5_000_000, False, True), True),
+    ((16, 4, 4, 56, False, 12_000_000, False, True), True), ((9, 4, 4, 56, False, 12_000_000, True, True), False),
+    ((4, 2, 2, 48, False, 1_000_000, False, True), False), ((8, 2, 2, 48, False, 5_000_000, False, True), True),
+    ((4, 2, 4, 32, False, 600_000, False, True), False), ((16, 2, 4, 32, False, 1_000_000, False, True), False),
+    ((16, 2, 4, 40, False, 1_000_000, False, True), True), ((10, 2, 4, 24, False, 3_000_000, False, True), True),
+    ((10, 2, 4, 16, False, 3_000_000, False, True), False), ((10, 2, 4, 16, False, 25_000_000, False, True), True),
+    ((16, 4, 4, 32, False, 25_000_000, False, True), True), ((32, 4, 4, 32, False, 1_000_000, True, False), True),
+    ((64, 4, 4, 4, False, 1_000_000, True, False), True),
+    ((8, 4, 4, 60, True, 300_000, False, True), False), ((8, 4, 4, 60, True, 12_000_000, False, True), False),
+    ((9, 4, 4, 40, True, 1_000_000, False, True), False), ((4, 4, 4, 44, True, 12_000_000, False, True), False),
+    ((16, 4, 4, 60, True, 3_000_000, False, True), True), ((16, 4, 4, 60, True, 1_000_000, False, True), False),
+    ((16, 4, 4, 0, False, 25_000_000, False, True), False),
+]
+
+
+def test_copies_apart(ask):
+    got = ask("apart", [r for r, _ in APART])
+    assert got == [want for _, want in APART], [r for (r, w), g in zip(APART, got) if w != g]
