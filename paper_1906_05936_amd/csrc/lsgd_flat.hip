@@ -8,6 +8,7 @@
 #include "lsgd_kernels.hpp"
 #include "lsgd_np2.hpp"
 #include "lsgd_pow2.hpp"
+#include "lsgd_rules.hpp"
 #include "lsgd_schedule.hpp"
 #include "lsgd_split_host.hpp"
 #include "lsgd_stream_host.hpp"
@@ -48,7 +49,7 @@ lsgd_status launch_means(MeanArgs& a, int K, int runs, bool bf16, void* stream, 
     const int64_t vec = bf16 ? Unit<uint16_t>::VEC : Unit<float>::VEC;
     a.W = K;
     LaunchShape ls = k.kernel ? launch_shape((a.n + vec - 1) / vec, k.tile)
-                              : launch_shape(stream_units(a.n, bf16), stream_tile(bf16));
+                              : launch_shape(stream_units(a.n, bf16, stream_tile(bf16)), stream_tile(bf16));
     if (static_cast<int64_t>(ls.blocks) * runs > kMaxGridBlocks) {   // the kernels stride over the rest
         ls.blocks = static_cast<unsigned>(kMaxGridBlocks / runs);
         ls.xcd_chunk = 0;
@@ -335,7 +336,8 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     const bool any_layout = !k.kernel;
     if (any_layout) {
         build();
-        k.tile = stream_tile(gdt == LSGD_BF16);
+        const bool two = gdt == LSGD_F32 && stream_two_units((n + 4095) / 4096, 2, n_workers, n, device_cus());
+        k.tile = stream_tile(gdt == LSGD_BF16, two);
     }
     // Copies per element besides parameters and momentum: the replicas, and
     // with the broadcast the mean gradient to the other N - 1 members. Split
@@ -354,11 +356,11 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     for (int64_t i = 0; i < K; ++i) {
         const int64_t lo = range_edge(n, K, i), hi = range_edge(n, K, i + 1);
         StepArgs ra = K == 1 ? a : offset_args(a, lo, hi, dtype_size(gdt), dtype_size(rdt), n_replicas);
-        const int64_t units = any_layout ? stream_units(ra.n, gdt == LSGD_BF16) : (ra.n + vec - 1) / vec;
+        const int64_t units = any_layout ? stream_units(ra.n, gdt == LSGD_BF16, k.tile) : (ra.n + vec - 1) / vec;
         const LaunchShape ls = launch_shape(units, k.tile);
         ra.xcd_chunk = ls.xcd_chunk;
         ra.upl = ls.upl;
-        if (any_layout) launch_flat_stream(ra, pr, gdt == LSGD_BF16, cached, ls.blocks, static_cast<hipStream_t>(stream));
+        if (any_layout) launch_flat_stream(ra, pr, gdt == LSGD_BF16, cached, k.tile, ls.blocks, static_cast<hipStream_t>(stream));
         else hipLaunchKernelGGL(k.kernel, dim3(ls.blocks), dim3(kBlock), 0, static_cast<hipStream_t>(stream), ra);
         if ((st = check_launch(what)) != LSGD_OK) return st;
         if (!split) continue;

@@ -43,6 +43,25 @@ inline bool split_serves(int64_t n, int n_workers, bool bf16, bool compile_time)
     return n <= (n_workers > 16 ? int64_t{3} << 17 : int64_t{1} << 18);
 }
 
+// ------------------------------------------- binary32 stream kernels, units
+//
+// Whether a binary32 step in a stream kernel takes lane tiles of two units and
+// nothing issued ahead instead of four: `pieces` workgroup tiles of 4096
+// elements on `cus` compute units, one at a time each, in at most `rounds`
+// rounds where the choice matters. Four / two units, us:
+//   up to 11 workers always (1x9: n = 1e6 10.0 / 9.9, 3e6 32.6 / 28.2, 1e7 95.2
+//   / 82.4, 2.5e7 245.9 / 233.3), up to 16 to 2^24 elements (1x14 1e7 122.0 /
+//   117.2, 2.5e7 329.0 / 336.0; unequal 2, 3, 5, 6 1e7 134.6 / 130.8, 2.5e7
+//   356.6 / 367.4);
+//   more workers, where the last round fills at most half of the units (8x8:
+//   n = 2^19 26.7 / 23.2, 6e5 30 / 33.8, 2^20 44.5 / 47.7, 2^20 + 1 57.7 / 48.6,
+//   1.1e6 63.2 / 54.6, 1.3e6 70.9 / 71.6, 1.6e6 73.3 / 78.0, 2.4e6 114.7 / 120.7;
+//   16x8: 2^19 48.9 / 43.1, 1.1e6 117.8 / 104.9), in the first two rounds.
+inline bool stream_two_units(int64_t pieces, int rounds, int n_workers, int64_t n, int cus) {
+    if (n_workers <= 16) return n_workers < 12 || n <= int64_t{1} << 24;
+    return pieces <= int64_t{rounds} * cus && (pieces - 1) % cus < cus / 2;
+}
+
 // ------------------------------------------------ copies in a pass of their own
 //
 // Parameters and momentum beyond this do not survive in the Infinity Cache

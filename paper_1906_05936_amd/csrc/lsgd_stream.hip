@@ -5,28 +5,35 @@ namespace lsgd {
 
 namespace {
 
-// LDS of the stack: a lane tile is 16 floats.
-size_t stack_bytes(const Program& pr) { return static_cast<size_t>(pr.stack_depth) * 16 * sizeof(float) * kBlock; }
-static_assert(StreamTile<float>::U * Unit<float>::VEC == 16 && StreamTile<uint16_t>::U * Unit<uint16_t>::VEC == 16, "");
+// LDS of the stack, whose slots hold a lane tile of `floats`.
+size_t stack_bytes(const Program& pr, int floats) {
+    return static_cast<size_t>(pr.stack_depth) * floats * sizeof(float) * kBlock;
+}
+
+template <int CACHED>
+auto pick_flat_stream(bool bf16, int tile) {
+    if (bf16) return step_flat_stream<uint16_t, 2, CACHED>;
+    return tile == 2 ? step_flat_stream<float, 2, CACHED> : step_flat_stream<float, 4, CACHED>;
+}
 
 }  // namespace
 
-void launch_flat_stream(const StepArgs& a, const Program& pr, bool bf16, bool cached, unsigned blocks, hipStream_t s) {
+void launch_flat_stream(const StepArgs& a, const Program& pr, bool bf16, bool cached, int tile, unsigned blocks,
+                        hipStream_t s) {
     FlatProgArgs fa;
     fa.a = a;
     fa.pr = pr;
-    const auto k = bf16 ? (cached ? step_flat_stream<uint16_t, 1> : step_flat_stream<uint16_t, 0>)
-                        : (cached ? step_flat_stream<float, 1> : step_flat_stream<float, 0>);
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr), s, fa);
+    const auto k = cached ? pick_flat_stream<1>(bf16, tile) : pick_flat_stream<0>(bf16, tile);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr, tile * (bf16 ? 8 : 4)), s, fa);
 }
 
 void launch_plan_stream(const PlanArgs& a, const Program& pr, bool bf16, bool cached, unsigned blocks, hipStream_t s) {
     PlanProgArgs pa;
     pa.a = a;
     pa.pr = pr;
-    const auto k = bf16 ? (cached ? step_plan_stream<uint16_t, 1> : step_plan_stream<uint16_t, 0>)
-                        : (cached ? step_plan_stream<float, 1> : step_plan_stream<float, 0>);
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr), s, pa);
+    const auto k = bf16 ? (cached ? step_plan_stream<uint16_t, 2, 1> : step_plan_stream<uint16_t, 2, 0>)
+                        : (cached ? step_plan_stream<float, 4, 1> : step_plan_stream<float, 4, 0>);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr, 16), s, pa);
 }
 
 void launch_mean_stream(const MeanArgs& a, const Program& pr, bool bf16, dim3 blocks, hipStream_t s) {
@@ -34,11 +41,11 @@ void launch_mean_stream(const MeanArgs& a, const Program& pr, bool bf16, dim3 bl
     ma.a = a;
     ma.pr = pr;
     const auto k = bf16 ? mean_stream<uint16_t> : mean_stream<float>;
-    hipLaunchKernelGGL(k, blocks, dim3(kBlock), stack_bytes(pr), s, ma);
+    hipLaunchKernelGGL(k, blocks, dim3(kBlock), stack_bytes(pr, 16), s, ma);
 }
 
-int64_t stream_units(int64_t n, bool bf16) {
-    const int64_t vec = bf16 ? Unit<uint16_t>::VEC : Unit<float>::VEC, per_tile = kBlock * stream_tile(bf16);
+int64_t stream_units(int64_t n, bool bf16, int tile) {
+    const int64_t vec = bf16 ? Unit<uint16_t>::VEC : Unit<float>::VEC, per_tile = kBlock * tile;
     return n % vec == 0 ? n / vec : (n / vec + per_tile - 1) / per_tile * per_tile + 1;
 }
 
@@ -47,7 +54,7 @@ void launch_lars_norms_stream(const LarsArgs& a, const Program& pr, bool bf16, u
     la.la = a;
     la.pr = pr;
     const auto k = bf16 ? lars_norms_stream<uint16_t> : lars_norms_stream<float>;
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr), s, la);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr, 16), s, la);
 }
 
 }  // namespace lsgd

@@ -14,11 +14,14 @@
 // 5, 6 4796 / 5714; binary32 10x4 5394 / 6353, 9x8 6104 / 6405, 20x3 5251 /
 // 6309. Bound by memory since: a large copy runs at 6443 GB/s.
 //
-// binary32: four units per lane (consecutive instructions of a wave stay on a
-// buffer's pages), the next batch's loads issued before the additions in LDS
-// (without that 9x8 ran at 6022 GB/s, with two units at 6019). bfloat16: two
-// units (one: 10x4 5775, 20x3 5675); issuing ahead took 256 registers and cost
-// it 7 to 17%.
+// binary32 has two forms. Four units per lane (consecutive instructions of a
+// wave stay on a buffer's pages), the next batch's loads issued before the
+// additions in LDS (without that 9x8 ran at 6022 GB/s, with two units at 6019):
+// one workgroup per compute unit, so a step takes as long as its fullest unit.
+// Two units, nothing issued ahead: two workgroups per unit, which is better for
+// few workers and where the last round of four-unit tiles leaves most units
+// idle (stream_two_units, lsgd_rules.hpp). bfloat16: two units (one: 10x4 5775,
+// 20x3 5675); issuing ahead took 256 registers and cost it 7 to 17%.
 //
 // A lane whose units lie beyond the end loads the last whole unit again and
 // stores nothing; the ragged end is a tile of its own, one element per lane.
@@ -31,9 +34,9 @@
 
 namespace lsgd {
 
-template <typename GT> struct StreamTile {
-    static constexpr int U = stream_tile(sizeof(GT) == 2);
-};
+// Whether a lane tile of U units issues the next batch's loads ahead.
+template <typename GT, int U>
+constexpr bool stream_ahead() { return sizeof(GT) == 4 && U == 4; }
 
 // A lane tile: its units' (or, tail, its element's) first elements, clamped
 // into the buffer, and whether each is the lane's to store.
@@ -181,7 +184,7 @@ struct MeanSrc {
 template <typename GT>
 __global__ __launch_bounds__(kBlock) void mean_stream(MeanProgArgs ma) {
     extern __shared__ f32x4 stream_lds[];
-    constexpr int U = StreamTile<GT>::U;
+    constexpr int U = stream_tile(sizeof(GT) == 2);
     constexpr int VEC = Unit<GT>::VEC;
     constexpr int T = U * VEC;
     const MeanArgs& a = ma.a;
@@ -212,7 +215,7 @@ __device__ __forceinline__ void stream_step_tile(const Src& s, const Program& pr
     constexpr int T = U * VEC;
     if (t.tail) {   // one element per lane
         float g[T];
-        stream_mean<GT, U, sizeof(GT) == 4>(s, pr, t, stk, g);
+        stream_mean<GT, U, stream_ahead<GT, U>()>(s, pr, t, stk, g);
         if (!t.own[0]) return;
         const int64_t e = t.e[0];
         float g1[1] = {g[0]}, p[1] = {gload_ptr<float>(s.p())[e]}, m[1] = {gload_ptr<float>(s.m())[e]};
@@ -230,7 +233,7 @@ __device__ __forceinline__ void stream_step_tile(const Src& s, const Program& pr
     }
     float p[T], m[T], g[T];
     load_state<VEC, U, false>(s, t.e, VEC, p, m);   // their latency overlaps the gradient stream
-    stream_mean<GT, U, sizeof(GT) == 4>(s, pr, t, stk, g);
+    stream_mean<GT, U, stream_ahead<GT, U>()>(s, pr, t, stk, g);
     sgd_update<T>(s.hyper(), g, p, m);
     // a lane's units past the end are its last ones: q units are its own
 #pragma unroll
@@ -250,10 +253,9 @@ __device__ __forceinline__ void stream_step_tile(const Src& s, const Program& pr
     }
 }
 
-template <typename GT, int CACHED>
+template <typename GT, int U, int CACHED>
 __global__ __launch_bounds__(kBlock) void step_flat_stream(FlatProgArgs fa) {
     extern __shared__ f32x4 stream_lds[];
-    constexpr int U = StreamTile<GT>::U;
     constexpr int VEC = Unit<GT>::VEC;
     const StepArgs& a = fa.a;
     const FlatSrcT<CACHED> s{a, resolve_hyper(a.h, a.lr_ptr)};
@@ -264,10 +266,9 @@ __global__ __launch_bounds__(kBlock) void step_flat_stream(FlatProgArgs fa) {
             stream_step_tile<GT, U>(s, fa.pr, tile_at<U, VEC>(0, a.n, base + q), stream_lds);
 }
 
-template <typename GT, int CACHED>
+template <typename GT, int U, int CACHED>
 __global__ __launch_bounds__(kBlock) void step_plan_stream(PlanProgArgs pa) {
     extern __shared__ f32x4 stream_lds[];
-    constexpr int U = StreamTile<GT>::U;
     constexpr int VEC = Unit<GT>::VEC;
     for_plan_chunks<CACHED>(pa.a, [&](const PlanSrcT<CACHED>& s, const PlanChunk& ch, int32_t) {
         const int64_t tiles = tile_count(ch.len, VEC, U);

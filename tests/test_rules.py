@@ -24,6 +24,7 @@ int main() {
         bool r = false;
         if (rule == "split") r = split_serves(v[0], (int)v[1], v[2], v[3]);
         else if (rule == "apart") r = copies_apart((int)v[0], (int)v[1], (int)v[2], v[3], v[4], v[5], v[6], v[7]);
+        else if (rule == "two") r = stream_two_units(v[0], (int)v[1], (int)v[2], v[3], (int)v[4]);
         else return 1;
         std::printf("%d\n", (int)r);
     }
@@ -90,3 +91,14 @@ APART = [
 def test_copies_apart(ask):
     got = ask("apart", [r for r, _ in APART])
     assert got == [want for _, want in APART], [r for (r, w), g in zip(APART, got) if w != g]
+
+
+# (elements, workers), two-unit tiles faster? (flat, 256 compute units)
+TWO_UNITS = [((25_557_032, 9), True), ((25_557_032, 14), False), ((10_000_000, 14), True), ((1 << 19, 64), True),
+             ((600_000, 64), False), ((1 << 20, 64), False), (((1 << 20) + 1, 64), True), ((1_100_000, 128), True),
+             ((1_600_000, 64), False), ((2_400_000, 64), False), ((25_557_032, 64), False)]
+
+
+def test_two_unit_tiles(ask):
+    got = ask("two", [(-(-n // 4096), 2, N, n, 256) for (n, N), _ in TWO_UNITS])
+    assert got == [want for _, want in TWO_UNITS], [r for (r, w), g in zip(TWO_UNITS, got) if w != g]
