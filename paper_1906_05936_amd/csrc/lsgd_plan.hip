@@ -1,12 +1,16 @@
 // Multi-tensor plans of liblsgd: the fused step over a list of parameter
 // tensors (a model's per-layer tensors) in one kernel launch.
 //
-// lsgd_plan_create cuts every tensor into pieces of P workgroup tile passes
-// (256 lanes x the kernel's lane tile: 2048 elements for binary32 and bf16
-// gradients alike, times P = the launch shape's passes per workgroup at plan
-// creation, 1 by default), starting on unit boundaries. One workgroup runs one
-// piece (a large tensor is walked exactly like the flat kernel walks a
-// vector); pieces are taken in the XCD-chunked order of the launch shape.
+// lsgd_plan_create cuts every tensor into pieces of 2048 elements (times the
+// launch shape's passes per workgroup at plan creation, 1 by default), starting
+// on unit boundaries, and, where the step or LARS norms kernel's lane tile makes
+// a workgroup cover 4096, into pieces of that size too. One workgroup runs one
+// piece (a large tensor is walked exactly like the flat kernel walks a vector);
+// pieces are taken in the XCD-chunked order of the launch shape. The copy-out
+// pass and the LARS update always take the 2048-element pieces, one lane tile of
+// theirs: over pieces of 4096 a workgroup made two trips one after the other
+// (binary32, n = 2.5e7, R = N, us: copies of 8x8 plans 2383 -> 2230 for the step,
+// 10x4 LARS 1643 -> 1574).
 #include <string.h>
 
 #include <algorithm>
@@ -15,18 +19,27 @@
 #include "lsgd_np2.hpp"
 #include "lsgd_plan_kernels.hpp"
 #include "lsgd_pow2.hpp"
+#include "lsgd_rules.hpp"
 #include "lsgd_split_host.hpp"
 #include "lsgd_stream_host.hpp"
+
+// One way to cut the plan's tensors: n pieces of `piece` elements in device memory.
+struct PieceTable {
+    int32_t n;
+    int64_t piece;
+    lsgd::PlanChunk* d;
+};
 
 struct lsgd_plan {
     int device;
     int32_t n_tensors, n_workers, n_groups, n_replicas;
     int32_t W;   // group size, 0 where the groups' sizes differ
     lsgd_dtype gdt, rdt;
-    int32_t n_chunks, stride;
-    int64_t piece;  // elements per piece
+    int32_t stride;
     int64_t total_elems;  // elements of all tensors
-    lsgd::PlanChunk* d_chunks;
+    PieceTable small, large;   // pieces of 2048 and of 4096 elements (large.n == 0: no kernel of the plan takes them)
+    int step_tile[2];          // units per lane tile of the step kernel: mean of means, paper-literal
+    int lars_tile;             // of the LARS norms kernel
     // small plans: the split kernels' pieces of at most kSplitElems elements
     // (n_fine == 0: the plan takes the other kernels)
     int32_t n_fine;
@@ -59,15 +72,18 @@ struct PlanPick {
     int tile;
 };
 
-// Elements per piece: one tile pass of the plan's kernel.
-template <typename GT>
-constexpr int64_t piece_elems(int tile) { return static_cast<int64_t>(kBlock) * Unit<GT>::VEC * tile; }
-static_assert(piece_elems<float>(1) % 8 == 0 && piece_elems<uint16_t>(1) % 8 == 0,
-              "pieces must start on unit boundaries");
+constexpr int64_t kSmallPiece = 2048, kLargePiece = 4096;
+
+// Whether a workgroup's lane tiles of `tile` units cover a large piece.
+constexpr bool large_pieces(int tile, bool bf16) {
+    return static_cast<int64_t>(kBlock) * tile * (bf16 ? Unit<uint16_t>::VEC : Unit<float>::VEC) > kSmallPiece;
+}
+static_assert(kSmallPiece % 8 == 0, "pieces must start on unit boundaries");
+static_assert(large_pieces(4, false) && !large_pieces(2, false) && large_pieces(2, true) && !large_pieces(1, true), "");
 
 // The plan kernel for (W, G): compile-time for the power-of-two groupings of
 // pick_flat (lsgd_flat.hip), with parameters and momentum through the caches
-// when `cached`; else none.
+// when `cached`; else none (and tile 0).
 template <typename GT>
 PlanPick pick_plan(int W, int G, bool cached = false) {
     const PlanKernel k = pick_plan_pow2<GT>(W, G, cached);
@@ -76,7 +92,7 @@ PlanPick pick_plan(int W, int G, bool cached = false) {
         const Np2PlanPick q = pick_plan_np2(W, G, cached, sizeof(GT) == 2);
         if (q.kernel) return PlanPick{q.kernel, q.tile};
     }
-    return PlanPick{nullptr, stream_tile(sizeof(GT) == 2)};
+    return PlanPick{nullptr, 0};
 }
 
 lsgd_status check_device(const lsgd_plan* plan) {
@@ -86,11 +102,23 @@ lsgd_status check_device(const lsgd_plan* plan) {
     return LSGD_OK;
 }
 
-// Kernel arguments of a plan step and the launch shape over its pieces.
-PlanArgs plan_args(const lsgd_plan* plan, Hyper h, const float* lr_device, LaunchShape& ls) {
+// The pieces a kernel with lane tiles of `tile` units takes.
+const PieceTable& pieces_for(const lsgd_plan* plan, int tile) {
+    return large_pieces(tile, plan->gdt == LSGD_BF16) ? plan->large : plan->small;
+}
+
+// Points the arguments at a table's pieces, with the launch shape over them.
+void use_pieces(const lsgd_plan* plan, const PieceTable& t, PlanArgs& a, LaunchShape& ls) {
+    a.chunks = t.d;
+    a.n_chunks = t.n;
+    ls = pad_for_xcd_chunk(t.n, (plan->gdt == LSGD_BF16 ? 2 : 4) * t.piece);
+    a.xcd_chunk = ls.xcd_chunk;
+}
+
+// Kernel arguments of a plan step and the launch shape over the pieces `t`.
+PlanArgs plan_args(const lsgd_plan* plan, const PieceTable& t, Hyper h, const float* lr_device, LaunchShape& ls) {
     PlanArgs a;
     memset(&a, 0, sizeof a);
-    a.chunks = plan->d_chunks;
     a.ptrs = plan->d_ptrs;
     a.stride = plan->stride;
     a.n_workers = plan->n_workers;
@@ -101,12 +129,9 @@ PlanArgs plan_args(const lsgd_plan* plan, Hyper h, const float* lr_device, Launc
     a.rdt = static_cast<int32_t>(plan->rdt);
     a.h = h;
     a.lr_ptr = lr_device;
-    a.n_chunks = plan->n_chunks;
     a.copy_src = 0;                              // the copy-out: p to the replicas
     a.copy_dst = 2 + plan->n_workers;
-    const int64_t block_bytes = (plan->gdt == LSGD_BF16 ? 2 : 4) * plan->piece;
-    ls = pad_for_xcd_chunk(plan->n_chunks, block_bytes);
-    a.xcd_chunk = ls.xcd_chunk;
+    use_pieces(plan, t, a, ls);
     return a;
 }
 
@@ -126,10 +151,13 @@ constexpr int kPlanCopyRKF32 = 1, kPlanCopyRKBF16 = 2;
 // group; a lane tile covers a 2048-element piece (the usual piece size).
 template <int VEC, int RK>
 lsgd_status launch_plan_copy_out(const lsgd_plan* plan, PlanArgs& a, hipStream_t s) {
-    constexpr int U = 2048 / (VEC * kBlock);
+    constexpr int U = kSmallPiece / (VEC * kBlock);
     static_assert(U >= 1, "at least one unit per lane");
-    const int64_t win = copy_window_blocks(4 * plan->piece, plan->n_chunks);
-    const int64_t blocks = (plan->n_chunks + win - 1) / win * ((a.n_replicas + RK - 1) / RK) * win;
+    const PieceTable& t = plan->small;
+    a.chunks = t.d;
+    a.n_chunks = t.n;
+    const int64_t win = copy_window_blocks(4 * t.piece, t.n);
+    const int64_t blocks = (t.n + win - 1) / win * ((a.n_replicas + RK - 1) / RK) * win;
     a.win_blocks = static_cast<int32_t>(win);
     a.copy_blocks = blocks;
     const int64_t grid = std::min<int64_t>(blocks, stride_grid_cap());   // the kernel strides over the rest
@@ -176,6 +204,10 @@ LarsKernel pick_lars(int W, int G) {
     return np2_group_count(G) ? pick_lars_np2(W, G, sizeof(GT) == 2) : nullptr;
 }
 
+// Units per lane tile of the LARS norms kernel for equal groups (W, G).
+template <typename GT>
+int lars_norms_tile(int W, int G) { return pick_lars<GT>(W, G) ? lars_tile_units<GT>(W * G, G) : kLarsStreamTile; }
+
 // LARS workspace layout: [gbar scratch | per-chunk partials | trust ratios],
 // each part starting on a 256-byte boundary.
 struct LarsLayout {
@@ -188,14 +220,15 @@ LarsLayout lars_layout(const lsgd_plan* plan) {
     LarsLayout l;
     l.gbar = 0;
     l.partials = round256(static_cast<size_t>(plan->gbar_floats) * sizeof(float));
-    l.trust = l.partials + round256(static_cast<size_t>(plan->n_fine ? plan->n_fine : plan->n_chunks) * 2 * sizeof(double));
+    l.trust = l.partials + round256(static_cast<size_t>(plan->n_fine ? plan->n_fine : pieces_for(plan, plan->lars_tile).n) * 2 * sizeof(double));
     l.total = l.trust + round256(static_cast<size_t>(plan->n_tensors) * sizeof(float));
     return l;
 }
 
 void free_plan(lsgd_plan* p) {
     if (!p) return;
-    if (p->d_chunks) (void)hipFree(p->d_chunks);
+    if (p->small.d) (void)hipFree(p->small.d);
+    if (p->large.d) (void)hipFree(p->large.d);
     if (p->d_fine) (void)hipFree(p->d_fine);
     if (p->d_ptrs) (void)hipFree(p->d_ptrs);
     if (p->d_gbar_off) (void)hipFree(p->d_gbar_off);
@@ -254,7 +287,7 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     LarsArgs la;
     memset(&la, 0, sizeof la);
     LaunchShape ls;
-    la.pa = plan_args(plan, Hyper{lr, momentum_coef, weight_decay}, lr_device, ls);
+    la.pa = plan_args(plan, pieces_for(plan, plan->lars_tile), Hyper{lr, momentum_coef, weight_decay}, lr_device, ls);
     la.gbar_off = plan->d_gbar_off;
     la.tensor_chunks = plan->d_tensor_chunks;
     char* ws = static_cast<char*>(workspace);
@@ -282,7 +315,7 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
             return plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, la.pa, s)
                                           : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, la.pa, s);
         }
-    } else if (plan->n_chunks > 0) {
+    } else if (plan->small.n > 0) {
         int32_t W = plan->W, G = plan->n_groups;
         if (one_group_form(W, G, false)) {
             W = plan->n_workers;
@@ -295,7 +328,8 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     }
     hipLaunchKernelGGL(lars_trust_kernel, dim3(plan->n_tensors), dim3(kBlock), 0, s, la);
     if ((st = check_launch("lsgd_lars_step_plan (trust)")) != LSGD_OK) return st;
-    if (plan->n_chunks == 0) return LSGD_OK;
+    if (plan->small.n == 0) return LSGD_OK;
+    use_pieces(plan, plan->small, la.pa, ls);
     // the update reads and writes as lsgd_sgd_step does: the same copy-out rule
     const bool split = separate_copy_out_update(plan->n_replicas, rsz,
                                                 use_cached_state(plan->n_workers, plan->total_elems));
@@ -339,21 +373,34 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     const int32_t stride = 2 + n_workers + n_replicas;
     std::vector<void*> table(static_cast<size_t>(n_tensors) * stride, nullptr);
     std::vector<Range> ranges;
-    std::vector<PlanChunk> chunks;
-    // one tile pass of the kernel, times the launch shape's passes per workgroup
+    std::vector<PlanChunk> chunks, large_chunks;
+    // the kernels' lane tiles, and with them which pieces they take
+    const bool bf16 = gdt == LSGD_BF16;
     const int32_t W = equal ? n_workers / n_groups : 0;
     const bool as_one = one_group_form(W, n_groups, false);
     const int32_t tW = as_one ? n_workers : W, tG = as_one ? 1 : n_groups;
-    const int tile = gdt == LSGD_BF16 ? pick_plan<uint16_t>(tW, tG).tile : pick_plan<float>(tW, tG).tile;
-    const int64_t kPiece = (gdt == LSGD_BF16 ? piece_elems<uint16_t>(tile) : piece_elems<float>(tile)) *
-                           launch_passes_per_block();
+    int64_t total_elems = 0, four_unit_pieces = 0;
+    for (int32_t t = 0; t < n_tensors; ++t) {
+        if (numel[t] < 0) return fail(LSGD_ERR_SIZE, "numel[%d]=%lld < 0", t, static_cast<long long>(numel[t]));
+        total_elems += numel[t];
+        four_unit_pieces += (numel[t] + kLargePiece - 1) / kLargePiece;
+    }
+    auto step_tile = [&](int32_t w, int32_t g) {
+        const PlanPick k = bf16 ? pick_plan<uint16_t>(w, g) : pick_plan<float>(w, g);
+        return k.kernel ? k.tile
+                        : stream_tile(bf16, !bf16 && stream_two_units(four_unit_pieces, 4, n_workers, total_elems, device_cus()));
+    };
+    const int mean_tile = step_tile(tW, tG), literal_tile = as_one ? step_tile(W, n_groups) : mean_tile;
+    const int lars_tile = W == 0 ? mean_tile : bf16 ? lars_norms_tile<uint16_t>(tW, tG) : lars_norms_tile<float>(tW, tG);
+    const bool need_large = large_pieces(mean_tile, bf16) || large_pieces(literal_tile, bf16) || large_pieces(lars_tile, bf16);
+    const int64_t kSmall = kSmallPiece * launch_passes_per_block(), kLarge = kLargePiece * launch_passes_per_block();
     std::vector<int64_t> gbar_off(n_tensors, 0);
     std::vector<int32_t> tensor_chunks(n_tensors + 1, 0);
     int64_t gbar_floats = 0;
     for (int32_t t = 0; t < n_tensors; ++t) {
         const int64_t ne = numel[t];
-        if (ne < 0) return fail(LSGD_ERR_SIZE, "numel[%d]=%lld < 0", t, static_cast<long long>(ne));
-        tensor_chunks[t] = static_cast<int32_t>(std::min<size_t>(chunks.size(), 0x7fffffff));
+        tensor_chunks[t] = static_cast<int32_t>(
+            std::min<size_t>(large_pieces(lars_tile, bf16) ? large_chunks.size() : chunks.size(), 0x7fffffff));
         gbar_off[t] = gbar_floats;
         gbar_floats += (ne + kGbarAlign - 1) / kGbarAlign * kGbarAlign;
         if (ne == 0) continue;
@@ -380,15 +427,14 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
             if ((st = add(rp, rsz, true, "replicas", r)) != LSGD_OK) return st;
             row[2 + n_workers + r] = rp;
         }
-        for (int64_t s0 = 0; s0 < ne; s0 += kPiece) {
-            const int64_t len = std::min(kPiece, ne - s0);
-            // every piece but a tensor's last has len == kPiece (a multiple of the unit)
-            chunks.push_back(PlanChunk{params[t], t, 0, s0, len});
-        }
+        // every piece but a tensor's last has the full length (a multiple of the unit)
+        for (int64_t s0 = 0; s0 < ne; s0 += kSmall)
+            chunks.push_back(PlanChunk{params[t], t, 0, s0, std::min(kSmall, ne - s0)});
+        if (need_large)
+            for (int64_t s0 = 0; s0 < ne; s0 += kLarge)
+                large_chunks.push_back(PlanChunk{params[t], t, 0, s0, std::min(kLarge, ne - s0)});
     }
     if ((st = check_overlap(ranges)) != LSGD_OK) return st;
-    int64_t total_elems = 0;
-    for (int32_t t = 0; t < n_tensors; ++t) total_elems += numel[t];
     Program mean_program, literal_program;
     memset(&mean_program, 0, sizeof mean_program);
     if (equal) build_program(n_groups, gstart.data(), false, mean_program);
@@ -413,7 +459,9 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     // one workgroup per tensor in the LARS trust kernel, in one launch
     if (n_tensors > kMaxGridBlocks)
         return fail(LSGD_ERR_SIZE, "more than %lld tensors", static_cast<long long>(kMaxGridBlocks));
-    tensor_chunks[n_tensors] = static_cast<int32_t>(fine.empty() ? chunks.size() : fine.size());
+    tensor_chunks[n_tensors] = static_cast<int32_t>(!fine.empty()                  ? fine.size()
+                                                    : large_pieces(lars_tile, bf16) ? large_chunks.size()
+                                                                                    : chunks.size());
 
     lsgd_plan* p = new lsgd_plan;
     memset(p, 0, sizeof *p);
@@ -428,9 +476,12 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     p->n_replicas = n_replicas;
     p->gdt = gdt;
     p->rdt = rdt;
-    p->n_chunks = static_cast<int32_t>(chunks.size());
+    p->small = PieceTable{static_cast<int32_t>(chunks.size()), kSmall, nullptr};
+    p->large = PieceTable{static_cast<int32_t>(large_chunks.size()), kLarge, nullptr};
+    p->step_tile[0] = mean_tile;
+    p->step_tile[1] = literal_tile;
+    p->lars_tile = lars_tile;
     p->stride = stride;
-    p->piece = kPiece;
     p->total_elems = total_elems;
     p->n_fine = static_cast<int32_t>(fine.size());
     p->mean_program = mean_program;
@@ -443,15 +494,16 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
         if (strcmp(r.what, "grads") == 0) r.written = true;
     p->grads_apart = !any_written_overlap(ranges);
     hipError_t e = hipSuccess;
-    const size_t chunk_bytes = std::max<size_t>(1, chunks.size()) * sizeof(PlanChunk);
     const size_t table_bytes = table.size() * sizeof(void*);
-    if (e == hipSuccess) e = hipMalloc(&p->d_chunks, chunk_bytes);
+    auto upload = [&](const std::vector<PlanChunk>& from, PlanChunk** to) {
+        if (e != hipSuccess || from.empty()) return;
+        e = hipMalloc(to, from.size() * sizeof(PlanChunk));
+        if (e == hipSuccess) e = hipMemcpy(*to, from.data(), from.size() * sizeof(PlanChunk), hipMemcpyHostToDevice);
+    };
+    upload(chunks, &p->small.d);
+    upload(large_chunks, &p->large.d);
+    upload(fine, &p->d_fine);
     if (e == hipSuccess) e = hipMalloc(&p->d_ptrs, table_bytes);
-    if (e == hipSuccess && !fine.empty()) e = hipMalloc(&p->d_fine, fine.size() * sizeof(PlanChunk));
-    if (e == hipSuccess && !fine.empty())
-        e = hipMemcpy(p->d_fine, fine.data(), fine.size() * sizeof(PlanChunk), hipMemcpyHostToDevice);
-    if (e == hipSuccess && !chunks.empty())
-        e = hipMemcpy(p->d_chunks, chunks.data(), chunks.size() * sizeof(PlanChunk), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(p->d_ptrs, table.data(), table_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc(&p->d_gbar_off, gbar_off.size() * sizeof(int64_t));
     if (e == hipSuccess) e = hipMalloc(&p->d_lars_exclude, static_cast<size_t>(n_tensors));
@@ -502,11 +554,12 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
         lsgd_status st = check_overlap(ranges);
         if (st != LSGD_OK) return st;
     }
-    if (plan->n_chunks == 0) return LSGD_OK;
+    if (plan->small.n == 0) return LSGD_OK;
     lsgd_status st = check_device(plan);
     if (st != LSGD_OK) return st;
+    const int tile = plan->step_tile[literal];
     LaunchShape ls;
-    PlanArgs a = plan_args(plan, Hyper{lr, momentum_coef, weight_decay}, lr_device, ls);
+    PlanArgs a = plan_args(plan, pieces_for(plan, tile), Hyper{lr, momentum_coef, weight_decay}, lr_device, ls);
     a.literal = literal ? 1 : 0;
     if (plan->n_fine > 0) {
         const Program& pr = literal ? plan->literal_program : plan->mean_program;
@@ -556,18 +609,18 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     a.n_replicas = k_step;
     const hipStream_t s = static_cast<hipStream_t>(stream);
     if (k) hipLaunchKernelGGL(k, dim3(ls.blocks), dim3(kBlock), 0, s, a);
-    else launch_plan_stream(a, literal ? plan->literal_program : plan->mean_program, plan->gdt == LSGD_BF16, cached, ls.blocks, s);
+    else launch_plan_stream(a, literal ? plan->literal_program : plan->mean_program, plan->gdt == LSGD_BF16, cached, tile, ls.blocks, s);
     if ((st = check_launch("lsgd_step_plan")) != LSGD_OK || !split) return st;
     return launch_plan_copies(plan, a, k_step, bcast_copies, s);
 }
 
 LSGD_API lsgd_status lsgd_plan_copy_out(const lsgd_plan* plan, void* stream) {
     if (!plan) return fail(LSGD_ERR_NULL, "plan is NULL");
-    if (plan->n_chunks == 0 || plan->n_replicas == 0) return LSGD_OK;
+    if (plan->small.n == 0 || plan->n_replicas == 0) return LSGD_OK;
     lsgd_status st = check_device(plan);
     if (st != LSGD_OK) return st;
     LaunchShape ls;
-    PlanArgs a = plan_args(plan, Hyper{0.f, 0.f, 0.f}, nullptr, ls);
+    PlanArgs a = plan_args(plan, plan->small, Hyper{0.f, 0.f, 0.f}, nullptr, ls);
     const hipStream_t s = static_cast<hipStream_t>(stream);
     return plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, a, s)
                                   : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, a, s);

@@ -181,7 +181,7 @@ __device__ __forceinline__ void copy_out_plan_block(const PlanArgs& a, int64_t b
     const int rem = len - full * VEC;
     const int units = full + (rem != 0 ? 1 : 0);
     // pieces of the usual size are one lane tile (loads, then stores, as in
-    // the flat pass); longer ones (units_per_lane above 1, four-unit tiles) loop
+    // the flat pass); longer ones (units_per_lane above 1) loop
     int t0 = static_cast<int>(threadIdx.x);
     do {
         float x[U][VEC];

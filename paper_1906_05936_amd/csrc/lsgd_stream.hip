@@ -16,6 +16,12 @@ auto pick_flat_stream(bool bf16, int tile) {
     return tile == 2 ? step_flat_stream<float, 2, CACHED> : step_flat_stream<float, 4, CACHED>;
 }
 
+template <int CACHED>
+auto pick_plan_stream(bool bf16, int tile) {
+    if (bf16) return step_plan_stream<uint16_t, 2, CACHED>;
+    return tile == 2 ? step_plan_stream<float, 2, CACHED> : step_plan_stream<float, 4, CACHED>;
+}
+
 }  // namespace
 
 void launch_flat_stream(const StepArgs& a, const Program& pr, bool bf16, bool cached, int tile, unsigned blocks,
@@ -27,13 +33,13 @@ void launch_flat_stream(const StepArgs& a, const Program& pr, bool bf16, bool ca
     hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr, tile * (bf16 ? 8 : 4)), s, fa);
 }
 
-void launch_plan_stream(const PlanArgs& a, const Program& pr, bool bf16, bool cached, unsigned blocks, hipStream_t s) {
+void launch_plan_stream(const PlanArgs& a, const Program& pr, bool bf16, bool cached, int tile, unsigned blocks,
+                        hipStream_t s) {
     PlanProgArgs pa;
     pa.a = a;
     pa.pr = pr;
-    const auto k = bf16 ? (cached ? step_plan_stream<uint16_t, 2, 1> : step_plan_stream<uint16_t, 2, 0>)
-                        : (cached ? step_plan_stream<float, 4, 1> : step_plan_stream<float, 4, 0>);
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr, 16), s, pa);
+    const auto k = cached ? pick_plan_stream<1>(bf16, tile) : pick_plan_stream<0>(bf16, tile);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr, tile * (bf16 ? 8 : 4)), s, pa);
 }
 
 void launch_mean_stream(const MeanArgs& a, const Program& pr, bool bf16, dim3 blocks, hipStream_t s) {
@@ -54,7 +60,7 @@ void launch_lars_norms_stream(const LarsArgs& a, const Program& pr, bool bf16, u
     la.la = a;
     la.pr = pr;
     const auto k = bf16 ? lars_norms_stream<uint16_t> : lars_norms_stream<float>;
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr, 16), s, la);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kBlock), stack_bytes(pr, kLarsStreamTile * (bf16 ? 8 : 4)), s, la);
 }
 
 }  // namespace lsgd

@@ -285,7 +285,7 @@ template <typename GT>
 __global__ __launch_bounds__(kBlock) void lars_norms_stream(LarsProgArgs sa) {
     extern __shared__ f32x4 stream_lds[];
     __shared__ double sums[kBlock / 64][2];
-    constexpr int U = 2;
+    constexpr int U = kLarsStreamTile;
     constexpr int VEC = Unit<GT>::VEC;
     constexpr int T = U * VEC;
     const LarsArgs& la = sa.la;
