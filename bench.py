@@ -793,7 +793,7 @@ def separate_copy_out(wl, R, mode="auto", bcast=False):
         return copy_bytes >= (16 if widened else 32)
     mb = wl.n * copy_bytes >> 20
     if widened:
-        return copy_bytes >= 24 and mb >= 32
+        return copy_bytes >= 24 and mb >= 26
     crossing = ((52 if wl.n_workers >= 12 else 64) if bcast else 64 if kernel_match(wl).endswith("_stream")
                 else 56 if wl.n_workers <= 4 else 48)
     return copy_bytes >= crossing and mb >= 128

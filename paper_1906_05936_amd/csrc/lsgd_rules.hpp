@@ -52,12 +52,14 @@ inline bool split_serves(int64_t n, int n_workers, bool bf16, bool compile_time)
 //   up to 11 workers always (1x9: n = 1e6 10.0 / 9.9, 3e6 32.6 / 28.2, 1e7 95.2
 //   / 82.4, 2.5e7 245.9 / 233.3), up to 16 to 2^24 elements (1x14 1e7 122.0 /
 //   117.2, 2.5e7 329.0 / 336.0; unequal 2, 3, 5, 6 1e7 134.6 / 130.8, 2.5e7
-//   356.6 / 367.4);
+//   356.6 / 367.4), but not where four-unit tiles make one round that is more
+//   than half full (1x9, n = 1e6, R = 4 11.6 / 13.4, R = 8 13.8 / 14.4);
 //   more workers, where the last round fills at most half of the units (8x8:
 //   n = 2^19 26.7 / 23.2, 6e5 30 / 33.8, 2^20 44.5 / 47.7, 2^20 + 1 57.7 / 48.6,
 //   1.1e6 63.2 / 54.6, 1.3e6 70.9 / 71.6, 1.6e6 73.3 / 78.0, 2.4e6 114.7 / 120.7;
 //   16x8: 2^19 48.9 / 43.1, 1.1e6 117.8 / 104.9), in the first two rounds.
 inline bool stream_two_units(int64_t pieces, int rounds, int n_workers, int64_t n, int cus) {
+    if (pieces <= cus && pieces > cus / 2) return false;
     if (n_workers <= 16) return n_workers < 12 || n <= int64_t{1} << 24;
     return pieces <= int64_t{rounds} * cus && (pieces - 1) % cus < cus / 2;
 }
@@ -81,9 +83,9 @@ constexpr int64_t kWarmStateBytes = int64_t{128} << 20;
 //    16 for bfloat16 gradients with binary32 replicas (unequal, 297 / 275);
 //  - else the pass has a launch (2 to 3 us) and a second reading of the
 //    parameters to make good. bfloat16 gradients with binary32 replicas: from
-//    24 bytes and 32 MB of copies (apart / in the kernel, 1x4 to 4x4: n = 6e5
-//    32 B 1.04 to 1.07, 1e6 24 B 1.05 to 1.14, 32 B 0.89 to 0.97, 3e6 24 B
-//    0.83 to 0.88);
+//    24 bytes and 26 MB of copies (apart / in the kernel, 1x4 to 4x4: n = 6e5
+//    32 B 1.04 to 1.07, 48 B 0.87 to 0.93, 1e6 24 B 1.05 to 1.14, 32 B 0.89 to
+//    0.97, 3e6 24 B 0.83 to 0.88);
 //  - the others: from 48 bytes (up to 4 workers 56, stream kernels 64) and 128
 //    MB of copies (4x4 binary32: n = 3e5 48 B 1.34, 1e6 48 B 1.15, 56 B 1.13, 2e6
 //    56 B 1.00, 3e6 48 B 0.98, 40 B 0.97 to 1.00 from 2e6; 1x4 48 B 1.01 to 1.11,
@@ -100,7 +102,7 @@ inline bool copies_apart(int n_workers, int gsz, int rsz, int64_t copy_bytes, bo
     const bool widened = gsz == 2 && rsz == 4;
     if (n > kWarmStateBytes / 8) return copy_bytes >= (widened ? 16 : 32);
     const int64_t mb = n * copy_bytes >> 20;
-    if (widened) return copy_bytes >= 24 && mb >= 32;
+    if (widened) return copy_bytes >= 24 && mb >= 26;
     const int crossing = broadcast ? (n_workers >= 12 ? 52 : 64) : stream ? 64 : n_workers <= 4 ? 56 : 48;
     return copy_bytes >= crossing && mb >= 128;
 }

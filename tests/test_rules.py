@@ -76,8 +76,9 @@ APART = [
     ((16, 4, 4, 48, False, 3_000_000, False, True), True), ((4, 4, 4, 56, False, 5_000_000, False, True), True),
     ((16, 4, 4, 56, False, 12_000_000, False, True), True), ((9, 4, 4, 56, False, 12_000_000, True, True), False),
     ((4, 2, 2, 48, False, 1_000_000, False, True), False), ((8, 2, 2, 48, False, 5_000_000, False, True), True),
-    ((4, 2, 4, 32, False, 600_000, False, True), False), ((16, 2, 4, 32, False, 1_000_000, False, True), False),
-    ((16, 2, 4, 40, False, 1_000_000, False, True), True), ((10, 2, 4, 24, False, 3_000_000, False, True), True),
+    ((4, 2, 4, 32, False, 600_000, False, True), False), ((16, 2, 4, 32, False, 1_000_000, False, True), True),
+    ((16, 2, 4, 40, False, 1_000_000, False, True), True), ((10, 2, 4, 32, False, 1_000_000, False, True), True),
+    ((10, 2, 4, 24, False, 1_000_000, False, True), False), ((10, 2, 4, 24, False, 3_000_000, False, True), True),
     ((10, 2, 4, 16, False, 3_000_000, False, True), False), ((10, 2, 4, 16, False, 25_000_000, False, True), True),
     ((16, 4, 4, 32, False, 25_000_000, False, True), True), ((32, 4, 4, 32, False, 1_000_000, True, False), True),
     ((64, 4, 4, 4, False, 1_000_000, True, False), True),
@@ -94,7 +95,7 @@ def test_copies_apart(ask):
 
 
 # (elements, workers), two-unit tiles faster? (flat, 256 compute units)
-TWO_UNITS = [((25_557_032, 9), True), ((25_557_032, 14), False), ((10_000_000, 14), True), ((1 << 19, 64), True),
+TWO_UNITS = [((25_557_032, 9), True), ((1_000_000, 9), False), ((500_000, 9), True), ((1_100_000, 9), True), ((25_557_032, 14), False), ((10_000_000, 14), True), ((1 << 19, 64), True),
              ((600_000, 64), False), ((1 << 20, 64), False), (((1 << 20) + 1, 64), True), ((1_100_000, 128), True),
              ((1_600_000, 64), False), ((2_400_000, 64), False), ((25_557_032, 64), False)]
 
