@@ -7,10 +7,11 @@
 // a workgroup cover 4096, into pieces of that size too. One workgroup runs one
 // piece (a large tensor is walked exactly like the flat kernel walks a vector);
 // pieces are taken in the XCD-chunked order of the launch shape. The copy-out
-// pass and the LARS update always take the 2048-element pieces, one lane tile of
-// theirs: over pieces of 4096 a workgroup made two trips one after the other
-// (binary32, n = 2.5e7, R = N, us: copies of 8x8 plans 2383 -> 2230 for the step,
-// 10x4 LARS 1643 -> 1574).
+// pass always takes the 2048-element pieces, one lane tile of its own: over
+// pieces of 4096 a workgroup made two trips one after the other (binary32, n =
+// 2.5e7, R = N, us: 8x8 plan 2383 -> 2230, 10x4 LARS 1643 -> 1574). The LARS
+// update takes the pieces of the norms: a workgroup then reads the mean gradient
+// from the L2 cache of the XCD that wrote it.
 #include <string.h>
 
 #include <algorithm>
@@ -40,12 +41,14 @@ struct lsgd_plan {
     PieceTable small, large;   // pieces of 2048 and of 4096 elements (large.n == 0: no kernel of the plan takes them)
     int step_tile[2];          // units per lane tile of the step kernel: mean of means, paper-literal
     int lars_tile;             // of the LARS norms kernel
-    // small plans: the split kernels' pieces of at most kSplitElems elements
-    // (n_fine == 0: the plan takes the other kernels)
+    // the split kernels' pieces of at most kSplitElems elements (n_fine == 0:
+    // neither the step nor LARS takes them)
     int32_t n_fine;
     lsgd::PlanChunk* d_fine;
     lsgd::Program mean_program, literal_program;
-    bool lars_merge;      // the LARS update sums each tensor's partials itself
+    bool step_fine;       // the step runs in the split kernels
+    bool lars_fine;       // the LARS norms too
+    bool lars_merge;      // and the LARS update, which sums each tensor's partials itself
     void** d_ptrs;
     // LARS: per-tensor scratch offsets and chunk ranges, and every buffer's
     // byte range (for the workspace aliasing check)
@@ -143,14 +146,14 @@ void use_fine_pieces(const lsgd_plan* plan, PlanArgs& a, LaunchShape& ls) {
     a.xcd_chunk = ls.xcd_chunk;
 }
 
-// Replicas per workgroup of the plan's copy-out pass (as for flat steps: a
-// lane loads 32 bytes of p and stores 32 bytes per tile).
+// Replicas per workgroup of the plan's copy-out pass over full pieces (as for
+// flat steps: a lane loads 32 bytes of p and stores 32 bytes per tile).
 constexpr int kPlanCopyRKF32 = 1, kPlanCopyRKBF16 = 2;
 
 // The copy-out pass of a plan step: one workgroup per piece and replica
 // group; a lane tile covers a 2048-element piece (the usual piece size).
 template <int VEC, int RK>
-lsgd_status launch_plan_copy_out(const lsgd_plan* plan, PlanArgs& a, hipStream_t s) {
+lsgd_status launch_copy_pieces(const lsgd_plan* plan, PlanArgs& a, hipStream_t s) {
     constexpr int U = kSmallPiece / (VEC * kBlock);
     static_assert(U >= 1, "at least one unit per lane");
     const PieceTable& t = plan->small;
@@ -165,14 +168,25 @@ lsgd_status launch_plan_copy_out(const lsgd_plan* plan, PlanArgs& a, hipStream_t
     return check_launch("lsgd_step_plan (copy-out)");
 }
 
+// The copy-out pass to the a.n_replicas destinations of type a.rdt.
+lsgd_status launch_plan_copy_out(const lsgd_plan* plan, PlanArgs& a, hipStream_t s) {
+    const int rk = copy_replicas_per_group(plan->total_elems, plan->small.n);
+    if (a.rdt == static_cast<int32_t>(LSGD_BF16))
+        return rk == 1   ? launch_copy_pieces<8, kPlanCopyRKBF16>(plan, a, s)
+               : rk == 2 ? launch_copy_pieces<8, 2 * kPlanCopyRKBF16>(plan, a, s)
+                         : launch_copy_pieces<8, 4 * kPlanCopyRKBF16>(plan, a, s);
+    return rk == 1   ? launch_copy_pieces<4, kPlanCopyRKF32>(plan, a, s)
+           : rk == 2 ? launch_copy_pieces<4, 2 * kPlanCopyRKF32>(plan, a, s)
+                     : launch_copy_pieces<4, 4 * kPlanCopyRKF32>(plan, a, s);
+}
+
 // The copy passes after a plan step that wrote the first k_step replicas and,
 // with the broadcast, the first member's gradient.
 lsgd_status launch_plan_copies(const lsgd_plan* plan, PlanArgs& a, int32_t k_step, int32_t bcast_copies, hipStream_t s) {
     if (plan->n_replicas > k_step) {
         a.copy_dst = 2 + plan->n_workers + k_step;
         a.n_replicas = plan->n_replicas - k_step;
-        const lsgd_status st = plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, a, s)
-                                                      : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, a, s);
+        const lsgd_status st = launch_plan_copy_out(plan, a, s);
         if (st != LSGD_OK) return st;
     }
     if (bcast_copies > 0) {   // the first member's gradient (slot 2) to the others (slots 3 ..)
@@ -180,7 +194,7 @@ lsgd_status launch_plan_copies(const lsgd_plan* plan, PlanArgs& a, int32_t k_ste
         a.copy_dst = 3;
         a.n_replicas = bcast_copies;
         a.rdt = static_cast<int32_t>(LSGD_F32);
-        return launch_plan_copy_out<4, kPlanCopyRKF32>(plan, a, s);
+        return launch_plan_copy_out(plan, a, s);
     }
     return LSGD_OK;
 }
@@ -220,7 +234,7 @@ LarsLayout lars_layout(const lsgd_plan* plan) {
     LarsLayout l;
     l.gbar = 0;
     l.partials = round256(static_cast<size_t>(plan->gbar_floats) * sizeof(float));
-    l.trust = l.partials + round256(static_cast<size_t>(plan->n_fine ? plan->n_fine : pieces_for(plan, plan->lars_tile).n) * 2 * sizeof(double));
+    l.trust = l.partials + round256(static_cast<size_t>(plan->lars_fine ? plan->n_fine : pieces_for(plan, plan->lars_tile).n) * 2 * sizeof(double));
     l.total = l.trust + round256(static_cast<size_t>(plan->n_tensors) * sizeof(float));
     return l;
 }
@@ -300,7 +314,7 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     la.trust_coef = trust_coef;
     const hipStream_t s = static_cast<hipStream_t>(stream);
     const int rsz = plan->rdt == LSGD_BF16 ? 2 : 4;
-    if (plan->n_fine > 0) {
+    if (plan->lars_fine) {
         LarsArgs fa = la;
         LaunchShape fs;
         use_fine_pieces(plan, fa.pa, fs);
@@ -312,8 +326,7 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
             if (apart) fa.pa.n_replicas = 0;
             launch_lars_update_split(fa, fs.blocks, s);
             if ((st = check_launch("lsgd_lars_step_plan (update)")) != LSGD_OK || !apart) return st;
-            return plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, la.pa, s)
-                                          : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, la.pa, s);
+            return launch_plan_copy_out(plan, la.pa, s);
         }
     } else if (plan->small.n > 0) {
         int32_t W = plan->W, G = plan->n_groups;
@@ -329,7 +342,6 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     hipLaunchKernelGGL(lars_trust_kernel, dim3(plan->n_tensors), dim3(kBlock), 0, s, la);
     if ((st = check_launch("lsgd_lars_step_plan (trust)")) != LSGD_OK) return st;
     if (plan->small.n == 0) return LSGD_OK;
-    use_pieces(plan, plan->small, la.pa, ls);
     // the update reads and writes as lsgd_sgd_step does: the same copy-out rule
     const bool split = separate_copy_out_update(plan->n_replicas, rsz,
                                                 use_cached_state(plan->n_workers, plan->total_elems));
@@ -337,8 +349,7 @@ lsgd_status lars_step(const lsgd_plan* plan, float lr, float momentum_coef, floa
     hipLaunchKernelGGL(lars_update_kernel<2>, dim3(ls.blocks), dim3(kBlock), 0, s, la);
     if ((st = check_launch("lsgd_lars_step_plan (update)")) != LSGD_OK || !split) return st;
     la.pa.n_replicas = plan->n_replicas;
-    return plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, la.pa, s)
-                                  : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, la.pa, s);
+    return launch_plan_copy_out(plan, la.pa, s);
 }
 
 }  // namespace lsgd
@@ -379,17 +390,22 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     const int32_t W = equal ? n_workers / n_groups : 0;
     const bool as_one = one_group_form(W, n_groups, false);
     const int32_t tW = as_one ? n_workers : W, tG = as_one ? 1 : n_groups;
-    int64_t total_elems = 0, four_unit_pieces = 0;
+    int64_t total_elems = 0, with_elems = 0, small_pieces = 0, four_unit_pieces = 0;
     for (int32_t t = 0; t < n_tensors; ++t) {
         if (numel[t] < 0) return fail(LSGD_ERR_SIZE, "numel[%d]=%lld < 0", t, static_cast<long long>(numel[t]));
         total_elems += numel[t];
+        with_elems += numel[t] > 0;
+        small_pieces += (numel[t] + kSmallPiece - 1) / kSmallPiece;
         four_unit_pieces += (numel[t] + kLargePiece - 1) / kLargePiece;
     }
     auto step_tile = [&](int32_t w, int32_t g) {
         const PlanPick k = bf16 ? pick_plan<uint16_t>(w, g) : pick_plan<float>(w, g);
         return k.kernel ? k.tile
-                        : stream_tile(bf16, !bf16 && stream_two_units(four_unit_pieces, 4, n_workers, total_elems, device_cus()));
+                        : stream_tile(bf16, !bf16 && plan_two_units(four_unit_pieces, small_pieces, n_workers, total_elems,
+                                                                    device_cus()));
     };
+    const PlanShape shape{total_elems, with_elems, small_pieces, n_workers, bf16,
+                          (bf16 ? pick_plan<uint16_t>(tW, tG).kernel : pick_plan<float>(tW, tG).kernel) != nullptr};
     const int mean_tile = step_tile(tW, tG), literal_tile = as_one ? step_tile(W, n_groups) : mean_tile;
     const int lars_tile = W == 0 ? mean_tile : bf16 ? lars_norms_tile<uint16_t>(tW, tG) : lars_norms_tile<float>(tW, tG);
     const bool need_large = large_pieces(mean_tile, bf16) || large_pieces(literal_tile, bf16) || large_pieces(lars_tile, bf16);
@@ -440,26 +456,31 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     if (equal) build_program(n_groups, gstart.data(), false, mean_program);
     build_program(n_groups, gstart.data(), true, literal_program);
     std::vector<PlanChunk> fine;
-    bool lars_merge = false;
-    if (use_split_plan(total_elems, n_workers, gdt == LSGD_BF16,
-                       std::max(mean_program.n_batches, literal_program.n_batches))) {
-        lars_merge = true;
+    bool step_fine = false, lars_fine = false, lars_merge = true;
+    // An empty tensor's trust ratio has no update workgroup that could write it.
+    for (int32_t t = 0; t < n_tensors; ++t)
+        if (numel[t] == 0 ||
+            (numel[t] / kSplitVec + kSplitUnits - 1) / kSplitUnits + (numel[t] % kSplitVec != 0) > kLarsMergeChunks)
+            lars_merge = false;
+    if (split_plan_allowed(std::max(mean_program.n_batches, literal_program.n_batches))) {
+        step_fine = split_serves_plan(shape);
+        lars_fine = split_serves_lars(shape, lars_merge);
+    }
+    if (step_fine || lars_fine) {
         for (int32_t t = 0; t < n_tensors; ++t) {
-            tensor_chunks[t] = static_cast<int32_t>(fine.size());
+            if (lars_fine) tensor_chunks[t] = static_cast<int32_t>(fine.size());
             const int64_t whole = numel[t] / kSplitVec * kSplitVec;
             for (int64_t s0 = 0; s0 < whole; s0 += kSplitElems)
                 fine.push_back(PlanChunk{params[t], t, 0, s0, std::min<int64_t>(kSplitElems, whole - s0)});
             if (whole < numel[t]) fine.push_back(PlanChunk{params[t], t, 0, whole, numel[t] - whole});
-            const size_t mine = fine.size() - static_cast<size_t>(tensor_chunks[t]);
-            // an empty tensor's trust ratio has no update workgroup that could write it
-            if (mine == 0 || mine > static_cast<size_t>(kLarsMergeChunks)) lars_merge = false;
         }
+        if (fine.empty()) step_fine = lars_fine = false;
     }
-    if (chunks.size() > 0x7fffffff) return fail(LSGD_ERR_SIZE, "too many pieces");
+    if (chunks.size() > 0x7fffffff || fine.size() > 0x7fffffff) return fail(LSGD_ERR_SIZE, "too many pieces");
     // one workgroup per tensor in the LARS trust kernel, in one launch
     if (n_tensors > kMaxGridBlocks)
         return fail(LSGD_ERR_SIZE, "more than %lld tensors", static_cast<long long>(kMaxGridBlocks));
-    tensor_chunks[n_tensors] = static_cast<int32_t>(!fine.empty()                  ? fine.size()
+    tensor_chunks[n_tensors] = static_cast<int32_t>(lars_fine                       ? fine.size()
                                                     : large_pieces(lars_tile, bf16) ? large_chunks.size()
                                                                                     : chunks.size());
 
@@ -486,6 +507,8 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     p->n_fine = static_cast<int32_t>(fine.size());
     p->mean_program = mean_program;
     p->literal_program = literal_program;
+    p->step_fine = step_fine;
+    p->lars_fine = lars_fine;
     p->lars_merge = lars_merge;
     p->gbar_floats = gbar_floats;
     p->ranges = new std::vector<Range>(ranges);
@@ -561,7 +584,7 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     LaunchShape ls;
     PlanArgs a = plan_args(plan, pieces_for(plan, tile), Hyper{lr, momentum_coef, weight_decay}, lr_device, ls);
     a.literal = literal ? 1 : 0;
-    if (plan->n_fine > 0) {
+    if (plan->step_fine) {
         const Program& pr = literal ? plan->literal_program : plan->mean_program;
         const int rsz = plan->rdt == LSGD_BF16 ? 2 : 4, gsz = plan->gdt == LSGD_BF16 ? 2 : 4;
         const int32_t bcast_copies = bcast ? plan->n_workers - 1 : 0;
@@ -622,8 +645,7 @@ LSGD_API lsgd_status lsgd_plan_copy_out(const lsgd_plan* plan, void* stream) {
     LaunchShape ls;
     PlanArgs a = plan_args(plan, plan->small, Hyper{0.f, 0.f, 0.f}, nullptr, ls);
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    return plan->rdt == LSGD_BF16 ? launch_plan_copy_out<8, kPlanCopyRKBF16>(plan, a, s)
-                                  : launch_plan_copy_out<4, kPlanCopyRKF32>(plan, a, s);
+    return launch_plan_copy_out(plan, a, s);
 }
 
 LSGD_API lsgd_status lsgd_step_plan(const lsgd_plan* plan, float lr, float momentum_coef,

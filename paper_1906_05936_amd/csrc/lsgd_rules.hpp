@@ -43,6 +43,74 @@ inline bool split_serves(int64_t n, int n_workers, bool bf16, bool compile_time)
     return n <= (n_workers > 16 ? int64_t{3} << 17 : int64_t{1} << 18);
 }
 
+// ------------------------------------------------------ split kernels, plans
+//
+struct PlanShape {
+    int64_t elems, tensors;    // elements of all tensors, tensors that have any
+    int64_t pieces;            // pieces of 2048 elements
+    int n_workers;
+    bool bf16, compile_time;   // a compile-time kernel serves the step
+};
+
+// Plans too small to fill the chip (split / the others; 30 tensors unless
+// noted): up to 2^19 elements (n = 2^19: binary32 1x4 4.1 / 5.2, 4x4 8.2 / 10.1,
+// 8x8 25.9 / 32.5), bfloat16 up to 2^20 (4x4 10.2 / 16.1, 8x8 33.9 / 56.1),
+// binary32 up to 2^20 where the tensors hold 2^15 elements or fewer on average
+// (n = 1e6: 60 tensors 0.92 of the others for 4x4, 0.95 for 8x8, 3 to 30 tensors
+// 1.03 to 1.12).
+inline bool plan_fits_split(const PlanShape& s) {
+    return s.elems <= int64_t{1} << 19 || (s.elems <= int64_t{1} << 20 && (s.bf16 || s.elems <= s.tensors << 15));
+}
+
+// Plans of any size whose tensors leave most of a workgroup's piece empty. One
+// piece of 2048 elements costs the other kernels the same however short it is
+// (4096-element tiles twice that), a split piece holds 256. R = 0, split / the
+// others: binary32 without compile-time kernel 10x4 20000 tensors of 200 204 /
+// 2196, 3000 of 700 80 / 306, 8x8 3000 of 700 122 / 141 with two-unit tiles;
+// 1x4 20000 of 200 28 / 74, 5000 of 1000 29 / 43, but 4x4 66 / 61 and 70 / 70;
+// bfloat16 4x4 20000 of 200 52 / 204, 8x8 2000 of 900 110 / 123.
+inline bool plan_of_small_tensors(const PlanShape& s) {
+    if (!s.bf16 && s.compile_time && s.n_workers > 8) return false;
+    const int64_t held = s.pieces * 2048;
+    return s.bf16 || s.compile_time ? 2 * s.elems < held : 5 * s.elems < 2 * held;
+}
+
+// Whether a plan's step takes the split kernels. A single tensor with a
+// compile-time kernel goes by the rule of the flat steps.
+inline bool split_serves_plan(const PlanShape& s) {
+    if (!plan_fits_split(s)) return plan_of_small_tensors(s);
+    return s.tensors > 1 || !s.compile_time || split_serves(s.elems, s.n_workers, s.bf16, true);
+}
+
+// Whether LARS steps take the split kernels; `merged`: every workgroup of the
+// update can sum its tensor's partials (else they need a launch of their own).
+// Split / the others, us:
+//   merged, binary32 of up to 16 workers to 2^19 elements (1x4, 60 tensors, n =
+//   2^19 0.81 of the others, 1e6 16.4 / 13.5), the rest to 2^20;
+//   not merged, only bfloat16 of more than 8 workers and binary32 of more than
+//   16 (n = 2^19: binary32 1x4 one tensor 16.8 / 12.4, 4x4 26.5 / 19.8; 8x8
+//   35.2 / 51.3; bfloat16 3 tensors 1x4 12.0 / 11.1, 4x4 14.6 / 17.1, 8x8 26.5
+//   / 44.8);
+//   binary32 beyond 2^19 elements not where the tensors are few and large (8x8,
+//   n = 1e6, 3 tensors 63.6 / 58.7, 16 tensors 63.8 / 76.5).
+inline bool split_serves_lars(const PlanShape& s, bool merged) {
+    if (!merged && s.n_workers <= (s.bf16 ? 8 : 16)) return false;
+    if (s.elems <= int64_t{1} << 19) return true;
+    return s.elems <= int64_t{1} << 20 && (s.bf16 || (s.n_workers > 16 && s.elems <= s.tensors << 18));
+}
+
+// ------------------------------------------------------ copy pass of a plan
+//
+// Replicas that a workgroup of the copy pass writes per piece of 2048 elements
+// (times 2 for bfloat16 replicas): 1, or more where the pieces are mostly empty
+// (`elems` in `pieces` pieces), so that fewer workgroups each read their tables.
+// Binary32, whole step, 1 / 2 / 4, us: 4x4 LARS, 3000 tensors of 700, R = 16 113
+// / 88 / 75; 1x4 LARS, 20000 of 200, R = 4 194 / 152 / 129; 8x8, 300 of 2500, R =
+// 64 98 / 76 / 78; 8x8, 60 tensors, 1.2e7 elements 1049 / 1095 / 1110.
+inline int copy_replicas_per_group(int64_t elems, int64_t pieces) {
+    return elems < pieces * 1024 ? 4 : elems < pieces * 1600 ? 2 : 1;
+}
+
 // ------------------------------------------- binary32 stream kernels, units
 //
 // Whether a binary32 step in a stream kernel takes lane tiles of two units and
@@ -62,6 +130,14 @@ inline bool stream_two_units(int64_t pieces, int rounds, int n_workers, int64_t 
     if (pieces <= cus && pieces > cus / 2) return false;
     if (n_workers <= 16) return n_workers < 12 || n <= int64_t{1} << 24;
     return pieces <= int64_t{rounds} * cus && (pieces - 1) % cus < cus / 2;
+}
+
+// The same for a plan of `pieces` pieces of 4096 elements and `small` of 2048:
+// two units also where half pieces are at most half as many again, so that
+// four-unit tiles would be half empty (10x4, 1000 tensors of 5000 204 / 174,
+// 3000 of 1500 325 / 156).
+inline bool plan_two_units(int64_t pieces, int64_t small, int n_workers, int64_t n, int cus) {
+    return 2 * small <= 3 * pieces || stream_two_units(pieces, 4, n_workers, n, cus);
 }
 
 // ------------------------------------------------ copies in a pass of their own

@@ -11,12 +11,6 @@ namespace {
 // waves share a compute unit.
 constexpr int kSplitMaxBatches = 64;
 
-// Plans of up to these sizes take the split kernels (30 tensors, split / the
-// others, us: n = 3e5 binary32 4x4 5.6 / 8.1; n = 1e6 8x8 50.8 / 62.2, bfloat16
-// 4x4 9.6 / 14.0, 8x8 31.4 / 51.2; n = 3e6 binary32 8x8 169 / 136).
-constexpr int64_t kSplitPlanMax = int64_t{1} << 20;
-constexpr int64_t kSplitPlanMaxFewF32 = int64_t{1} << 19;    // binary32, at most 16 workers
-
 // A caller that sets more than one pass per workgroup gets the kernels the
 // setting is about.
 bool split_allowed(int n_batches) { return n_batches <= kSplitMaxBatches && launch_passes_per_block() == 1; }
@@ -27,9 +21,7 @@ bool use_split_flat(int64_t n, int32_t n_workers, bool bf16, bool compile_time, 
     return split_serves(n, n_workers, bf16, compile_time) && split_allowed(n_batches);
 }
 
-bool use_split_plan(int64_t n, int32_t n_workers, bool bf16, int n_batches) {
-    return n <= (!bf16 && n_workers <= 16 ? kSplitPlanMaxFewF32 : kSplitPlanMax) && split_allowed(n_batches);
-}
+bool split_plan_allowed(int n_batches) { return split_allowed(n_batches); }
 
 // A copy pass of its own costs a launch (2.5 to 4 us): up to 64 MB of copies
 // the split kernel writes them itself. Measured apart / in the kernel, us:

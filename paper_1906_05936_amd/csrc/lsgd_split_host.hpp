@@ -16,10 +16,11 @@ constexpr int kSplitUnits = 64;        // lanes with elements per workgroup
 constexpr int kSplitElems = kSplitVec * kSplitUnits;
 constexpr int kLarsMergeChunks = 512;  // most pieces of a tensor whose partials every update workgroup sums itself
 
-// Whether a flat step (a plan step) of n elements takes the split kernels;
-// `compile_time`: a compile-time kernel serves the layout.
+// Whether a flat step of n elements takes the split kernels; `compile_time`: a
+// compile-time kernel serves the layout.
 bool use_split_flat(int64_t n, int32_t n_workers, bool bf16, bool compile_time, int n_batches);
-bool use_split_plan(int64_t n, int32_t n_workers, bool bf16, int n_batches);
+// Whether a plan may have split pieces (its rules: split_serves_plan, plan_fits_split).
+bool split_plan_allowed(int n_batches);
 // Whether a split step writes its copies in passes of their own, given what
 // the rule for the other kernels says (`apart`).
 bool separate_copy_out_small(int64_t n, int64_t copy_bytes, bool apart);

@@ -25,6 +25,12 @@ int main() {
         if (rule == "split") r = split_serves(v[0], (int)v[1], v[2], v[3]);
         else if (rule == "apart") r = copies_apart((int)v[0], (int)v[1], (int)v[2], v[3], v[4], v[5], v[6], v[7]);
         else if (rule == "two") r = stream_two_units(v[0], (int)v[1], (int)v[2], v[3], (int)v[4]);
+        else if (rule == "plan") {
+            r = split_serves_plan(PlanShape{v[0], v[1], v[2], (int)v[3], v[4] != 0, v[5] != 0});
+        } else if (rule == "lars") {
+            r = split_serves_lars(PlanShape{v[0], v[1], v[2], (int)v[3], v[4] != 0, v[5] != 0}, v[6]);
+        } else if (rule == "copies") r = copy_replicas_per_group(v[0], v[1]) == (int)v[2];
+        else if (rule == "plantwo") r = plan_two_units(v[0], v[1], (int)v[2], v[3], (int)v[4]);
         else return 1;
         std::printf("%d\n", (int)r);
     }
@@ -103,3 +109,59 @@ TWO_UNITS = [((25_557_032, 9), True), ((1_000_000, 9), False), ((500_000, 9), Tr
 def test_two_unit_tiles(ask):
     got = ask("two", [(-(-n // 4096), 2, N, n, 256) for (n, N), _ in TWO_UNITS])
     assert got == [want for _, want in TWO_UNITS], [r for (r, w), g in zip(TWO_UNITS, got) if w != g]
+
+
+def shape(sizes, workers, bf16, compile_time):
+    return (sum(sizes), sum(s > 0 for s in sizes), sum(-(-s // 2048) for s in sizes), workers, bf16, compile_time)
+
+
+GROWING = [30_000 * k // 20 + 7 for k in range(1, 31)]   # 30 tensors of 7e5 elements in all
+# plan and its step, split kernel faster?
+PLAN_SPLIT = [
+    (shape([200] * 20_000, 40, F32, False), True), (shape([700] * 3_000, 64, F32, False), True),
+    (shape([900] * 2_000, 64, F32, False), False), (shape([1_500] * 1_000, 64, F32, False), False),
+    (shape([200] * 20_000, 4, F32, True), True), (shape([1_000] * 5_000, 4, F32, True), True),
+    (shape([200] * 20_000, 16, F32, True), False), (shape([200] * 20_000, 16, BF16, True), True),
+    (shape([900] * 2_000, 64, BF16, True), True), (shape([2_048] * 2_000, 64, BF16, True), False),
+    (shape(GROWING, 16, F32, True), True), (shape(GROWING, 16, BF16, True), True),
+    (shape([333_333] * 3, 16, F32, True), False), (shape([333_333] * 3, 64, F32, False), False),
+    (shape([333_333] * 3, 16, BF16, True), True), (shape([16_667] * 60, 16, F32, True), True),
+    (shape([175_000] * 3, 4, F32, True), False), (shape([170_000] * 3, 4, F32, True), True),
+    (shape([524_288], 16, F32, True), False), (shape([65_536], 4, F32, True), False), (shape([65_536], 16, F32, True), True),
+    (shape([262_144], 16, BF16, True), False), (shape([131_069], 16, BF16, True), True),
+    (shape([100_000, 100_000], 4, F32, True), True), (shape([519_000, 5_000], 16, BF16, True), True),
+    (shape([524_288, 0], 16, F32, True), False), (shape([524_288], 9, BF16, False), True),
+]
+
+
+def test_plan_split_kernels(ask):
+    got = ask("plan", [r for r, _ in PLAN_SPLIT])
+    assert got == [want for _, want in PLAN_SPLIT], [r for (r, w), g in zip(PLAN_SPLIT, got) if w != g]
+
+
+def test_plan_two_unit_tiles(ask):
+    rows = [([1_500] * 1_000, 64, True), ([5_000] * 1_000, 40, True), ([20_000] * 600, 64, False), ([700_000] * 3, 64, True),
+            ([1_000_000] * 3, 64, False), ([400_000] * 30, 9, True)]
+    got = ask("plantwo", [(sum(-(-x // 4096) for x in s), sum(-(-x // 2048) for x in s), n, sum(s), 256) for s, n, _ in rows])
+    assert got == [want for _, _, want in rows]
+
+
+# plan, merged and its LARS step, split kernels faster?
+LARS_SPLIT = [
+    (shape([524_288], 4, F32, True), False, False), (shape([524_288], 64, F32, True), False, True),
+    (shape([8_738] * 60, 4, F32, True), True, True), (shape([16_667] * 60, 4, F32, True), True, False),
+    (shape([16_667] * 60, 64, F32, True), True, True), (shape([333_333] * 3, 64, F32, True), False, False),
+    (shape([62_500] * 16, 64, F32, True), True, True), (shape([174_762] * 3, 4, BF16, True), False, False),
+    (shape([174_762] * 3, 16, BF16, True), False, True), (shape([300_000] * 3, 64, BF16, True), False, True),
+    (shape([131_072], 4, F32, True), True, True), (shape([700] * 3_000, 64, BF16, True), True, False),
+]
+
+
+def test_lars_split_kernels(ask):
+    got = ask("lars", [r + (merged,) for r, merged, _ in LARS_SPLIT])
+    assert got == [want for _, _, want in LARS_SPLIT], [r for (r, _, w), g in zip(LARS_SPLIT, got) if w != g]
+
+
+def test_copy_pass_of_small_pieces(ask):
+    rows = [([700] * 3_000, 4), ([200] * 20_000, 4), ([2_500] * 300, 2), ([200_000] * 60, 1), ([2_048] * 8, 1)]
+    assert all(ask("copies", [(sum(x), sum(-(-n // 2048) for n in x), rk) for x, rk in rows]))
