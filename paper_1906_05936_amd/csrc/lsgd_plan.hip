@@ -390,22 +390,21 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     const int32_t W = equal ? n_workers / n_groups : 0;
     const bool as_one = one_group_form(W, n_groups, false);
     const int32_t tW = as_one ? n_workers : W, tG = as_one ? 1 : n_groups;
-    int64_t total_elems = 0, with_elems = 0, small_pieces = 0, four_unit_pieces = 0;
+    int64_t total_elems = 0, with_elems = 0, small_pieces = 0, four_unit_pieces = 0, ragged = 0;
     for (int32_t t = 0; t < n_tensors; ++t) {
         if (numel[t] < 0) return fail(LSGD_ERR_SIZE, "numel[%d]=%lld < 0", t, static_cast<long long>(numel[t]));
         total_elems += numel[t];
         with_elems += numel[t] > 0;
+        ragged += numel[t] % (bf16 ? Unit<uint16_t>::VEC : Unit<float>::VEC) != 0;
         small_pieces += (numel[t] + kSmallPiece - 1) / kSmallPiece;
         four_unit_pieces += (numel[t] + kLargePiece - 1) / kLargePiece;
     }
+    const PlanShape shape{total_elems, with_elems, small_pieces, ragged, n_workers, bf16,
+                          (bf16 ? pick_plan<uint16_t>(tW, tG).kernel : pick_plan<float>(tW, tG).kernel) != nullptr};
     auto step_tile = [&](int32_t w, int32_t g) {
         const PlanPick k = bf16 ? pick_plan<uint16_t>(w, g) : pick_plan<float>(w, g);
-        return k.kernel ? k.tile
-                        : stream_tile(bf16, !bf16 && plan_two_units(four_unit_pieces, small_pieces, n_workers, total_elems,
-                                                                    device_cus()));
+        return k.kernel ? k.tile : stream_tile(bf16, !bf16 && plan_two_units(shape, four_unit_pieces, device_cus()));
     };
-    const PlanShape shape{total_elems, with_elems, small_pieces, n_workers, bf16,
-                          (bf16 ? pick_plan<uint16_t>(tW, tG).kernel : pick_plan<float>(tW, tG).kernel) != nullptr};
     const int mean_tile = step_tile(tW, tG), literal_tile = as_one ? step_tile(W, n_groups) : mean_tile;
     const int lars_tile = W == 0 ? mean_tile : bf16 ? lars_norms_tile<uint16_t>(tW, tG) : lars_norms_tile<float>(tW, tG);
     const bool need_large = large_pieces(mean_tile, bf16) || large_pieces(literal_tile, bf16) || large_pieces(lars_tile, bf16);

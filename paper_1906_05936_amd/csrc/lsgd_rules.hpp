@@ -48,6 +48,7 @@ inline bool split_serves(int64_t n, int n_workers, bool bf16, bool compile_time)
 struct PlanShape {
     int64_t elems, tensors;    // elements of all tensors, tensors that have any
     int64_t pieces;            // pieces of 2048 elements
+    int64_t ragged;            // tensors that end in part of a gradient unit
     int n_workers;
     bool bf16, compile_time;   // a compile-time kernel serves the step
 };
@@ -67,36 +68,61 @@ inline bool plan_fits_split(const PlanShape& s) {
 // (4096-element tiles twice that), a split piece holds 256. R = 0, split / the
 // others: binary32 without compile-time kernel 10x4 20000 tensors of 200 204 /
 // 2196, 3000 of 700 80 / 306, 8x8 3000 of 700 122 / 141 with two-unit tiles;
-// 1x4 20000 of 200 28 / 74, 5000 of 1000 29 / 43, but 4x4 66 / 61 and 70 / 70;
+// 1x4 20000 of 200 28 / 74, 5000 of 1000 29 / 43, but 2x4 2000 of 900 20.0 /
+// 16.4, 4x4 66 / 61 and 70 / 70;
 // bfloat16 4x4 20000 of 200 52 / 204, 8x8 2000 of 900 110 / 123.
 inline bool plan_of_small_tensors(const PlanShape& s) {
-    if (!s.bf16 && s.compile_time && s.n_workers > 8) return false;
+    if (!s.bf16 && s.compile_time && s.n_workers > 4) return false;
     const int64_t held = s.pieces * 2048;
     return s.bf16 || s.compile_time ? 2 * s.elems < held : 5 * s.elems < 2 * held;
 }
 
-// Whether a plan's step takes the split kernels. A single tensor with a
-// compile-time kernel goes by the rule of the flat steps.
+// Whether a plan's step takes the split kernels. Where no tensor is ragged a
+// compile-time kernel serves few workers better (split / compile-time over the
+// time before either, sizes that are multiples of 64):
+//   bfloat16 up to 16 workers always (1x4 10 tensors n = 65536 0.93 / 0.80, 60
+//   tensors 2^19 0.97 / 0.90; 4x4 10 to 160 tensors 0.25 to 1.15, split the
+//   slower by 0 to 0.2), more only beyond 3 * 2^16 (8x8 131072 0.53 to 0.76 / 0.64
+//   to 0.98, 262144 0.48 to 1.23 / 0.39 to 0.98);
+//   binary32 up to 3 workers (1x2 n = 2^19, 10 tensors 1.06 / 0.97) unless the
+//   tensors are small (1e6, 160 tensors 0.93 / 1.24), up to 7 with at most 3
+//   tensors (1x4 131072 1.00 to 1.03 / 0.97, 10 tensors 2^19 0.82 / 0.98).
+// A single tensor goes by the rule of the flat steps.
 inline bool split_serves_plan(const PlanShape& s) {
     if (!plan_fits_split(s)) return plan_of_small_tensors(s);
-    return s.tensors > 1 || !s.compile_time || split_serves(s.elems, s.n_workers, s.bf16, true);
+    if (!s.compile_time) return true;
+    if (s.ragged == 0) {
+        if (s.bf16) return s.n_workers > 16 && s.elems <= int64_t{3} << 16;
+        if (s.n_workers <= 3) return s.elems > int64_t{1} << 19 && s.elems <= s.tensors << 13;
+        if (s.n_workers < 8 && s.tensors <= 3) return false;
+    }
+    return s.tensors > 1 || split_serves(s.elems, s.n_workers, s.bf16, true);
 }
 
 // Whether LARS steps take the split kernels; `merged`: every workgroup of the
 // update can sum its tensor's partials (else they need a launch of their own).
-// Split / the others, us:
-//   merged, binary32 of up to 16 workers to 2^19 elements (1x4, 60 tensors, n =
-//   2^19 0.81 of the others, 1e6 16.4 / 13.5), the rest to 2^20;
-//   not merged, only bfloat16 of more than 8 workers and binary32 of more than
-//   16 (n = 2^19: binary32 1x4 one tensor 16.8 / 12.4, 4x4 26.5 / 19.8; 8x8
-//   35.2 / 51.3; bfloat16 3 tensors 1x4 12.0 / 11.1, 4x4 14.6 / 17.1, 8x8 26.5
-//   / 44.8);
-//   binary32 beyond 2^19 elements not where the tensors are few and large (8x8,
-//   n = 1e6, 3 tensors 63.6 / 58.7, 16 tensors 63.8 / 76.5).
+// Split / the others, us, or of the time before either where noted:
+//   merged, binary32 of up to 16 workers to 2^19 elements, or 2^20 where the
+//   tensors are small (1x4 2^19, 60 tensors 0.81 of the others, 1e6 16.4 / 13.5,
+//   160 tensors 1.03 / 1.14 of the time before);
+//   bfloat16 with a compile-time kernel and no ragged tensor, of the time before:
+//   merged to 9 * 2^16 (4x4 2^18 0.79 / 0.85, 60 tensors 2^19 0.87 / 0.87 and,
+//   R = 16, 14.1 / 18.1 us, 1e6 1.11 / 1.00), else more than 16 workers to 3 * 2^16
+//   (8x8 131072 0.50 to 0.75 / 0.68 to 0.98, 3 tensors 262144 1.27 / 0.99);
+//   not merged, bfloat16 of 9 to 16 workers to 2^19 (1x4 3 tensors 2^19 12.0 /
+//   11.1, 4x4 14.6 / 17.1, 1x9 13.5 / 14.1, 1e6 21.5 / 18.0) and more than 16
+//   workers (8x8 2^19 26.5 / 44.8; binary32 35.2 / 51.3, but 1x4, one tensor, 16.8
+//   / 12.4, 4x4 26.5 / 19.8);
+//   binary32 of more than 16 workers beyond 2^19 not where the tensors are few and
+//   large (8x8, n = 1e6, 3 tensors 63.6 / 58.7, 16 tensors 63.8 / 76.5).
 inline bool split_serves_lars(const PlanShape& s, bool merged) {
-    if (!merged && s.n_workers <= (s.bf16 ? 8 : 16)) return false;
-    if (s.elems <= int64_t{1} << 19) return true;
-    return s.elems <= int64_t{1} << 20 && (s.bf16 || (s.n_workers > 16 && s.elems <= s.tensors << 18));
+    const int64_t n = s.elems;
+    const bool many = s.n_workers > 16;
+    if (n > int64_t{1} << 20) return false;
+    if (s.bf16 && s.compile_time && s.ragged == 0)
+        return merged ? n <= int64_t{9} << 16 : many && n <= int64_t{3} << 16;
+    if (!merged && !many && !(s.bf16 && s.n_workers > 8 && n <= int64_t{1} << 19)) return false;
+    return s.bf16 || n <= int64_t{1} << 19 || n <= s.tensors << (many ? 18 : 13);
 }
 
 // ------------------------------------------------------ copy pass of a plan
@@ -132,12 +158,14 @@ inline bool stream_two_units(int64_t pieces, int rounds, int n_workers, int64_t 
     return pieces <= int64_t{rounds} * cus && (pieces - 1) % cus < cus / 2;
 }
 
-// The same for a plan of `pieces` pieces of 4096 elements and `small` of 2048:
-// two units also where half pieces are at most half as many again, so that
-// four-unit tiles would be half empty (10x4, 1000 tensors of 5000 204 / 174,
-// 3000 of 1500 325 / 156).
-inline bool plan_two_units(int64_t pieces, int64_t small, int n_workers, int64_t n, int cus) {
-    return 2 * small <= 3 * pieces || stream_two_units(pieces, 4, n_workers, n, cus);
+// The same for a plan of `pieces` pieces of 4096 elements: two units also where
+// the pieces of 2048 (s.pieces) are at most half as many again, so that four-unit
+// tiles would be half empty (10x4, 1000 tensors of 5000 204 / 174, 3000 of 1500
+// 325 / 156), and where more than a fifth of the pieces end in a ragged element,
+// a tile of its own after the other (8x8: 1000 ragged tensors of 3000 217 / 154,
+// whole ones 133 / 152, 300 of 10000 161 / 146, 1000 of 9000 486 / 438).
+inline bool plan_two_units(const PlanShape& s, int64_t pieces, int cus) {
+    return 2 * s.pieces <= 3 * pieces || 5 * s.ragged > pieces || stream_two_units(pieces, 4, s.n_workers, s.elems, cus);
 }
 
 // ------------------------------------------------ copies in a pass of their own

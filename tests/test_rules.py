@@ -26,11 +26,11 @@ int main() {
         else if (rule == "apart") r = copies_apart((int)v[0], (int)v[1], (int)v[2], v[3], v[4], v[5], v[6], v[7]);
         else if (rule == "two") r = stream_two_units(v[0], (int)v[1], (int)v[2], v[3], (int)v[4]);
         else if (rule == "plan") {
-            r = split_serves_plan(PlanShape{v[0], v[1], v[2], (int)v[3], v[4] != 0, v[5] != 0});
+            r = split_serves_plan(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0});
         } else if (rule == "lars") {
-            r = split_serves_lars(PlanShape{v[0], v[1], v[2], (int)v[3], v[4] != 0, v[5] != 0}, v[6]);
+            r = split_serves_lars(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0}, v[7]);
         } else if (rule == "copies") r = copy_replicas_per_group(v[0], v[1]) == (int)v[2];
-        else if (rule == "plantwo") r = plan_two_units(v[0], v[1], (int)v[2], v[3], (int)v[4]);
+        else if (rule == "plantwo") r = plan_two_units(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0}, v[7], 256);
         else return 1;
         std::printf("%d\n", (int)r);
     }
@@ -112,7 +112,9 @@ def test_two_unit_tiles(ask):
 
 
 def shape(sizes, workers, bf16, compile_time):
-    return (sum(sizes), sum(s > 0 for s in sizes), sum(-(-s // 2048) for s in sizes), workers, bf16, compile_time)
+    unit = 8 if bf16 else 4
+    return (sum(sizes), sum(s > 0 for s in sizes), sum(-(-s // 2048) for s in sizes), sum(s % unit > 0 for s in sizes), workers,
+            bf16, compile_time)
 
 
 GROWING = [30_000 * k // 20 + 7 for k in range(1, 31)]   # 30 tensors of 7e5 elements in all
@@ -126,10 +128,12 @@ PLAN_SPLIT = [
     (shape(GROWING, 16, F32, True), True), (shape(GROWING, 16, BF16, True), True),
     (shape([333_333] * 3, 16, F32, True), False), (shape([333_333] * 3, 64, F32, False), False),
     (shape([333_333] * 3, 16, BF16, True), True), (shape([16_667] * 60, 16, F32, True), True),
-    (shape([175_000] * 3, 4, F32, True), False), (shape([170_000] * 3, 4, F32, True), True),
+    (shape([175_000] * 3, 4, F32, True), False), (shape([170_001] * 3, 4, F32, True), True), (shape([170_000] * 3, 4, F32, True), False),
     (shape([524_288], 16, F32, True), False), (shape([65_536], 4, F32, True), False), (shape([65_536], 16, F32, True), True),
     (shape([262_144], 16, BF16, True), False), (shape([131_069], 16, BF16, True), True),
-    (shape([100_000, 100_000], 4, F32, True), True), (shape([519_000, 5_000], 16, BF16, True), True),
+    (shape([100_001, 100_001], 4, F32, True), True), (shape([100_000, 100_000], 4, F32, True), False), (shape([519_001, 5_000], 16, BF16, True), True),
+    (shape([17_472] * 60, 4, F32, True), True), (shape([6_400] * 160, 2, F32, True), True), (shape([52_480] * 10, 2, F32, True), False),
+    (shape([8_704] * 60, 4, BF16, True), False), (shape([8_703] * 60, 4, BF16, True), True), (shape([13_120] * 10, 64, BF16, True), True),
     (shape([524_288, 0], 16, F32, True), False), (shape([524_288], 9, BF16, False), True),
 ]
 
@@ -141,8 +145,9 @@ def test_plan_split_kernels(ask):
 
 def test_plan_two_unit_tiles(ask):
     rows = [([1_500] * 1_000, 64, True), ([5_000] * 1_000, 40, True), ([20_000] * 600, 64, False), ([700_000] * 3, 64, True),
-            ([1_000_000] * 3, 64, False), ([400_000] * 30, 9, True)]
-    got = ask("plantwo", [(sum(-(-x // 4096) for x in s), sum(-(-x // 2048) for x in s), n, sum(s), 256) for s, n, _ in rows])
+            ([1_000_000] * 3, 64, False), ([400_000] * 30, 9, True), ([3_000] * 1_000, 64, False), ([3_001] * 1_000, 64, True),
+            ([9_001] * 1_000, 64, True), ([9_000] * 1_000, 64, False)]
+    got = ask("plantwo", [shape(s, n, F32, False) + (sum(-(-x // 4096) for x in s),) for s, n, _ in rows])
     assert got == [want for _, _, want in rows]
 
 
@@ -152,7 +157,10 @@ LARS_SPLIT = [
     (shape([8_738] * 60, 4, F32, True), True, True), (shape([16_667] * 60, 4, F32, True), True, False),
     (shape([16_667] * 60, 64, F32, True), True, True), (shape([333_333] * 3, 64, F32, True), False, False),
     (shape([62_500] * 16, 64, F32, True), True, True), (shape([174_762] * 3, 4, BF16, True), False, False),
-    (shape([174_762] * 3, 16, BF16, True), False, True), (shape([300_000] * 3, 64, BF16, True), False, True),
+    (shape([174_762] * 3, 16, BF16, True), False, True), (shape([300_001] * 3, 64, BF16, True), False, True), (shape([300_000] * 3, 64, BF16, True), False, False),
+    (shape([8_704] * 60, 16, BF16, True), True, True), (shape([16_704] * 60, 16, BF16, True), True, False),
+    (shape([1_000_001], 9, BF16, False), False, False), (shape([500_001], 9, BF16, False), False, True),
+    (shape([6_272] * 160, 4, F32, True), True, True), (shape([131_072], 16, BF16, True), False, False),
     (shape([131_072], 4, F32, True), True, True), (shape([700] * 3_000, 64, BF16, True), True, False),
 ]
 
