@@ -24,12 +24,14 @@ struct MeanPick {
 };
 
 // The mean of K inputs: compile-time K of 1 to 8, 12, 16; else none
-// (mean_stream).
+// (mean_stream). Two units per lane, one for bfloat16 except for the widening
+// of many single workers (64 groups of one, n = 1e6, one unit / two 86 / 78 us,
+// 1e7 915 / 838, 3e6 401 / 416; 9 groups of one 1e6 20.9 / 22.6; 4x4 9.6 / 9.8).
 template <typename GT>
-MeanPick pick_mean(int K) {
+MeanPick pick_mean(int K, int runs) {
     constexpr int U = sizeof(GT) == 4 ? 2 : 1;   // up to 16 inputs: the unrolled form
     switch (K) {
-        case 1: return MeanPick{mean_kernel_ct<GT, 1, U>, U};
+        case 1: return runs >= 32 ? MeanPick{mean_kernel_ct<GT, 1, 2>, 2} : MeanPick{mean_kernel_ct<GT, 1, U>, U};
         case 2: return MeanPick{mean_kernel_ct<GT, 2, U>, U};
         case 3: return MeanPick{mean_kernel_ct<GT, 3, U>, U};
         case 4: return MeanPick{mean_kernel_ct<GT, 4, U>, U};
@@ -45,11 +47,12 @@ MeanPick pick_mean(int K) {
 
 // Means of `runs` runs of K consecutive inputs of a.in to a.out.
 lsgd_status launch_means(MeanArgs& a, int K, int runs, bool bf16, void* stream, const char* what) {
-    const MeanPick k = bf16 ? pick_mean<uint16_t>(K) : pick_mean<float>(K);
+    const MeanPick k = bf16 ? pick_mean<uint16_t>(K, runs) : pick_mean<float>(K, runs);
     const int64_t vec = bf16 ? Unit<uint16_t>::VEC : Unit<float>::VEC;
     a.W = K;
+    const int tile = mean_stream_tile(K, a.n, bf16);
     LaunchShape ls = k.kernel ? launch_shape((a.n + vec - 1) / vec, k.tile)
-                              : launch_shape(stream_units(a.n, bf16, stream_tile(bf16)), stream_tile(bf16));
+                              : launch_shape(stream_units(a.n, bf16, tile), tile);
     if (static_cast<int64_t>(ls.blocks) * runs > kMaxGridBlocks) {   // the kernels stride over the rest
         ls.blocks = static_cast<unsigned>(kMaxGridBlocks / runs);
         ls.xcd_chunk = 0;

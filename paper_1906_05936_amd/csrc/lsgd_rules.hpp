@@ -211,4 +211,22 @@ inline bool copies_apart(int n_workers, int gsz, int rsz, int64_t copy_bytes, bo
     return copy_bytes >= crossing && mb >= 128;
 }
 
+// ---------------------------------------------------- means, any input count
+//
+// The form of the binary32 stream kernel for means of `inputs` inputs of n
+// elements. One unit per lane, nothing issued ahead, up to 2^19 elements (n =
+// 1e5, four units / one, us: 9 inputs 9.1 / 5.3, 64 24.8 / 11.2, 128 43.1 /
+// 20.8; 3e5, 128: 46.3 / 27.6); one unit, the next batch issued ahead, beyond
+// (9 inputs 1e6 11.7 / 11.0, 1e7 95 / 81, 20 inputs 2.5e7 386 / 379, 64 1057 /
+// 992); but four units for 32 inputs or more up to 2^22 (32 inputs 1e6 22.4 /
+// 23.7, 3e6 64.9 / 71.4; 64 1e6 41.9 / 44.5).
+enum class MeanForm { kOne, kOneAhead, kFourAhead };
+inline MeanForm mean_stream_form(int inputs, int64_t n) {
+    if (n <= int64_t{1} << 19) return MeanForm::kOne;
+    return inputs >= 32 && n <= int64_t{1} << 22 ? MeanForm::kFourAhead : MeanForm::kOneAhead;
+}
+inline int mean_stream_tile(int inputs, int64_t n, bool bf16) {
+    return !bf16 && mean_stream_form(inputs, n) == MeanForm::kFourAhead ? 4 : 1;
+}
+
 }  // namespace lsgd

@@ -1,4 +1,5 @@
 // Launches of the stream step kernels.
+#include "lsgd_rules.hpp"
 #include "lsgd_stream.hpp"
 
 namespace lsgd {
@@ -46,8 +47,12 @@ void launch_mean_stream(const MeanArgs& a, const Program& pr, bool bf16, dim3 bl
     MeanProgArgs ma;
     ma.a = a;
     ma.pr = pr;
-    const auto k = bf16 ? mean_stream<uint16_t> : mean_stream<float>;
-    hipLaunchKernelGGL(k, blocks, dim3(kBlock), stack_bytes(pr, 16), s, ma);
+    const MeanForm form = mean_stream_form(a.W, a.n);
+    const auto k = bf16                           ? mean_stream<uint16_t, 1, false>
+                   : form == MeanForm::kOne       ? mean_stream<float, 1, false>
+                   : form == MeanForm::kOneAhead ? mean_stream<float, 1, true>
+                                                  : mean_stream<float, 4, true>;
+    hipLaunchKernelGGL(k, blocks, dim3(kBlock), stack_bytes(pr, mean_stream_tile(a.W, a.n, bf16) * (bf16 ? 8 : 4)), s, ma);
 }
 
 int64_t stream_units(int64_t n, bool bf16, int tile) {

@@ -181,10 +181,12 @@ struct MeanSrc {
     __device__ const void* grad(int k) const { return a.in[first + k]; }
 };
 
-template <typename GT>
+// U units per lane, kAhead as for stream_mean: mean_stream_form's choice for
+// binary32; one unit and nothing ahead for bfloat16 (9 inputs, n = 1e5, two units
+// / one 7.5 / 5.4 us, 1e7 57.9 / 53.7; 64 inputs 1e5 16.8 / 11.2).
+template <typename GT, int U, bool kAhead>
 __global__ __launch_bounds__(kBlock) void mean_stream(MeanProgArgs ma) {
     extern __shared__ f32x4 stream_lds[];
-    constexpr int U = stream_tile(sizeof(GT) == 2);
     constexpr int VEC = Unit<GT>::VEC;
     constexpr int T = U * VEC;
     const MeanArgs& a = ma.a;
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(kBlock) void mean_stream(MeanProgArgs ma) {
         for (uint32_t i = 0; i < a.upl && base + i < tiles; ++i) {
             const Tile<U> t = tile_at<U, VEC>(0, a.n, base + i);
             float g[T];
-            stream_mean<GT, U, sizeof(GT) == 4>(s, ma.pr, t, stream_lds, g);
+            stream_mean<GT, U, kAhead>(s, ma.pr, t, stream_lds, g);
             if (t.tail) {
                 if (t.own[0]) gstore_ptr<float>(out)[t.e[0]] = g[0];
                 continue;

@@ -31,6 +31,7 @@ int main() {
             r = split_serves_lars(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0}, v[7]);
         } else if (rule == "copies") r = copy_replicas_per_group(v[0], v[1]) == (int)v[2];
         else if (rule == "plantwo") r = plan_two_units(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0}, v[7], 256);
+        else if (rule == "mean") r = mean_stream_form((int)v[0], v[1]) == (MeanForm)v[2];
         else return 1;
         std::printf("%d\n", (int)r);
     }
@@ -173,3 +174,10 @@ def test_lars_split_kernels(ask):
 def test_copy_pass_of_small_pieces(ask):
     rows = [([700] * 3_000, 4), ([200] * 20_000, 4), ([2_500] * 300, 2), ([200_000] * 60, 1), ([2_048] * 8, 1)]
     assert all(ask("copies", [(sum(x), sum(-(-n // 2048) for n in x), rk) for x, rk in rows]))
+
+
+def test_mean_forms(ask):
+    one, ahead, four = 0, 1, 2
+    rows = [(9, 100_000, one), (128, 300_000, one), (9, 1_000_000, ahead), (20, 25_000_000, ahead), (64, 1_000_000, four),
+            (32, 3_000_000, four), (64, 25_000_000, ahead)]
+    assert all(ask("mean", rows))
