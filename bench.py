@@ -829,12 +829,9 @@ def library_ranges(n):
     return list(zip(edges[:-1], edges[1:]))
 
 
-def ct_grouping(W, G, f32=None, listed=False):
-    """Whether the library has a compile-time step kernel for G groups of W
-    (f32: for that gradient type, else for either); listed: whether its pickers
-    know the grouping at all."""
-    if f32 is None and not listed:
-        return ct_grouping(W, G, True) or ct_grouping(W, G, False)
+def ct_grouping(W, G, f32=False, listed=False):
+    """Whether the library has a compile-time step kernel for G groups of W and
+    that gradient type; listed: whether its pickers know the grouping at all."""
     pow2 = (1, 2, 4, 8, 16, 32, 64, 128)
     if W * G > 128 or (W == 1 and G not in pow2):
         return False

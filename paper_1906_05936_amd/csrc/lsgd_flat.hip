@@ -272,7 +272,6 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
     a.n = n;
     a.h = Hyper{lr, momentum_coef, weight_decay};
     a.n_workers = n_workers;
-    a.n_groups = n_groups;
     a.n_replicas = n_replicas;
     a.rdt = static_cast<int32_t>(rdt);
     a.lr_ptr = o.lr_device;
@@ -290,7 +289,7 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
             if (gstart[j + 1] - gstart[j] != gstart[1] - gstart[0]) W = 0;
     const bool cached = use_cached_state(n_workers, n);
     // a compile-time kernel for (W, G): power-of-two group counts, then 3, 5,
-    // 6, 7 and 12 (lsgd_np2.hpp)
+    // 6 and 7 (lsgd_np2.hpp)
     auto pick_ct = [&](int32_t w, int32_t g) {
         FlatPick p = gdt == LSGD_BF16 ? pick_flat<uint16_t>(w, g, cached) : pick_flat<float>(w, g, cached);
         if (!p.kernel && np2_group_count(g)) {
@@ -333,8 +332,6 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
         }
     }
 
-    a.n_groups = G;
-    a.W = W;
     const int64_t vec = gdt == LSGD_BF16 ? Unit<uint16_t>::VEC : Unit<float>::VEC;
     const bool any_layout = !k.kernel;
     if (any_layout) {

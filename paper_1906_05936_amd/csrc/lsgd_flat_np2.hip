@@ -1,4 +1,4 @@
-// Compile-time flat step kernels for group counts 3, 5, 6, 7 and 12.
+// Compile-time flat step kernels for group counts 3, 5, 6 and 7.
 #include "lsgd_host.hpp"
 #include "lsgd_kernels.hpp"
 #include "lsgd_np2.hpp"
@@ -49,7 +49,6 @@ FlatKernel np2_flat_g(int W, int G, bool cached) {
         case 5: return np2_flat_w<GT, 5>(W, cached);
         case 6: return np2_flat_w<GT, 6>(W, cached);
         case 7: return np2_flat_w<GT, 7>(W, cached);
-        case 12: return np2_flat_w<GT, 12>(W, cached);
     }
     return nullptr;
 }

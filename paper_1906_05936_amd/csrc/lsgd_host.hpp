@@ -97,7 +97,7 @@ int32_t launch_passes_per_block();
 bool separate_copy_out_bytes(int32_t n_workers, size_t gsz, size_t rsz, int64_t copy_bytes, bool broadcast, int64_t n,
                              bool stream);
 // Group counts other than powers of two that have compile-time kernels too
-// (lsgd_np2.hpp).
+// (lsgd_np2.hpp; 12: the LARS norms only).
 inline bool np2_group_count(int G) { return G == 3 || G == 5 || G == 6 || G == 7 || G == 12; }
 
 // One worker per group in a count that is no power of two, under the mean of
@@ -136,8 +136,6 @@ LaunchShape pad_for_xcd_chunk(int64_t blocks, int64_t block_bytes);
 
 // Compute units of the current device (cached per device).
 int device_cus();
-
-inline bool is_pow2_le16(int x) { return x == 1 || x == 2 || x == 4 || x == 8 || x == 16; }
 
 // lsgd_lars_step_plan with its scratch at `workspace` (workspace_bytes long);
 // `library_workspace`: the scratch is the library's own per-device array

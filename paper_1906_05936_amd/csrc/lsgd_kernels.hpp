@@ -1,12 +1,15 @@
 // Device code of liblsgd: the Layered SGD aggregation and update for gfx950.
 //
 // Every step is elementwise along the parameter vector, so the kernels stream
-// HBM: each lane owns one 16-byte "unit" of the gradient layout (4 binary32 or
-// 8 bfloat16 elements), loads all N worker units of it with 128-bit nontemporal
-// loads, reduces them in registers in the fixed pairwise order, applies the
-// update and writes parameters, momentum and replicas with 128-bit stores.
-// No element is touched by two lanes, so there are no atomics, no LDS and no
-// cross-lane reductions: a lane's result depends only on its own inputs.
+// HBM: in the kernels here a lane owns one or more 16-byte "units" of the
+// gradient layout (4 binary32 or 8 bfloat16 elements), loads all N worker units
+// of each with 128-bit nontemporal loads, reduces them in registers in the fixed
+// pairwise order, applies the update and writes parameters, momentum and replicas
+// with 128-bit stores. No element is touched by two lanes, so they need no
+// atomics, no LDS and no cross-lane reductions. (The stream kernels,
+// lsgd_stream.hpp, keep a lane's partial sums in LDS; the split kernels,
+// lsgd_split.hpp, divide a unit's members over waves; the LARS norms, in
+// lsgd_plan_kernels.hpp, sum squares over a workgroup.)
 //
 // Rounding contract (matches the header): binary32, one rounding per written
 // operation, no contraction into fused multiply-add.
@@ -265,25 +268,12 @@ __device__ __forceinline__ void store_replica(void* r, int rdt, int64_t e0, int 
     }
 }
 
-// One 16-byte gradient unit as raw bits (4 binary32 or 8 bfloat16 values), so
-// that a batch of loads in flight costs four registers each whatever the
-// dtype. TAIL units read cnt elements and leave the rest zero.
-template <typename GT, bool TAIL>
-__device__ __forceinline__ u32x4 load_raw(const void* g, int64_t e0, int cnt) {
-    const GT* p = static_cast<const GT*>(g) + e0;
-    if constexpr (!TAIL) {
-        return __builtin_nontemporal_load(gload_ptr<u32x4>(p));
-    } else {
-        constexpr int VEC = Unit<GT>::VEC;
-        uint32_t h[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            if constexpr (sizeof(GT) == 4) h[v] = v < cnt ? gload_ptr<uint32_t>(p)[v] : 0u;
-            else h[v] = v < cnt ? static_cast<uint32_t>(gload_ptr<uint16_t>(p)[v]) : 0u;
-        }
-        if constexpr (sizeof(GT) == 4) return u32x4{h[0], h[1], h[2], h[3]};
-        else return u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-    }
+// One whole 16-byte gradient unit as raw bits (4 binary32 or 8 bfloat16
+// values), so that a batch of loads in flight costs four registers each whatever
+// the dtype.
+template <typename GT>
+__device__ __forceinline__ u32x4 load_raw(const void* g, int64_t e0) {
+    return __builtin_nontemporal_load(gload_ptr<u32x4>(static_cast<const GT*>(g) + e0));
 }
 
 // Raw unit bits -> binary32 values (bfloat16 widening is exact).
@@ -325,39 +315,35 @@ __device__ __forceinline__ void pw_tree(const Leaf& leaf, float (&out)[VEC]) {
 // the left: exactly PW(x[0..k)) with the largest-power-of-two split.
 // Every slot is updated by a select, never by a conditional store, so that the
 // compiler cannot merge the per-level stores into one variable-index store
-// (which would move the slots to scratch memory). `levels` (uniform, <= LEVELS)
-// bounds the levels a push visits: pushes beyond 2^levels - 1 terms are not
-// supported.
+// (which would move the slots to scratch memory). At most 2^LEVELS - 1 pushes.
 template <int VEC, int LEVELS>
 struct PwAcc {
     float slot[LEVELS][VEC];
     uint32_t count = 0;
 
-    __device__ __forceinline__ void push(float (&x)[VEC], int levels = LEVELS) {
+    __device__ __forceinline__ void push(float (&x)[VEC]) {
         bool carrying = true;
 #pragma unroll
         for (int l = 0; l < LEVELS; ++l) {
-            if (l < levels) {
-                const bool full = (count >> l) & 1u;
-                const bool merge = carrying && full;
-                const bool park = carrying && !full;
+            const bool full = (count >> l) & 1u;
+            const bool merge = carrying && full;
+            const bool park = carrying && !full;
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float merged = slot[l][v] + x[v];
-                    slot[l][v] = park ? x[v] : slot[l][v];
-                    x[v] = merge ? merged : x[v];
-                }
-                carrying = merge;
+            for (int v = 0; v < VEC; ++v) {
+                const float merged = slot[l][v] + x[v];
+                slot[l][v] = park ? x[v] : slot[l][v];
+                x[v] = merge ? merged : x[v];
             }
+            carrying = merge;
         }
         ++count;
     }
 
-    __device__ __forceinline__ void result(float (&out)[VEC], int levels = LEVELS) const {
+    __device__ __forceinline__ void result(float (&out)[VEC]) const {
         bool have = false;
 #pragma unroll
         for (int l = 0; l < LEVELS; ++l) {
-            if (l < levels && ((count >> l) & 1u)) {
+            if ((count >> l) & 1u) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) out[v] = have ? slot[l][v] + out[v] : slot[l][v];
                 have = true;
@@ -404,7 +390,7 @@ struct StepArgs {
     const float* gbar;  // lsgd_sgd_step only
     int64_t n;
     Hyper h;
-    int32_t n_workers, n_groups, W;
+    int32_t n_workers;
     int32_t n_replicas, rdt;
     uint32_t xcd_chunk, upl;
     const float* lr_ptr;   // non-null: the learning rate is read here when the kernel runs
@@ -632,7 +618,7 @@ __device__ __forceinline__ void mean_tile_ct(const Src& s, const int64_t (&e0)[U
     constexpr int T = U * VEC;
     const bool lit = s.literal() != 0;
     // Divisions by powers of two are the exact multiplications by 1/W, 1/N or
-    // 1/G; the others (W = 3, 5, 6 or 7; G = 3, 5, 6, 7 or 12; N of either)
+    // 1/G; the others (W = 3, 5, 6 or 7; G = 3, 5, 6, 7 or (LARS norms) 12; N of either)
     // are divisions. The mean of means divides each group's sum by W and the
     // total by G; the literal reduction each group's sum by N, the total by 1.
     constexpr bool kPow2W = (W & (W - 1)) == 0;
@@ -705,7 +691,6 @@ struct FlatSrcT {
     __device__ int rdt() const { return a.rdt; }
     __device__ Hyper hyper() const { return h; }
     __device__ int bcast_grad() const { return a.bcast_grad; }
-    __device__ int n_workers() const { return a.n_workers; }
     __device__ int literal() const { return a.literal; }
     __device__ int cached_state() const { return CACHED; }
 };

@@ -91,7 +91,7 @@ template <typename GT>
 PlanPick pick_plan(int W, int G, bool cached = false) {
     const PlanKernel k = pick_plan_pow2<GT>(W, G, cached);
     if (k) return PlanPick{k, tile_units<GT>(W * G)};
-    if (np2_group_count(G)) {   // group counts 3, 5, 6, 7 and 12 (lsgd_np2.hpp)
+    if (np2_group_count(G)) {   // group counts 3, 5, 6 and 7 (lsgd_np2.hpp)
         const Np2PlanPick q = pick_plan_np2(W, G, cached, sizeof(GT) == 2);
         if (q.kernel) return PlanPick{q.kernel, q.tile};
     }
@@ -126,8 +126,6 @@ PlanArgs plan_args(const lsgd_plan* plan, const PieceTable& t, Hyper h, const fl
     a.stride = plan->stride;
     a.n_workers = plan->n_workers;
     a.cached_state = use_cached_state(plan->n_workers, plan->total_elems) ? 1 : 0;   // read by the LARS update
-    a.n_groups = plan->n_groups;
-    a.W = plan->W;
     a.n_replicas = plan->n_replicas;
     a.rdt = static_cast<int32_t>(plan->rdt);
     a.h = h;
@@ -611,8 +609,6 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     if (one_group_form(W, G, literal)) {
         W = plan->n_workers;
         G = 1;
-        a.W = W;
-        a.n_groups = 1;
     }
     if (W > 0)
         k = plan->gdt == LSGD_BF16 ? pick_plan<uint16_t>(W, G, cached).kernel : pick_plan<float>(W, G, cached).kernel;

@@ -1,6 +1,6 @@
 // Device code of liblsgd's multi-tensor plans: the fused step over a list of
 // tensors in one launch (piece and pointer tables built by lsgd_plan_create),
-// its copy-out pass, and the LARS step. Included by lsgd_plan.hip only.
+// its copy-out pass, and the LARS step.
 #pragma once
 
 #include "lsgd_kernels.hpp"
@@ -28,7 +28,7 @@ struct PlanChunk {
 struct PlanArgs {
     const PlanChunk* chunks;      // [n_chunks]
     void* const* ptrs;
-    int32_t stride, n_workers, n_groups, W;
+    int32_t stride, n_workers;
     int32_t n_replicas, rdt;
     int32_t n_chunks;
     uint32_t xcd_chunk;
@@ -57,7 +57,6 @@ struct PlanSrcT {
     __device__ int rdt() const { return a.rdt; }
     __device__ Hyper hyper() const { return h; }
     __device__ int bcast_grad() const { return a.bcast_grad; }
-    __device__ int n_workers() const { return a.n_workers; }
     __device__ int literal() const { return a.literal; }
     __device__ int cached_state() const { return CACHED < 0 ? a.cached_state : CACHED; }
 };

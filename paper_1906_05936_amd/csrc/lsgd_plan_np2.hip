@@ -1,5 +1,5 @@
-// Compile-time plan step and LARS norm kernels for group counts 3, 5, 6, 7
-// and 12.
+// Compile-time plan step kernels for group counts 3, 5, 6 and 7, LARS norm
+// kernels for these and, binary32, 12.
 #include "lsgd_host.hpp"
 #include "lsgd_np2.hpp"
 #include "lsgd_plan_kernels.hpp"
@@ -78,7 +78,6 @@ PlanKernel np2_plan_g(int W, int G, bool cached) {
         case 5: return np2_plan_w<GT, 5>(W, cached);
         case 6: return np2_plan_w<GT, 6>(W, cached);
         case 7: return np2_plan_w<GT, 7>(W, cached);
-        case 12: return np2_plan_w<GT, 12>(W, cached);
     }
     return nullptr;
 }
@@ -90,7 +89,8 @@ Np2LarsKernel np2_lars_g(int W, int G) {
         case 5: return np2_lars_w<GT, 5>(W);
         case 6: return np2_lars_w<GT, 6>(W);
         case 7: return np2_lars_w<GT, 7>(W);
-        case 12: return np2_lars_w<GT, 12>(W);
+        case 12:
+            if constexpr (sizeof(GT) == 4) return np2_lars_w<GT, 12>(W);   // bfloat16: the stream kernel
     }
     return nullptr;
 }

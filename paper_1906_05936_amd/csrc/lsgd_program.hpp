@@ -25,6 +25,9 @@ namespace lsgd {
 constexpr int kBatchMembers = 8;
 constexpr int kMaxBatches = 128;   // every batch holds at least one of the kMaxWorkers members
 constexpr int kMaxLevels = 16;
+// Most partial sums the stack form ever holds: 63 single workers leave six, and
+// a group of 57 to 65 members after them three more.
+constexpr int kMaxStack = 9;
 
 // One batch, and what the stack form of the program does with its sum:
 // `pre` additions of a popped partial sum (earlier partial + sum), a division

@@ -11,6 +11,8 @@ size_t stack_bytes(const Program& pr, int floats) {
     return static_cast<size_t>(pr.stack_depth) * floats * sizeof(float) * kBlock;
 }
 
+static_assert(kMaxStack * 16 * sizeof(float) * kBlock <= 160 * 1024, "the deepest stack fits a compute unit's LDS");
+
 template <int CACHED>
 auto pick_flat_stream(bool bf16, int tile) {
     if (bf16) return step_flat_stream<uint16_t, 2, CACHED>;

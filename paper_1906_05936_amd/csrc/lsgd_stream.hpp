@@ -113,7 +113,7 @@ __device__ __forceinline__ void stream_mean(const Src& s, const Program& pr, con
                 if (k < count) {
                     const void* g = s.grad(first + k);
 #pragma unroll
-                    for (int q = 0; q < U; ++q) r[k][q] = load_raw<GT, false>(g, t.e[q], VEC);
+                    for (int q = 0; q < U; ++q) r[k][q] = load_raw<GT>(g, t.e[q]);
                 }
             }
         } else {

@@ -12,6 +12,8 @@ import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1906_05936_amd", "csrc")
 
+MAX_STACK = 9   # kMaxStack: a lane's partial sums in LDS, 16 KB a level
+
 DUMP = r"""
 #include <cstdio>
 #include <vector>
@@ -109,7 +111,7 @@ def check(sizes, literal, line):
             x = (stack.pop(), x)
         stack.append(x)
         most = max(most, len(stack))
-    assert len(stack) == 1 and most == depth
+    assert len(stack) == 1 and most == depth <= MAX_STACK
     assert over(stack[0], total) == want
 
 
@@ -146,3 +148,14 @@ def test_random_partitions(dump):
         layouts.append((sizes, True))
     for (sizes, lit), line in zip(layouts, dump(layouts)):
         check(sizes, lit, line)
+
+
+def test_deepest_stacks(dump):
+    """A group of every size after every count of single workers that fits (the
+    partial sums of the groups before wait while a group's own pile up)."""
+    layouts = [([1] * k + [s], True) for k in range(1, 128) for s in range(1, 129 - k)]
+    depths = [int(line.split()[2]) for line in dump(layouts)]
+    assert max(depths) == MAX_STACK
+    for (sizes, lit), d, line in zip(layouts, depths, dump(layouts)):
+        if d == MAX_STACK:
+            check(sizes, lit, line)

@@ -1,6 +1,7 @@
 """The per-grouping wave-cap tables of the compile-time kernels: every entry
-names a grouping that has a compile-time kernel (an entry for any other
-would never be used), no grouping is listed twice in a table, and every cap
+names a grouping that has a compile-time kernel for the table's gradient type (an
+entry for any other would never be used; the bfloat16 LARS norms have one where
+the step has), no grouping is listed twice in a table, and every cap
 is 2 or 3 waves per SIMD. The tables are read from the kernel headers."""
 import os
 import re
@@ -31,6 +32,6 @@ def test_entries_name_compile_time_groupings():
             assert len(keys) == len(set(keys)), name
             for w, g, cap in entries:
                 assert cap in (2, 3), (name, w, g, cap)
-                assert bench.ct_grouping(w, g), (name, w, g)
+                assert bench.ct_grouping(w, g, f32=name.endswith("F32")), (name, w, g)
             n += len(entries)
     assert n >= 100
