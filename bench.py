@@ -382,7 +382,8 @@ def time_steps_cold(setup, steps, warmup, flush, fn=None, repeats=REPEATS):
 
 def whole_step_label(wl, R, setup, args):
     """The kernels of one step, for a roofline line taken over the whole step."""
-    names = [kernel_match(wl, setup.reduction, args.lars)]
+    rsz = 2 if wl.replica_dtype == "bf16" else 4
+    names = [kernel_match(wl, setup.reduction, args.lars, R * rsz)]
     if args.lars:
         names += ["lars_trust_kernel", "lars_update_kernel"]
     if (lars_separate_copy_out(wl, R, args.copy_out) if args.lars
@@ -783,7 +784,7 @@ def separate_copy_out(wl, R, mode="auto", bcast=False):
     if mode == "separate":
         return True
     cached = wl.n_workers <= 16 and 8 * wl.n <= (288 << 20)   # parameters and momentum through the caches
-    if kernel_match(wl).endswith("_split") and wl.n * copy_bytes <= (64 << 20):
+    if kernel_match(wl, copy_bytes=copy_bytes).endswith("_split") and wl.n * copy_bytes <= (64 << 20):
         return False
     # copies_apart of lsgd_rules.hpp
     if wl.n_workers * wl.grad_bytes >= 256 or not cached:
@@ -842,23 +843,30 @@ def ct_grouping(W, G, f32=False, listed=False):
     return G in (3, 5, 6, 7, 12) and (W <= 8 or W in (12, 16, 32))
 
 
-def kernel_match(wl, reduction=None, lars=False):
+def kernel_match(wl, reduction=None, lars=False, copy_bytes=0):
+    """The step kernel's name, for labels and profile lookups; copy_bytes: bytes
+    of copies per element."""
     G, W = wl.groups, wl.workers_per_group
-    few = wl.n_workers <= 16
+    N = wl.n_workers
+    few = N <= 16
     f32 = wl.grad_dtype == "f32"
     ct = not wl.group_sizes and ct_grouping(W, G, f32)
     if (not ct and not wl.group_sizes and W == 1 and G & (G - 1) and reduction != "literal"):
         ct = ct_grouping(G, 1, f32)   # one worker per group: run as one group of all workers
-    if wl.tensor_sizes:   # the library's size rules for its split kernels (lsgd_split.hip, lsgd_rules.hpp)
-        split = wl.n <= (1 << 19 if f32 and few else 1 << 20)
+    whole = wl.n % (4 if f32 else 8) == 0
+    if wl.tensor_sizes:   # split_serves_plan goes by the tensors too; no plan of large tensors beyond 2^20 elements
+        split = wl.n <= 1 << 19
     elif ct and few:   # split_serves of lsgd_rules.hpp
-        whole = wl.n % (4 if f32 else 8) == 0
-        split = wl.n <= 1 << 18 and (wl.n_workers >= (8 if whole else 2) and wl.n > (1024 if wl.n_workers > 8 else 4096)
-                                     if f32 else not whole)
+        if not f32:
+            split = not whole or copy_bytes > 32 and N > 4
+        else:
+            split = copy_bytes > 32 or (wl.n > 1024 and N >= (5 if copy_bytes else 8) if whole
+                                        else N >= (4 if copy_bytes else 2))
+        split = split and wl.n <= 1 << 18
     elif f32:
-        split = wl.n <= (1 << 18 if few else 3 << 17)
+        split = wl.n <= (1 << 18) + (0 if few else (1 << 23) // N)
     else:
-        split = wl.n <= (3 << 16 if ct and wl.n % 8 == 0 and wl.n_workers > 64 else 1 << 18)
+        split = wl.n <= (3 << 16 if ct and whole and N > 64 else 1 << 18)
     if lars:
         ct = ct or f32 and (W > 1 or G & (G - 1) == 0) and ct_grouping(W, G, listed=True)
         return "lars_norms_split" if split else "lars_norms_kernel" if ct else "lars_norms_stream"

@@ -314,9 +314,9 @@ LSGD_API lsgd_status lsgd_step_ex(float* params, float* momentum, void* const* g
         }
         build_program(n_groups, gstart.data(), literal, pr);
     };
-    if (use_split_flat(n, n_workers, gdt == LSGD_BF16, k.kernel != nullptr, 1)) {
+    if (use_split_flat(n, n_workers, gdt == LSGD_BF16, k.kernel != nullptr, copy_bytes, 1)) {
         build();
-        if (use_split_flat(n, n_workers, gdt == LSGD_BF16, k.kernel != nullptr, pr.n_batches)) {
+        if (use_split_flat(n, n_workers, gdt == LSGD_BF16, k.kernel != nullptr, copy_bytes, pr.n_batches)) {
             const bool apart = separate_copy_out_small(
                 n, copy_bytes,
                 separate_copy_out_bytes(n_workers, dtype_size(gdt), dtype_size(rdt), copy_bytes, bcast, n, false));

@@ -46,7 +46,7 @@ struct lsgd_plan {
     int32_t n_fine;
     lsgd::PlanChunk* d_fine;
     lsgd::Program mean_program, literal_program;
-    bool step_fine;       // the step runs in the split kernels
+    bool step_fine[2];    // the step runs in the split kernels: mean of means, paper-literal
     bool lars_fine;       // the LARS norms too
     bool lars_merge;      // and the LARS update, which sums each tensor's partials itself
     void** d_ptrs;
@@ -397,8 +397,12 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
         small_pieces += (numel[t] + kSmallPiece - 1) / kSmallPiece;
         four_unit_pieces += (numel[t] + kLargePiece - 1) / kLargePiece;
     }
-    const PlanShape shape{total_elems, with_elems, small_pieces, ragged, n_workers, bf16,
-                          (bf16 ? pick_plan<uint16_t>(tW, tG).kernel : pick_plan<float>(tW, tG).kernel) != nullptr};
+    auto plan_shape = [&](int32_t w, int32_t g) {
+        return PlanShape{total_elems, with_elems, small_pieces, ragged, n_workers, bf16,
+                         (bf16 ? pick_plan<uint16_t>(w, g).kernel : pick_plan<float>(w, g).kernel) != nullptr,
+                         (g & (g - 1)) == 0, static_cast<int64_t>(n_replicas * rsz)};
+    };
+    const PlanShape shape = plan_shape(tW, tG);
     auto step_tile = [&](int32_t w, int32_t g) {
         const PlanPick k = bf16 ? pick_plan<uint16_t>(w, g) : pick_plan<float>(w, g);
         return k.kernel ? k.tile : stream_tile(bf16, !bf16 && plan_two_units(shape, four_unit_pieces, device_cus()));
@@ -453,17 +457,18 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     if (equal) build_program(n_groups, gstart.data(), false, mean_program);
     build_program(n_groups, gstart.data(), true, literal_program);
     std::vector<PlanChunk> fine;
-    bool step_fine = false, lars_fine = false, lars_merge = true;
+    bool step_fine[2] = {false, false}, lars_fine = false, lars_merge = true;
     // An empty tensor's trust ratio has no update workgroup that could write it.
     for (int32_t t = 0; t < n_tensors; ++t)
         if (numel[t] == 0 ||
             (numel[t] / kSplitVec + kSplitUnits - 1) / kSplitUnits + (numel[t] % kSplitVec != 0) > kLarsMergeChunks)
             lars_merge = false;
     if (split_plan_allowed(std::max(mean_program.n_batches, literal_program.n_batches))) {
-        step_fine = split_serves_plan(shape);
+        step_fine[0] = split_serves_plan(shape);
+        step_fine[1] = as_one ? split_serves_plan(plan_shape(W, n_groups)) : step_fine[0];
         lars_fine = split_serves_lars(shape, lars_merge);
     }
-    if (step_fine || lars_fine) {
+    if (step_fine[0] || step_fine[1] || lars_fine) {
         for (int32_t t = 0; t < n_tensors; ++t) {
             if (lars_fine) tensor_chunks[t] = static_cast<int32_t>(fine.size());
             const int64_t whole = numel[t] / kSplitVec * kSplitVec;
@@ -471,7 +476,7 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
                 fine.push_back(PlanChunk{params[t], t, 0, s0, std::min<int64_t>(kSplitElems, whole - s0)});
             if (whole < numel[t]) fine.push_back(PlanChunk{params[t], t, 0, whole, numel[t] - whole});
         }
-        if (fine.empty()) step_fine = lars_fine = false;
+        if (fine.empty()) step_fine[0] = step_fine[1] = lars_fine = false;
     }
     if (chunks.size() > 0x7fffffff || fine.size() > 0x7fffffff) return fail(LSGD_ERR_SIZE, "too many pieces");
     // one workgroup per tensor in the LARS trust kernel, in one launch
@@ -504,7 +509,8 @@ LSGD_API lsgd_status lsgd_plan_create(lsgd_plan** out, int32_t n_tensors, const 
     p->n_fine = static_cast<int32_t>(fine.size());
     p->mean_program = mean_program;
     p->literal_program = literal_program;
-    p->step_fine = step_fine;
+    p->step_fine[0] = step_fine[0];
+    p->step_fine[1] = step_fine[1];
     p->lars_fine = lars_fine;
     p->lars_merge = lars_merge;
     p->gbar_floats = gbar_floats;
@@ -581,7 +587,7 @@ LSGD_API lsgd_status lsgd_step_plan_ex(const lsgd_plan* plan, float lr, float mo
     LaunchShape ls;
     PlanArgs a = plan_args(plan, pieces_for(plan, tile), Hyper{lr, momentum_coef, weight_decay}, lr_device, ls);
     a.literal = literal ? 1 : 0;
-    if (plan->step_fine) {
+    if (plan->step_fine[literal]) {
         const Program& pr = literal ? plan->literal_program : plan->mean_program;
         const int rsz = plan->rdt == LSGD_BF16 ? 2 : 4, gsz = plan->gdt == LSGD_BF16 ? 2 : 4;
         const int32_t bcast_copies = bcast ? plan->n_workers - 1 : 0;

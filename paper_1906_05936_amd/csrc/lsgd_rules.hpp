@@ -17,30 +17,42 @@ namespace lsgd {
 // and a ragged end is a second pass of one lane. `compile_time`: a
 // compile-time kernel serves the layout.
 //
-// Up to 16 workers with a compile-time kernel, split / compile-time:
-//   whole vectors: bfloat16 never (1x4 n = 65536 2.6 / 2.4, 4x4 131072 3.6 /
-//   3.1, 2x5 100000 4.1 / 3.2); binary32 from 8 workers (1x4 65536 2.9 / 2.4,
-//   131072 3.2 / 2.8; 2x4 40000 0.76, 262144 0.88 of it; 4x4 65536 3.4 / 4.6),
-//   beyond 4096 elements (4x4: 1024; n = 1000: 1.2 of it, every layout);
-//   ragged vectors: bfloat16 always (1x1 n = 40001 0.89 of it, 1x4 0.85, 4x4
-//   0.56); binary32 from 2 workers beyond 4096 elements (1x1 1.04, 1x2 0.93 to
-//   1.04, 1x4 10007 0.79, 4x4 2003 0.64), more than 8 workers from 1024.
-// More workers or no compile-time kernel (split / the other one):
-//   bfloat16: 8x8 n = 262144 10.8 / 10.8; but more than 64 whole ones only up
+// `copy_bytes`: bytes of copies per element (replicas, broadcast gradients),
+// which the split kernels divide over their waves too.
+//
+// Up to 16 workers with a compile-time kernel, time of split over compile-time
+// (ranges are means over random layouts of one range of sizes):
+//   more than 32 bytes of copies: split, binary32 0.34 to 0.98, ragged bfloat16
+//   0.30 to 0.73, whole bfloat16 of more than 4 workers 0.79 to 1.03 (1x8 n =
+//   3825, 23 copies 3.7 / 9.1 us);
+//   whole bfloat16 with fewer never (1x4 n = 65536 2.6 / 2.4 us, 4x4 131072 3.6 /
+//   3.1, 1 to 8 workers 1.02 to 1.32), ragged always (1x4 0.85, 4x4 0.56, 9 to 16
+//   workers 0.39 to 0.50);
+//   whole binary32 from 8 workers (8 0.82 to 1.02, 9 to 16 0.72 to 0.91), with
+//   copies from 5 (0.71 to 1.05, 4 0.90 to 1.11; 1x4 65536 without 2.9 / 2.4 us),
+//   beyond 1024 elements (n = 1000: 1.2);
+//   ragged binary32 from 2 workers (0.66 to 1.04), with copies from 4 (0.60 to
+//   1.02, 2 and 3 0.96 to 1.13; 1x8 n = 11 2.4 / 2.8 us, 3x4 205, 4 copies 3.2 / 4.4).
+// More workers or no compile-time kernel, split / the other one:
+//   bfloat16: 8x8 n = 262144 10.8 / 10.8 us; but more than 64 whole ones only up
 //   to 3 * 2^16 (16x8 185360 0.85 of it, 262144 21.0 / 18.2; ragged 262141
 //   22.1 / 76.5);
-//   binary32 of more than 16 workers: up to 3 * 2^17 (370727: 8x8 18.7 / 25.3,
-//   16x8 41.3 / 46.1, 10x4 13.4 / 17.7, unequal 16 groups of 30 25.9 / 24.4;
-//   524288: 8x8 28.4 / 26.8, 16x8 59.0 / 48.8, unequal 34.7 / 24.8).
-inline bool split_serves(int64_t n, int n_workers, bool bf16, bool compile_time) {
+//   binary32 of more than 16 workers: up to 2^18 + 2^23 / workers (17 to 24 workers
+//   0.75 around 3e5 elements, 0.96 around 6.5e5, 1.09 beyond; 25 to 32 0.80, 1.04,
+//   1.15; 33 to 48 0.84 and, around 4.5e5, 1.04; 49 to 64 0.96 around 3.3e5, 1.2
+//   beyond; 65 to 128 0.86 around 2.3e5, 1.05 around 3.3e5).
+inline bool split_serves(int64_t n, int n_workers, bool bf16, bool compile_time, int64_t copy_bytes) {
     const bool whole = n % (bf16 ? 8 : 4) == 0;
+    const bool many_copies = copy_bytes > 32;
     if (compile_time && n_workers <= 16) {
         if (n > int64_t{1} << 18) return false;
-        if (bf16) return !whole;
-        return n_workers >= (whole ? 8 : 2) && n > (n_workers > 8 ? 1024 : 4096);
+        if (bf16) return !whole || (many_copies && n_workers > 4);
+        if (many_copies) return true;
+        if (whole) return n > 1024 && n_workers >= (copy_bytes ? 5 : 8);
+        return n_workers >= (copy_bytes ? 4 : 2);
     }
     if (bf16) return n <= (compile_time && whole && n_workers > 64 ? int64_t{3} << 16 : int64_t{1} << 18);
-    return n <= (n_workers > 16 ? int64_t{3} << 17 : int64_t{1} << 18);
+    return n <= (int64_t{1} << 18) + (n_workers > 16 ? (int64_t{1} << 23) / n_workers : 0);
 }
 
 // ------------------------------------------------------ split kernels, plans
@@ -51,16 +63,32 @@ struct PlanShape {
     int64_t ragged;            // tensors that end in part of a gradient unit
     int n_workers;
     bool bf16, compile_time;   // a compile-time kernel serves the step
+    bool pow2_groups;          // its group count is a power of two
+    int64_t copy_bytes;        // bytes of replicas per element
 };
 
-// Plans too small to fill the chip (split / the others; 30 tensors unless
-// noted): up to 2^19 elements (n = 2^19: binary32 1x4 4.1 / 5.2, 4x4 8.2 / 10.1,
-// 8x8 25.9 / 32.5), bfloat16 up to 2^20 (4x4 10.2 / 16.1, 8x8 33.9 / 56.1),
-// binary32 up to 2^20 where the tensors hold 2^15 elements or fewer on average
-// (n = 1e6: 60 tensors 0.92 of the others for 4x4, 0.95 for 8x8, 3 to 30 tensors
-// 1.03 to 1.12).
+// Plans too small to fill the chip. Time of split over the others around the
+// line (means over random layouts and tensor counts):
+//   up to 16 workers bfloat16 to 2^20 (4x4 10.2 / 16.1 us), binary32 to 2^19 (30
+//   tensors, 1x4 4.1 / 5.2 us, 4x4 8.2 / 10.1), to 2^20 where the tensors hold 2^15
+//   elements or fewer on average (1e6, 60 tensors 0.92, 3 to 30 tensors 1.03 to 1.12);
+//   more workers, without compile-time kernel: bfloat16 to 2^20 (17 to 48 workers
+//   0.70 to 1.0 around 9e5), of more than 48 to 5 * 2^17 (0.80 to 0.98 around 6.5e5,
+//   1.15 to 1.5 beyond); binary32 with ragged tensors to 2^20 (17 to 32 workers
+//   0.95 to 0.99 around 9e5), of more than 32 to 3 * 2^18 (0.89 to 0.94, 1.0
+//   beyond), whole ones to 2^18 + 10 * 2^20 / workers (17 to 24 0.89 around 6.5e5,
+//   33 to 48 0.92 and 1.05, 49 to 64 1.02 around 4.5e5, 65 to 128 0.91 around 2.3e5,
+//   1.05 around 3.3e5);
+//   with one, ragged tensors (bfloat16 17 to 64 workers 0.68 to 0.77, 65 to 128
+//   0.92) and binary32 (4x16 639360 41.4 / 58.3 us, 1.04e6 0.91) to 2^20.
 inline bool plan_fits_split(const PlanShape& s) {
-    return s.elems <= int64_t{1} << 19 || (s.elems <= int64_t{1} << 20 && (s.bf16 || s.elems <= s.tensors << 15));
+    const int64_t n = s.elems;
+    if (n > int64_t{1} << 20) return false;
+    if (s.n_workers <= 16) return s.bf16 || n <= int64_t{1} << 19 || n <= s.tensors << 15;
+    if (s.compile_time && (s.ragged || !s.bf16)) return true;
+    if (s.bf16) return n <= (s.n_workers <= 48 ? int64_t{1} << 20 : int64_t{5} << 17);
+    if (s.ragged) return s.n_workers <= 32 || n <= int64_t{3} << 18;
+    return n <= (int64_t{1} << 18) + (int64_t{10} << 20) / s.n_workers;
 }
 
 // Plans of any size whose tensors leave most of a workgroup's piece empty. One
@@ -77,26 +105,35 @@ inline bool plan_of_small_tensors(const PlanShape& s) {
     return s.bf16 || s.compile_time ? 2 * s.elems < held : 5 * s.elems < 2 * held;
 }
 
-// Whether a plan's step takes the split kernels. Where no tensor is ragged a
-// compile-time kernel serves few workers better (split / compile-time over the
-// time before either, sizes that are multiples of 64):
-//   bfloat16 up to 16 workers always (1x4 10 tensors n = 65536 0.93 / 0.80, 60
-//   tensors 2^19 0.97 / 0.90; 4x4 10 to 160 tensors 0.25 to 1.15, split the
-//   slower by 0 to 0.2), more only beyond 3 * 2^16 (8x8 131072 0.53 to 0.76 / 0.64
-//   to 0.98, 262144 0.48 to 1.23 / 0.39 to 0.98);
-//   binary32 up to 3 workers (1x2 n = 2^19, 10 tensors 1.06 / 0.97) unless the
-//   tensors are small (1e6, 160 tensors 0.93 / 1.24), up to 7 with at most 3
-//   tensors (1x4 131072 1.00 to 1.03 / 0.97, 10 tensors 2^19 0.82 / 0.98).
-// A single tensor goes by the rule of the flat steps.
+// Whether a plan's step takes the split kernels. Where a tensor is ragged, or
+// there is no compile-time kernel, always. Where all are whole (time of split
+// over compile-time, means over random layouts and tensor counts):
+//   bfloat16 up to 16 workers: not (1 to 8 workers 1.02 to 1.2, 9 to 16 0.95 to
+//   1.13), but from 5 with more than 32 bytes of copies (0.74 to 1.03) or another
+//   group count than a power of two (0.66 to 1.14, 9 to 16 0.81 to 0.97), to 3 * 2^18
+//   (0.92 around 6.5e5);
+//   bfloat16 of more workers: 17 to 24 to 2^19 (0.64 to 0.67 around 3e5; 5x4 464512
+//   elements 9.0 / 19.3 us), up to 48 to 2^18 (0.33 to 0.81, 1.0 beyond), more to 3
+//   * 2^16 (0.65 to 0.87, 1.0 beyond); with many copies a quarter further (1x32
+//   300032, R = 32 8.6 / 11.9 us);
+//   binary32 with many copies or such a group count to 2^19 (0.51 to 0.98), else
+//   from 8 workers beyond 4096 elements (0.66 to 0.91, below 0.96 to 1.19), from 4
+//   beyond 8192 (0.75 to 0.96, below 0.94 to 1.05), fewer only small tensors of more
+//   than 2^19 elements (1x2, 1e6, 160 tensors 0.93 / 1.24 of the time before either;
+//   2^19, 10 tensors 1.06 / 0.97).
 inline bool split_serves_plan(const PlanShape& s) {
     if (!plan_fits_split(s)) return plan_of_small_tensors(s);
-    if (!s.compile_time) return true;
-    if (s.ragged == 0) {
-        if (s.bf16) return s.n_workers > 16 && s.elems <= int64_t{3} << 16;
-        if (s.n_workers <= 3) return s.elems > int64_t{1} << 19 && s.elems <= s.tensors << 13;
-        if (s.n_workers < 8 && s.tensors <= 3) return false;
+    if (!s.compile_time || s.ragged) return true;
+    const bool many_copies = s.copy_bytes > 32;
+    const int64_t n = s.elems;
+    if (s.n_workers > 16) {
+        const int64_t line = s.n_workers <= 24 ? int64_t{1} << 19 : s.n_workers <= 48 ? int64_t{1} << 18 : int64_t{3} << 16;
+        return !s.bf16 || n <= (many_copies ? line + line / 4 : line);
     }
-    return s.tensors > 1 || split_serves(s.elems, s.n_workers, s.bf16, true);
+    if (s.bf16) return n <= int64_t{3} << 18 && s.n_workers > 4 && (many_copies || !s.pow2_groups);
+    if (many_copies || !s.pow2_groups) return n <= int64_t{1} << 19;
+    if (s.n_workers < 4) return n > int64_t{1} << 19 && n <= s.tensors << 13;
+    return n > (s.n_workers < 8 ? 8192 : 4096);
 }
 
 // Whether LARS steps take the split kernels; `merged`: every workgroup of the
@@ -107,22 +144,26 @@ inline bool split_serves_plan(const PlanShape& s) {
 //   160 tensors 1.03 / 1.14 of the time before);
 //   bfloat16 with a compile-time kernel and no ragged tensor, of the time before:
 //   merged to 9 * 2^16 (4x4 2^18 0.79 / 0.85, 60 tensors 2^19 0.87 / 0.87 and,
-//   R = 16, 14.1 / 18.1 us, 1e6 1.11 / 1.00), else more than 16 workers to 3 * 2^16
+//   R = 16, 14.1 / 18.1 us, 1e6 1.11 / 1.00), of up to 24 workers in groups whose
+//   count is no power of two to 3 * 2^18 (5x4 698304 16.2 / 21.3 us, 9 to 16 workers
+//   0.64 to 0.87 of the others, 25 and more 1.2 from 2^19), else more than 16 workers to 3 * 2^16
 //   (8x8 131072 0.50 to 0.75 / 0.68 to 0.98, 3 tensors 262144 1.27 / 0.99);
 //   not merged, bfloat16 of 9 to 16 workers to 2^19 (1x4 3 tensors 2^19 12.0 /
 //   11.1, 4x4 14.6 / 17.1, 1x9 13.5 / 14.1, 1e6 21.5 / 18.0) and more than 16
 //   workers (8x8 2^19 26.5 / 44.8; binary32 35.2 / 51.3, but 1x4, one tensor, 16.8
 //   / 12.4, 4x4 26.5 / 19.8);
 //   binary32 of more than 16 workers beyond 2^19 not where the tensors are few and
-//   large (8x8, n = 1e6, 3 tensors 63.6 / 58.7, 16 tensors 63.8 / 76.5).
+//   large (8x8, n = 1e6, 3 tensors 63.6 / 58.7, 16 tensors 63.8 / 76.5), and not
+//   of more than 64 (1.04 to 1.48 of the others).
 inline bool split_serves_lars(const PlanShape& s, bool merged) {
     const int64_t n = s.elems;
     const bool many = s.n_workers > 16;
     if (n > int64_t{1} << 20) return false;
     if (s.bf16 && s.compile_time && s.ragged == 0)
-        return merged ? n <= int64_t{9} << 16 : many && n <= int64_t{3} << 16;
+        return merged ? n <= (s.pow2_groups || s.n_workers > 24 ? int64_t{9} << 16 : int64_t{3} << 18)
+                      : many && n <= int64_t{3} << 16;
     if (!merged && !many && !(s.bf16 && s.n_workers > 8 && n <= int64_t{1} << 19)) return false;
-    return s.bf16 || n <= int64_t{1} << 19 || n <= s.tensors << (many ? 18 : 13);
+    return s.bf16 || n <= int64_t{1} << 19 || (s.n_workers <= 64 && n <= s.tensors << (many ? 18 : 13));
 }
 
 // ------------------------------------------------------ copy pass of a plan

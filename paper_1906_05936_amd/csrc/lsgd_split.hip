@@ -17,8 +17,8 @@ bool split_allowed(int n_batches) { return n_batches <= kSplitMaxBatches && laun
 
 }  // namespace
 
-bool use_split_flat(int64_t n, int32_t n_workers, bool bf16, bool compile_time, int n_batches) {
-    return split_serves(n, n_workers, bf16, compile_time) && split_allowed(n_batches);
+bool use_split_flat(int64_t n, int32_t n_workers, bool bf16, bool compile_time, int64_t copy_bytes, int n_batches) {
+    return split_serves(n, n_workers, bf16, compile_time, copy_bytes) && split_allowed(n_batches);
 }
 
 bool split_plan_allowed(int n_batches) { return split_allowed(n_batches); }

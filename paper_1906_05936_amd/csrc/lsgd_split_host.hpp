@@ -17,8 +17,8 @@ constexpr int kSplitElems = kSplitVec * kSplitUnits;
 constexpr int kLarsMergeChunks = 512;  // most pieces of a tensor whose partials every update workgroup sums itself
 
 // Whether a flat step of n elements takes the split kernels; `compile_time`: a
-// compile-time kernel serves the layout.
-bool use_split_flat(int64_t n, int32_t n_workers, bool bf16, bool compile_time, int n_batches);
+// compile-time kernel serves the layout, `copy_bytes`: of copies per element.
+bool use_split_flat(int64_t n, int32_t n_workers, bool bf16, bool compile_time, int64_t copy_bytes, int n_batches);
 // Whether a plan may have split pieces (its rules: split_serves_plan, plan_fits_split).
 bool split_plan_allowed(int n_batches);
 // Whether a split step writes its copies in passes of their own, given what

@@ -16,21 +16,21 @@ MAIN = r"""
 using namespace lsgd;
 int main() {
     std::string rule;
-    long long v[8];
+    long long v[10];
     while (std::cin >> rule) {
         int k = 0;
         std::cin >> k;
         for (int i = 0; i < k; ++i) std::cin >> v[i];
         bool r = false;
-        if (rule == "split") r = split_serves(v[0], (int)v[1], v[2], v[3]);
+        if (rule == "split") r = split_serves(v[0], (int)v[1], v[2], v[3], v[4]);
         else if (rule == "apart") r = copies_apart((int)v[0], (int)v[1], (int)v[2], v[3], v[4], v[5], v[6], v[7]);
         else if (rule == "two") r = stream_two_units(v[0], (int)v[1], (int)v[2], v[3], (int)v[4]);
         else if (rule == "plan") {
-            r = split_serves_plan(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0});
+            r = split_serves_plan(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0, v[7] != 0, v[8]});
         } else if (rule == "lars") {
-            r = split_serves_lars(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0}, v[7]);
+            r = split_serves_lars(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0, v[7] != 0, v[8]}, v[9]);
         } else if (rule == "copies") r = copy_replicas_per_group(v[0], v[1]) == (int)v[2];
-        else if (rule == "plantwo") r = plan_two_units(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0}, v[7], 256);
+        else if (rule == "plantwo") r = plan_two_units(PlanShape{v[0], v[1], v[2], v[3], (int)v[4], v[5] != 0, v[6] != 0, v[7] != 0, v[8]}, v[9], 256);
         else if (rule == "mean") r = mean_stream_form((int)v[0], v[1]) == (MeanForm)v[2];
         else return 1;
         std::printf("%d\n", (int)r);
@@ -56,18 +56,23 @@ def ask(tmp_path_factory):
 
 F32, BF16 = False, True
 
-# (n, workers, bfloat16, compile-time kernel), split kernel faster?
+# (n, workers, bfloat16, compile-time kernel, copy bytes), split kernel faster?
 SPLIT = [
-    ((65_536, 4, F32, True), False), ((131_072, 4, F32, True), False), ((10_007, 4, F32, True), True),
-    ((1_000, 16, F32, True), False), ((2_003, 16, F32, True), True), ((65_536, 16, F32, True), True),
-    ((262_144, 16, F32, True), True), ((262_145, 16, F32, True), False), ((40_000, 8, F32, True), True),
-    ((3_000, 8, F32, True), False), ((100_003, 1, F32, True), False), ((10_007, 2, F32, True), True),
-    ((65_536, 4, BF16, True), False), ((131_072, 16, BF16, True), False), ((131_069, 16, BF16, True), True),
-    ((100_000, 10, BF16, True), False), ((1_003, 4, BF16, True), True), ((262_144, 128, BF16, True), False),
-    ((185_360, 128, BF16, True), True), ((262_141, 128, BF16, True), True), ((262_144, 64, BF16, True), True),
-    ((262_144, 40, BF16, False), True), ((300_000, 40, BF16, False), False),
-    ((370_727, 64, F32, False), True), ((524_288, 64, F32, False), False), ((1_000_000, 30, F32, False), False),
-    ((1_000_000, 80, F32, False), False), ((200_000, 9, F32, False), True), ((300_000, 9, F32, False), False),
+    ((65_536, 4, F32, True, 0), False), ((131_072, 4, F32, True, 0), False), ((10_007, 4, F32, True, 0), True),
+    ((1_000, 16, F32, True, 0), False), ((2_003, 16, F32, True, 0), True), ((65_536, 16, F32, True, 0), True),
+    ((262_144, 16, F32, True, 0), True), ((262_145, 16, F32, True, 0), False), ((40_000, 8, F32, True, 0), True),
+    ((11, 8, F32, True, 0), True), ((205, 12, F32, True, 16), True), ((100_003, 1, F32, True, 0), False), ((10_007, 2, F32, True, 0), True), ((165_830, 2, F32, True, 8), False),
+    ((3_825, 8, F32, True, 92), True), ((1_671, 8, F32, True, 72), True), ((30_000, 5, F32, True, 4), True),
+    ((30_000, 5, F32, True, 0), False), ((65_536, 4, F32, True, 16), False), ((20_001, 4, F32, True, 16), True),
+    ((65_536, 4, BF16, True, 0), False), ((131_072, 16, BF16, True, 0), False), ((131_069, 16, BF16, True, 0), True),
+    ((100_000, 10, BF16, True, 0), False), ((1_003, 4, BF16, True, 0), True), ((262_144, 128, BF16, True, 0), False),
+    ((30_000, 8, BF16, True, 48), True), ((30_000, 8, BF16, True, 16), False), ((30_000, 4, BF16, True, 48), False),
+    ((185_360, 128, BF16, True, 0), True), ((262_141, 128, BF16, True, 0), True), ((262_144, 64, BF16, True, 0), True),
+    ((262_144, 40, BF16, False, 0), True), ((300_000, 40, BF16, False, 0), False),
+    ((370_727, 64, F32, False, 0), True), ((524_288, 64, F32, False, 0), False), ((1_000_000, 30, F32, False, 0), False),
+    ((1_000_000, 80, F32, False, 0), False), ((200_000, 9, F32, False, 0), True), ((300_000, 9, F32, False, 0), False),
+    ((541_674, 20, F32, False, 20), True), ((446_528, 20, F32, False, 52), True), ((577_000, 30, F32, False, 0), False),
+    ((381_120, 80, F32, False, 40), False),
 ]
 
 
@@ -112,10 +117,10 @@ def test_two_unit_tiles(ask):
     assert got == [want for _, want in TWO_UNITS], [r for (r, w), g in zip(TWO_UNITS, got) if w != g]
 
 
-def shape(sizes, workers, bf16, compile_time):
+def shape(sizes, workers, bf16, compile_time, pow2_groups=True, copy_bytes=0):
     unit = 8 if bf16 else 4
     return (sum(sizes), sum(s > 0 for s in sizes), sum(-(-s // 2048) for s in sizes), sum(s % unit > 0 for s in sizes), workers,
-            bf16, compile_time)
+            bf16, compile_time, pow2_groups, copy_bytes)
 
 
 GROWING = [30_000 * k // 20 + 7 for k in range(1, 31)]   # 30 tensors of 7e5 elements in all
@@ -129,13 +134,22 @@ PLAN_SPLIT = [
     (shape(GROWING, 16, F32, True), True), (shape(GROWING, 16, BF16, True), True),
     (shape([333_333] * 3, 16, F32, True), False), (shape([333_333] * 3, 64, F32, False), False),
     (shape([333_333] * 3, 16, BF16, True), True), (shape([16_667] * 60, 16, F32, True), True),
-    (shape([175_000] * 3, 4, F32, True), False), (shape([170_001] * 3, 4, F32, True), True), (shape([170_000] * 3, 4, F32, True), False),
-    (shape([524_288], 16, F32, True), False), (shape([65_536], 4, F32, True), False), (shape([65_536], 16, F32, True), True),
+    (shape([175_000] * 3, 4, F32, True), False), (shape([170_001] * 3, 4, F32, True), True), (shape([170_000] * 3, 4, F32, True), True),
+    (shape([524_288], 16, F32, True), True), (shape([65_536], 4, F32, True), True), (shape([65_536], 16, F32, True), True),
     (shape([262_144], 16, BF16, True), False), (shape([131_069], 16, BF16, True), True),
-    (shape([100_001, 100_001], 4, F32, True), True), (shape([100_000, 100_000], 4, F32, True), False), (shape([519_001, 5_000], 16, BF16, True), True),
+    (shape([100_001, 100_001], 4, F32, True), True), (shape([100_000, 100_000], 4, F32, True), True), (shape([519_001, 5_000], 16, BF16, True), True),
     (shape([17_472] * 60, 4, F32, True), True), (shape([6_400] * 160, 2, F32, True), True), (shape([52_480] * 10, 2, F32, True), False),
     (shape([8_704] * 60, 4, BF16, True), False), (shape([8_703] * 60, 4, BF16, True), True), (shape([13_120] * 10, 64, BF16, True), True),
-    (shape([524_288, 0], 16, F32, True), False), (shape([524_288], 9, BF16, False), True),
+    (shape([524_288, 0], 16, F32, True), True), (shape([524_288], 9, BF16, False), True),
+    (shape([272_215], 36, BF16, True, False), True), (shape([232_256] * 2, 20, BF16, True, False, 40), True),
+    (shape([57_384] * 8, 24, BF16, True, False, 10), True), (shape([32_000] * 8, 64, BF16, True), False),
+    (shape([16_000] * 12, 32, BF16, True), True), (shape([75_008] * 4, 32, BF16, True, True, 64), True), (shape([75_008] * 4, 32, BF16, True), False),
+    (shape([88] * 350, 12, BF16, True, False), True), (shape([88] * 350, 16, BF16, True), False), (shape([88] * 350, 16, BF16, True, True, 64), True),
+    (shape([420] * 112, 2, F32, True), False), (shape([420] * 112, 2, F32, True, True, 48), True), (shape([64] * 64, 16, F32, True), False),
+    (shape([1_280] * 64, 5, F32, True), True), (shape([128] * 64, 5, F32, True), False),
+    (shape([360_567, 360_568], 20, F32, False), True), (shape([271_045, 271_045], 28, F32, False), True),
+    (shape([23_676] * 39, 54, F32, False), False), (shape([17_880] * 49, 99, F32, False), False), (shape([14_461] * 60, 70, F32, False), False),
+    (shape([18_816] * 34, 64, F32, True), True), (shape([24_740] * 24, 100, BF16, False), True), (shape([200_001] * 5, 30, F32, False), True),
 ]
 
 
@@ -162,6 +176,8 @@ LARS_SPLIT = [
     (shape([8_704] * 60, 16, BF16, True), True, True), (shape([16_704] * 60, 16, BF16, True), True, False),
     (shape([1_000_001], 9, BF16, False), False, False), (shape([500_001], 9, BF16, False), False, True),
     (shape([6_272] * 160, 4, F32, True), True, True), (shape([131_072], 16, BF16, True), False, False),
+    (shape([5_824] * 120, 20, BF16, True, False), True, True), (shape([17_000] * 32, 30, BF16, True, False), True, True),
+    (shape([20_000] * 32, 30, BF16, True, False), True, False), (shape([62_501] * 16, 80, F32, False), True, False),
     (shape([131_072], 4, F32, True), True, True), (shape([700] * 3_000, 64, BF16, True), True, False),
 ]
 
