@@ -2,6 +2,8 @@
 // (lsgd_program.hpp): the register batches and the kernel arguments.
 #pragma once
 
+#include <stddef.h>
+
 #include "lsgd_kernels.hpp"
 #include "lsgd_plan_kernels.hpp"
 #include "lsgd_program.hpp"
@@ -11,6 +13,10 @@
 namespace lsgd {
 
 // The steps' arguments with the reduction program, all in the kernel arguments.
+// The program's batches, which every wave reads first, start a cache line (the
+// padding in StepArgs and PlanArgs sees to it): 8 bytes off it a split step of up
+// to 30000 elements took 2 % longer (1x32 bfloat16 n = 2500 3.15 / 3.22 us, 2x24
+// binary32 3.61 / 3.70; plans of ten tensors 1.6 %).
 struct FlatProgArgs {
     StepArgs a;
     Program pr;
@@ -23,6 +29,12 @@ struct LarsProgArgs {
     LarsArgs la;
     Program pr;
 };
+template <typename A>
+constexpr bool batches_on_a_line() {
+    return (offsetof(A, pr) + offsetof(Program, batch)) % 64 == 0;
+}
+static_assert(batches_on_a_line<FlatProgArgs>() && batches_on_a_line<PlanProgArgs>() && batches_on_a_line<LarsProgArgs>(),
+              "adjust the padding");
 
 // Calls f(count, sub) with the batch's member count and inner group size as
 // compile-time constants.

@@ -391,6 +391,7 @@ struct StepArgs {
     int64_t n;
     Hyper h;
     int32_t n_workers;
+    int32_t pad[2];        // lsgd_batches.hpp: the reduction program behind starts a cache line
     int32_t n_replicas, rdt;
     uint32_t xcd_chunk, upl;
     const float* lr_ptr;   // non-null: the learning rate is read here when the kernel runs

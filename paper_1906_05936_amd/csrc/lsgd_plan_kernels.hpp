@@ -29,6 +29,7 @@ struct PlanArgs {
     const PlanChunk* chunks;      // [n_chunks]
     void* const* ptrs;
     int32_t stride, n_workers;
+    int32_t pad[2];               // as in StepArgs
     int32_t n_replicas, rdt;
     int32_t n_chunks;
     uint32_t xcd_chunk;
