@@ -102,14 +102,14 @@ LSGD_API const char* lsgd_last_error(void);
  * Launch shape of the planless kernels, process-wide (a tuning knob; results
  * of the steps are bit-identical for every shape, because each element is
  * computed by one lane from its own inputs in a fixed order). Plans launch one
- * workgroup per bucket: xcd_chunk applies at each lsgd_step_plan, units_per_lane
+ * workgroup per piece of a tensor: xcd_chunk applies at each lsgd_step_plan, units_per_lane
  * at lsgd_plan_create, blocks_per_cu only to their copy-out pass. The one
  * result that can depend on a shape is a LARS trust ratio
  * (lsgd_lars_step_plan): its norms are summed piece by piece, and a plan's
- * piece size is fixed by units_per_lane when the plan is created, so plans
- * created with different units_per_lane may give ratios (and hence LARS
- * steps) that differ in the last bit; for one plan, LARS results do not
- * depend on the shape.
+ * piece size is fixed when the plan is created, by units_per_lane, the tensors'
+ * sizes and the number and type of the gradients, so plans that differ in these
+ * may give ratios (and hence LARS steps) that differ in the last bit; for one
+ * plan, LARS results do not depend on the shape.
  *   xcd_chunk       0 = workgroups in hardware order; C > 0 = each of the eight
  *                   XCDs runs C consecutive logical workgroups per turn (the grid
  *                   is padded to a multiple of 8*C; not applied to grids smaller
@@ -139,11 +139,14 @@ LSGD_API lsgd_status lsgd_get_launch_shape(int32_t* xcd_chunk, int32_t* blocks_p
  * mostly from cache) and writes the replicas one window of the vector at a
  * time. Results are identical either way. LSGD_COPY_OUT_AUTO (the default)
  * takes the separate pass where it measured faster: for the fused steps when
- * the replica bytes R*s_r per element are at least 32 (for at most 16 workers
- * with parameters and momentum within 128 MB: 40, or 48 for a layout without a
- * compile-time kernel; with bfloat16 gradients and binary32 replicas 24, or 16
- * up to 288 MB) or the gradient bytes N*s_g at least 256; short vectors and
- * small plans write up to 64 MB of copies in the step kernel;
+ * the gradient bytes N*s_g per element are at least 256, or the bytes of copies
+ * (replicas R*s_r, with broadcast_grad also the mean gradients) at least 32 - for
+ * at most 16 workers with parameters and momentum within 128 MB at least 48 (56
+ * up to 4 workers, 64 for a layout without a compile-time kernel; with
+ * broadcast_grad 64, or 52 from 12 workers) and 128 MB of copies in all; with
+ * bfloat16 gradients and binary32 replicas 24 and 26 MB, or 16 between 128 and
+ * 288 MB of parameters and momentum. Steps in the kernels for short vectors and
+ * small plans write up to 64 MB of copies themselves;
  * for lsgd_sgd_step and the LARS update when R*s_r >= 16 (parameters and
  * momentum within 288 MB; beyond, binary32 replicas and R >= 4).
  * Process-wide, for launches after the call returns. Errors: LSGD_ERR_SIZE
@@ -226,21 +229,23 @@ LSGD_API lsgd_status lsgd_copy_out(const float* params, int64_t n, void* const* 
  * One fused Layered SGD step: group means, global mean, update and copy-out.
  * The step kernel reads every gradient, parameter and momentum element once
  * and writes parameters and momentum once; the group means and the mean
- * gradient stay in registers. The replicas are written either by that kernel
+ * gradient stay in registers or LDS. The replicas are written either by that kernel
  * or, where lsgd_set_copy_out_mode's rule takes the separate form, by a copy-out
  * pass launched right after it, which reads the new parameters once more
  * (the step kernel then still writes the first lsgd_set_step_replicas
  * replicas). Vectors longer than 2^26 elements are processed range by range
  * (about 2^24 elements each, edges on multiples of 2^20 elements: the step
  * kernel, then its copy-out pass) unless the step kernel writes every
- * replica itself. Short vectors (up to 2^18 elements, 2^20 for binary32
- * gradients of more than 16 workers) take kernels that divide the workers'
- * gradients over the waves of a workgroup. Compile-time kernels (the pairwise
+ * replica itself. Short vectors (up to 2^18 elements, 2^18 + 2^23 / n_workers for
+ * binary32 gradients of more than 16 workers) take kernels that divide the
+ * workers' gradients over the waves of a workgroup, unless a compile-time kernel
+ * serves them better (n a multiple of 16 bytes' elements, few workers, few
+ * copies). Compile-time kernels (the pairwise
  * trees unrolled) serve binary32 gradients of up to 16 workers, and a power of
  * two of groups of 16, and bfloat16 gradients, for power-of-two group counts
  * with groups of 1 to 16 workers (a power of two, or 3, 5, 6, 7 or 12), 32 to
  * 128 workers in up to 4 groups, 32 to 128 groups of up to 4 workers, and 3,
- * 5, 6 or 7 (binary32: or 12) groups of 2 to 8, 12, 16 or 32 workers;
+ * 5, 6 or 7 groups of 2 to 8, 12, 16 or 32 workers;
  * every other grouping takes a runtime-layout kernel. Arguments as for the
  * three calls above. The results are bit-identical to lsgd_group_mean, then
  * lsgd_global_mean, then lsgd_sgd_step, in every form.
@@ -333,14 +338,13 @@ LSGD_API lsgd_status lsgd_lr_schedule_step(const lsgd_lr_schedule* schedule, int
 /*
  * Multi-tensor plan: the fused step over a model's list of parameter tensors
  * (e.g. the 161 tensors of ResNet-50, the model of Sec. 5.3) in ONE kernel
- * launch. The plan copies a chunk table and a pointer table to device memory
- * once; lsgd_step_plan then launches one kernel. Tensors are cut into pieces
- * of 2048 elements (4096 for binary32 gradients without a compile-time kernel,
- * as listed for lsgd_step, or of 32 to 128 workers in groups of 16, and for
- * bfloat16 gradients without one; times the launch shape's units_per_lane at
- * creation); small
- * plans (up to 2^20 elements, 2^19 for binary32 gradients of at most 16
- * workers, with units_per_lane 1) into pieces of 256. One workgroup per piece.
+ * launch (and, as for lsgd_step, a copy-out pass where its rule says so). The
+ * plan copies tables of pieces and pointers to device memory once. Tensors are
+ * cut into pieces of 2048 elements, for the kernels whose workgroups cover that
+ * many at a time into pieces of 4096 (times the launch shape's units_per_lane
+ * at creation); plans of up to 2^20 elements, and larger ones whose tensors are
+ * small, where the kernels for short vectors serve them better (units_per_lane
+ * 1) into pieces of 256. One workgroup per piece.
  *   numel     [n_tensors] host int64, elements of each tensor (>= 0).
  *   params, momentum [n_tensors] device pointers (binary32).
  *   grads     [n_workers * n_tensors] device pointers, worker-major:

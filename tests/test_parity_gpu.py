@@ -119,8 +119,10 @@ STEP_CASES = [
     (2, 5, "f32", 2_000_003, 10, "f32", "shuffled"),
     (2, 2, "bf16", 4_000_003, 4, "f32", "contiguous"),
     (1, 3, "f32", 2_000_003, 3, "f32", "contiguous"),
-    # compile-time kernels for 32 to 128 groups of few workers, and for groups
-    # of 32 to 128 workers (members streamed through an accumulator)
+    # 32 to 128 groups of few workers, and groups of 32 to 128 workers. (Here
+    # and below: sizes up to 2^18 with ragged ends, as these, take the split
+    # kernels by default; test_large_kernels_gpu.py runs all these cases again
+    # in the kernels that serve the same groupings at large sizes.)
     (32, 4, "f32", 300_007, 8, "f32", "shuffled"),
     (32, 4, "bf16", 70_001, 2, "bf16", "shuffled"),
     (64, 2, "f32", 50_001, 0, "f32", "shuffled"),
@@ -130,15 +132,14 @@ STEP_CASES = [
     (1, 128, "f32", 20_011, 2, "bf16", "contiguous"),
     (1, 32, "bf16", 33_335, 1, "bf16", "contiguous"),
     # non-power-of-two group counts with power-of-two groups, and groups of 3,
-    # 5 or 6 (the segmented kernel)
+    # 5 or 6
     (3, 8, "f32", 100_003, 24, "f32", "shuffled"),
     (6, 4, "bf16", 50_001, 2, "bf16", "shuffled"),
     (12, 8, "f32", 30_007, 1, "f32", "shuffled"),
     (4, 6, "f32", 65_537, 24, "f32", "shuffled"),
     (9, 1, "bf16", 5_555, 0, "f32", "contiguous"),
     (3, 2, "f32", 4_101, 6, "f32", "shuffled"),
-    # the segmented kernel's accumulator forms: counts up to 7 take 3 levels
-    # (above), up to 15 four, up to 31 five, larger eight (1 x 100 above)
+    # other counts (stream kernels at large sizes)
     (1, 9, "f32", 6_007, 3, "f32", "contiguous"),
     (20, 3, "f32", 7_001, 2, "f32", "shuffled"),
     (3, 20, "bf16", 5_003, 1, "bf16", "shuffled"),
@@ -148,9 +149,8 @@ STEP_CASES = [
     (12, 1, "f32", 33_333, 3, "f32", "shuffled"),
     (6, 1, "bf16", 20_005, 2, "bf16", "shuffled"),
     (12, 1, "f32", 2_000_003, 12, "f32", "shuffled"),
-    # compile-time kernels for groups of 3, 5, 6 or 7 in a power-of-two count
-    # (the group mean a true division); 16 and 32 groups of 3 stream their
-    # groups in power-of-two batches
+    # groups of 3, 5, 6 or 7 in a power-of-two count (the group mean a true
+    # division)
     (8, 3, "f32", 100_003, 24, "f32", "shuffled"),
     (16, 3, "f32", 2_000_003, 4, "f32", "shuffled"),
     (32, 3, "f32", 10_007, 2, "f32", "shuffled"),
@@ -160,23 +160,20 @@ STEP_CASES = [
     (2, 7, "f32", 30_011, 14, "f32", "contiguous"),
     (4, 7, "bf16", 7_003, 1, "f32", "contiguous"),
     (16, 6, "f32", 20_003, 1, "f32", "shuffled"),
-    # compile-time kernels for 3, 5, 6, 7 or 12 groups (the total a true
-    # division; 12 groups stream through the accumulator in batches of a
-    # divisor of 12)
+    # 3, 5, 6, 7 or 12 groups (the total a true division)
     (12, 4, "f32", 2_000_003, 12, "f32", "shuffled"),
     (12, 8, "bf16", 30_001, 2, "bf16", "shuffled"),
     (7, 16, "bf16", 9_999, 1, "f32", "shuffled"),
     (5, 16, "f32", 8_011, 3, "f32", "contiguous"),
     (6, 3, "f32", 60_013, 18, "f32", "shuffled"),
     (12, 1, "bf16", 11_111, 2, "bf16", "shuffled"),
-    # groups of 12 workers: compile-time kernels for power-of-two counts and
-    # for 3, 5, 6 and 7 groups
+    # groups of 12 workers, power-of-two counts and 3, 5, 6 and 7 groups
     (4, 12, "f32", 100_003, 12, "f32", "shuffled"),
     (8, 12, "bf16", 30_007, 2, "bf16", "shuffled"),
     (3, 12, "f32", 20_011, 3, "f32", "shuffled"),
     (7, 12, "bf16", 9_001, 0, "f32", "shuffled"),
     (1, 12, "f32", 8_191, 1, "f32", "contiguous"),
-    # 3 groups of 32: members streamed through the accumulator, G a division
+    # 3 groups of 32: G a division
     (3, 32, "f32", 20_011, 2, "f32", "shuffled"),
     (3, 32, "bf16", 9_001, 0, "f32", "contiguous"),
 ]
@@ -353,7 +350,7 @@ def test_plan_matches_oracle(G, W, gdt, R, rdt):
 
 
 def test_plan_equals_flat_bitwise():
-    """Different launch shapes (plan buckets vs grid-stride flat kernel) give the
+    """Different launch shapes (plan pieces vs grid-stride flat kernel) give the
     same bits: every element's result depends only on its own inputs."""
     sizes = workloads.resnet50_param_sizes()[:40]
     n = sum(sizes)
@@ -775,15 +772,15 @@ LITERAL_CASES = [
     (list(range(7)), 7, "f32", 3_001, 0, False),
     ([3, 0, 6, 1, 5, 2, 4], 7, "f32", 3_001, 1, False),   # one worker per group, shuffled: divides per group
     ([0, 0, 0, 1, 1, 2] * 20, 3, "f32", 4_099, 3, True),
-    # equal power-of-two groups: the compile-time kernels, on XCD-renumbered
-    # grids, with the replicas and the broadcast in copy passes of their own
+    # equal power-of-two groups: at 1e6 elements and more the compile-time
+    # kernels, on XCD-renumbered grids, with the replicas and the broadcast in
+    # copy passes of their own
     ("shuffled4x4", 4, "f32", 2_000_003, 16, False),
     ("shuffled4x4", 4, "f32", 2_000_003, 16, True),
     ("shuffled4x4", 4, "f32", 33_333, 2, True),
     ("contiguous8x8", 8, "bf16", 100_003, 2, False),
     ("contiguous2x2", 2, "f32", 1_000_001, 1, True),
-    # equal groups of 3 in a power-of-two count: the compile-time kernel, each
-    # group's sum divided by N = 24
+    # equal groups of 3 in a power-of-two count: each group's sum divided by N = 24
     (workloads.shuffled_groups(8, 3, 5), 8, "f32", 40_003, 3, True),
 ]
 
@@ -834,9 +831,8 @@ def extreme_grads(rng, n, N, gdt):
 
 @pytest.mark.parametrize("gdt", ["f32", "bf16"])
 def test_literal_power_of_two_groups_at_range_extremes(gdt):
-    """The paper-literal reduction on equal power-of-two groups (the
-    compile-time kernels, flat and plan) with subnormal and near-overflow
-    gradients: bit-exact against the oracle's literal step. With binary32
+    """The paper-literal reduction on equal power-of-two groups (flat and plan)
+    with subnormal and near-overflow gradients: bit-exact against the oracle's literal step. With binary32
     gradients that step differs from the mean of means on some of these
     elements (division by N against division by W then G, where the quotient
     is subnormal); bfloat16 subnormals are multiples of 2^-133, whose
@@ -1246,7 +1242,7 @@ def test_nontemporal_forms_above_the_cache_limit(G, W, gdt, R, rdt, plan):
     """Vectors whose parameters and momentum exceed the cached form's limit
     (8n > 288 MB) take the nontemporal kernels even with 16 or fewer workers:
     two steps on sampled elements against the oracle, flat (compile-time and
-    segmented) and through a three-tensor plan."""
+    stream kernels) and through a three-tensor plan."""
     n = 40_000_003
     log("n = %d above the cache limit: G=%d W=%d %s R=%d %s plan=%s" % (n, G, W, gdt, R, rdt, plan))
     N = G * W
@@ -1318,9 +1314,10 @@ def test_every_tail_size_flat(gdt, G, W, R, rdt):
 
 @pytest.mark.parametrize("gdt,G,W", [("f32", 2, 4), ("bf16", 2, 4), ("f32", 8, 4)])
 def test_every_tail_size_as_plan_tensors(gdt, G, W):
-    """The same sizes as the tensors of one plan (many small tensors share a
-    bucket): plain step, then a LARS step, each tensor bit-exact against the
-    oracle (8x4 binary32: four-unit tiles and 4096-element pieces)."""
+    """The same sizes as the tensors of one plan (a workgroup and more
+    each): plain step, then a LARS step, each tensor bit-exact against the
+    oracle. (A plan this small takes the split kernels by default;
+    test_large_kernels_gpu.py repeats it in the others.)"""
     rng = np.random.default_rng(68)
     N = G * W
     gow = groups_for(G, W, "shuffled", seed=4)
@@ -1349,7 +1346,7 @@ def test_every_tail_size_as_plan_tensors(gdt, G, W):
         assert np.float32(tg[t]) == np.float32(tr), (s, tg[t], tr)
         assert_close(to_host(params[t]), ph[t], "LARS params size %d" % s)
         assert_close(to_host(mom[t]), mh[t], "LARS momentum size %d" % s)
-    # the plan's copy-out pass on its own over every tail size (shared buckets too)
+    # the plan's copy-out pass on its own over every tail size (whole pieces too)
     for x in reps[0]:
         x.fill_(3)
     plan.copy_out()
