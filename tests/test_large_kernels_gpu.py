@@ -36,11 +36,6 @@ def test_random_case(two_passes, k):
     randomized.test_random_case_matches_oracle(k)
 
 
-@pytest.mark.parametrize("case", [c for c in parity.STEP_CASES if c[3] < 1 << 19], ids=lambda c: "%dx%d-%s-%d" % c[:4])
-def test_fused_step(two_passes, case):
-    parity.test_fused_step_matches_oracle(*case)
-
-
 @pytest.mark.parametrize("case", [c for c in parity.LITERAL_CASES if c[3] < 1 << 19], ids=lambda c: "%s-%s-%d-%s" % (c[1], c[2], c[3], c[5]))
 def test_literal_reduction(two_passes, case):
     parity.test_literal_reduction_matches_oracle(*case)

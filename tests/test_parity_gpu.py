@@ -121,8 +121,8 @@ STEP_CASES = [
     (1, 3, "f32", 2_000_003, 3, "f32", "contiguous"),
     # 32 to 128 groups of few workers, and groups of 32 to 128 workers. (Here
     # and below: sizes up to 2^18 with ragged ends, as these, take the split
-    # kernels by default; test_large_kernels_gpu.py runs all these cases again
-    # in the kernels that serve the same groupings at large sizes.)
+    # kernels by default; test_split_gpu.py runs all these cases again in the
+    # kernels that serve the same groupings at large sizes.)
     (32, 4, "f32", 300_007, 8, "f32", "shuffled"),
     (32, 4, "bf16", 70_001, 2, "bf16", "shuffled"),
     (64, 2, "f32", 50_001, 0, "f32", "shuffled"),
