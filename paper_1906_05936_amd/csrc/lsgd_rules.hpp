@@ -146,8 +146,9 @@ inline bool split_serves_plan(const PlanShape& s) {
 //   merged to 9 * 2^16 (4x4 2^18 0.79 / 0.85, 60 tensors 2^19 0.87 / 0.87 and,
 //   R = 16, 14.1 / 18.1 us, 1e6 1.11 / 1.00), of up to 24 workers in groups whose
 //   count is no power of two to 3 * 2^18 (5x4 698304 16.2 / 21.3 us, 9 to 16 workers
-//   0.64 to 0.87 of the others, 25 and more 1.2 from 2^19), else more than 16 workers to 3 * 2^16
-//   (8x8 131072 0.50 to 0.75 / 0.68 to 0.98, 3 tensors 262144 1.27 / 0.99);
+//   0.64 to 0.87 of the others, 25 and more 1.2 from 2^19); not merged, more than
+//   16 workers to 3 * 2^16 (8x8 131072 0.50 to 0.75 / 0.68 to 0.98, 3 tensors
+//   262144 1.27 / 0.99);
 //   not merged, bfloat16 of 9 to 16 workers to 2^19 (1x4 3 tensors 2^19 12.0 /
 //   11.1, 4x4 14.6 / 17.1, 1x9 13.5 / 14.1, 1e6 21.5 / 18.0) and more than 16
 //   workers (8x8 2^19 26.5 / 44.8; binary32 35.2 / 51.3, but 1x4, one tensor, 16.8
